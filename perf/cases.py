@@ -1,0 +1,535 @@
+"""Performance cases of the particle-mesh library, through its Python binding.
+
+Each case is one call (or one whole run) as a program makes it: particle sets
+painted and turned into forces, initial conditions, runs, batches of runs,
+power spectra, transforms, the reverse sweep of a run and the pyramid force.
+Inputs are drawn on the GPU from the seed alone; ``exact`` computes the same
+outputs in float64 with plain torch and numpy.
+
+Bytes in ``work`` count each input and output of a call once, and for every
+force evaluation the four real meshes it cannot avoid (density and three
+force components), each written once and read once.
+"""
+import math
+from dataclasses import replace
+
+import numpy as np
+import torch
+
+from paper_2010_11847_amd import inputs
+from paper_2010_11847_amd.binding import PMBatch, PMContext
+
+DEV = "cuda"
+
+
+def listed():
+    return [
+        # a single force of a tiny simulation: launch latency (unit tests, interactive use)
+        dict(name="force_32", kind="force", n_mesh=32, np=32 ** 3, points="lattice", deconv=0),
+        # 32^3 / 32^3 for 10 steps: the smallest preset as a whole run
+        dict(name="run_32", kind="run", n_mesh=32, n_part=32, cell=3.125, steps=10, deconv=0, scheme=0),
+        # four 64^3 / 64^3 requests served together: the common serving class, at its mean step count
+        dict(name="batch_64", kind="batch", n_mesh=64, n_part=64, cell=2.0, steps=7, members=4),
+        # 128^3 / 256^3 for 10 steps: the ordinary run
+        dict(name="run_256", kind="run", n_mesh=256, n_part=128, cell=1.0, steps=10, deconv=0, scheme=0),
+        # 512^3 / 1024^3 for 10 steps: the largest run
+        dict(name="run_1024", kind="run", n_mesh=1024, n_part=512, cell=1.0, steps=10, deconv=0, scheme=0),
+        # force at an odd number of clustered particles in arbitrary order (a catalogue), deconvolved
+        dict(name="force_catalogue", kind="force", n_mesh=256, np=1234567, points="clustered", deconv=2),
+        # overdensity of a large unordered particle set
+        dict(name="paint_512", kind="paint", n_mesh=512, np=30000001, points="clustered"),
+        # measured power spectrum of a density mesh
+        dict(name="power_512", kind="power", n_mesh=512, n_bins=256, n_max=0, deconv=True),
+        # forward and inverse transform of a mesh
+        dict(name="fft_256", kind="fft", n_mesh=256),
+        # 2LPT initial conditions
+        dict(name="lpt_256", kind="lpt", n_mesh=512, n_part=256, cell=1.0, order=2, a0=0.1),
+        # reverse sweep of a 5-step run down to the white noise (reconstruction, variational inference)
+        dict(name="adjoint_256", kind="adjoint", n_mesh=256, n_part=128, cell=1.5625, steps=5, deconv=0),
+        # the multi-grid force of the paper
+        dict(name="pyramid_512", kind="pyramid", n_mesh=512, np=256 ** 3, points="lattice", levels=2),
+    ]
+
+
+def draw(rng):
+    known = [{k: v for k, v in c.items() if k != "name"} for c in listed()]
+    while True:
+        c = _draw(rng)
+        if c not in known:
+            return c
+
+
+def _draw(rng):
+    kind = rng.choice(["force", "run", "batch", "paint", "power", "fft", "lpt", "adjoint", "pyramid"])
+
+    def mesh(lo, hi):
+        return 1 << rng.randint(int(math.log2(lo)), int(math.log2(hi)))
+
+    def ragged(hi):
+        return int(round(math.exp(rng.uniform(math.log(50.0), math.log(float(hi))))))
+
+    points = rng.choice(["uniform", "clustered"])
+    cell = round(rng.uniform(1.0, 4.0), 3)
+    if kind in ("force", "paint"):
+        n = mesh(8, 1024)
+        c = dict(kind=kind, n_mesh=n, np=ragged(min(2 * n ** 3, 1 << 26)), points=points)
+        return dict(c, deconv=rng.randint(0, 2)) if kind == "force" else c
+    if kind == "pyramid":
+        n = mesh(64, 1024)
+        return dict(kind=kind, n_mesh=n, np=ragged(min(n ** 3, 1 << 26)), points=points, levels=rng.randint(1, 3))
+    if kind == "power":
+        n = mesh(16, 1024)
+        return dict(kind=kind, n_mesh=n, n_bins=rng.randint(n // 4, n // 2), n_max=rng.choice([0, 0, n // 4]),
+                    deconv=rng.random() < 0.5)
+    if kind == "fft":
+        return dict(kind=kind, n_mesh=mesh(8, 1024))
+    if kind == "lpt":
+        n = mesh(8, 512)
+        return dict(kind=kind, n_mesh=n * rng.choice([1, 2]), n_part=n, cell=cell, order=rng.randint(1, 2),
+                    a0=round(rng.uniform(0.05, 0.2), 3))
+    if kind == "batch":
+        n = mesh(32, 128)
+        return dict(kind=kind, n_mesh=2 * n, n_part=rng.choice([n, 2 * n]), cell=cell, steps=rng.randint(5, 10),
+                    members=rng.randint(2, 6))
+    n = mesh(32, 512) if kind == "run" else mesh(32, 256)
+    c = dict(kind=kind, n_mesh=n, n_part=n // rng.choice([1, 2, 2, 4]), cell=cell, steps=rng.randint(3, 10),
+             deconv=rng.choice([0, 0, 1, 2]))
+    return dict(c, scheme=rng.choice([0, 0, 0, inputs.INT_COLA])) if kind == "run" else c
+
+
+# ---- inputs ------------------------------------------------------------------
+def _gen(seed):
+    return torch.Generator(device=DEV).manual_seed(int(seed))
+
+
+def _wrap(x, n):
+    x = torch.remainder(x, float(n)).float()
+    return torch.where(x >= n, torch.zeros_like(x), x).contiguous()
+
+
+def _lattice(n_part, n_mesh):
+    i = torch.arange(n_part, device=DEV, dtype=torch.float32) * (n_mesh // n_part)
+    return torch.stack(torch.meshgrid(i, i, i, indexing="ij"), -1).reshape(-1, 3)
+
+
+def _points(c, seed):
+    """A perturbed lattice, uniform points, or half of them in Gaussian clumps, in arbitrary order."""
+    g, n, m = _gen(seed), c["n_mesh"], c["np"]
+    if c["points"] == "lattice":
+        q = _lattice(round(m ** (1 / 3)), n)
+        return _wrap(q + torch.randn(q.shape, generator=g, device=DEV), n)
+    x = torch.rand((m, 3), generator=g, device=DEV) * n
+    if c["points"] == "clustered":
+        clumps = max(4, m // 4096)
+        centre = torch.rand((clumps, 3), generator=g, device=DEV) * n
+        k = torch.randint(0, clumps, (m,), generator=g, device=DEV)
+        near = centre[k] + 2.0 * torch.randn((m, 3), generator=g, device=DEV)
+        x = torch.where(torch.rand((m, 1), generator=g, device=DEV) < 0.5, near, x)
+    return _wrap(x, n)
+
+
+def _delta(n, seed):
+    """Overdensity of a set of points: non-negative density with a mean of one."""
+    d = torch.randn((n, n, n), generator=_gen(seed), device=DEV).mul_(0.7).exp_()
+    return d.div_(d.mean()).sub_(1.0)
+
+
+def _a_list(c):
+    return inputs.a_linear(0.1, 1.0, c["steps"])
+
+
+def _workload(c, seed=0):
+    n_part = c.get("n_part", 8)
+    w = inputs.Workload("case", c.get("cell", 1.0) * c["n_mesh"], c["n_mesh"], n_part, seed,
+                        _a_list(c) if "steps" in c else (0.1, 1.0))
+    return replace(w, deconv_order=int(c.get("deconv", 0)) if c["kind"] != "power" else 0,
+                   lpt_order=c.get("order", 2), pyramid_levels=c.get("levels", 0), integrator=c.get("scheme", 0))
+
+
+def _trajectory(c, seed):
+    """Checkpoints of a run (positions further from the lattice with time,
+    momenta), the white noise it started from and a cotangent of its final
+    density."""
+    g, n, p = _gen(seed), c["n_mesh"], c["n_part"]
+    q = _lattice(p, n)
+    ck = torch.empty((c["steps"] + 1, 2, p ** 3, 3), device=DEV)
+    for i in range(c["steps"] + 1):
+        ck[i, 0] = _wrap(q + (0.3 + 0.4 * i) * torch.randn(q.shape, generator=g, device=DEV), n)
+        ck[i, 1] = torch.randn(q.shape, generator=g, device=DEV)
+    noise = torch.randn((p, p, p), generator=g, device=DEV)
+    return ck, noise, torch.randn((n, n, n), generator=g, device=DEV)
+
+
+def prepare(c, seed):
+    kind, n = c["kind"], c["n_mesh"]
+    s = {"case": c, "seed": int(seed)}
+    if kind in ("force", "paint", "pyramid"):
+        s["ctx"] = PMContext(_workload(c), max_particles=max(c["np"], 512))
+        s["x"] = _points(c, seed)
+    elif kind == "power":
+        s["ctx"] = PMContext(_workload(c))
+        s["delta"] = _delta(n, seed)
+    elif kind == "fft":
+        s["ctx"] = PMContext(_workload(c))
+        s["real"] = torch.randn((n, n, n), generator=_gen(seed), device=DEV)
+        s["spec"] = torch.fft.rfftn(torch.randn((n, n, n), generator=_gen(seed + 1), device=DEV)).contiguous()
+    elif kind == "lpt":
+        s["ctx"] = PMContext(_workload(c))
+    elif kind == "adjoint":
+        s["ctx"] = PMContext(_workload(c))
+        s["ckpt"], s["noise"], s["dbar"] = _trajectory(c, seed)
+    elif kind == "run":
+        s["ctx"] = PMContext(_workload(c, seed))
+        s["pos"], s["mom"] = (torch.empty((c["n_part"] ** 3, 3), device=DEV) for _ in range(2))
+        s["q"] = _lattice(c["n_part"], n)
+        if c["scheme"] == inputs.INT_COLA:
+            s["ctx"].pm_set_lpt_frame()
+    elif kind == "batch":
+        s["stream"] = torch.cuda.Stream()
+        s["stream"].wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s["stream"]):   # a plan replays one captured graph per step
+            s["plan"] = PMBatch(_workload(c, seed), c["members"], stream=s["stream"])
+            s["plan"].pm_use_graphs(True)
+            s["state"] = [[torch.empty((c["n_part"] ** 3, 3), device=DEV) for _ in range(2)]
+                          for _ in range(c["members"])]
+            s["q"] = _lattice(c["n_part"], n)
+    return s
+
+
+# ---- one pass ------------------------------------------------------------------
+def _displacement(pos, q, n):
+    """Displacement from the lattice sites, nearest image."""
+    d = pos - q
+    return d.sub_(torch.round(d / n).mul_(n))
+
+
+def run(s):
+    c, kind = s["case"], s["case"]["kind"]
+    if kind in ("force", "pyramid"):
+        return s["ctx"].pm_force(s["x"])
+    if kind == "paint":
+        return s["ctx"].pm_paint(s["x"])
+    if kind == "power":
+        return s["ctx"].pm_power(s["delta"], n_bins=c["n_bins"], n_max=c["n_max"], deconv=c["deconv"])
+    if kind == "fft":
+        return s["ctx"].pm_rfft(s["real"]), s["ctx"].pm_irfft(s["spec"])
+    if kind == "lpt":
+        return s["ctx"].pm_init_lpt(s["seed"], c["a0"])
+    if kind == "adjoint":
+        return s["ctx"].pm_run_adjoint(_a_list(c), s["ckpt"], noise=s["noise"], grad_delta=s["dbar"])
+    if kind == "run":
+        a = _a_list(c)
+        s["ctx"].pm_init_lpt(s["seed"], a[0], pos=s["pos"], mom=s["mom"])
+        s["ctx"].pm_run(a, s["pos"], s["mom"])
+        return _displacement(s["pos"], s["q"], c["n_mesh"]), s["mom"]
+    return _run_batch(s, c)
+
+
+def _run_batch(s, c):
+    a, plan, out = _a_list(c), s["plan"], []
+    s["stream"].wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s["stream"]):
+        for m, (pos, mom) in enumerate(s["state"]):
+            plan.member(m).pm_init_lpt(s["seed"] + 1000 * m, a[0], pos=pos, mom=mom)
+            plan.pm_batch_begin(m, a, pos, mom)
+        while plan.pm_batch_advance():
+            pass
+        for m, (pos, mom) in enumerate(s["state"]):
+            plan.pm_batch_end(m)
+            out.append((_displacement(pos, s["q"], c["n_mesh"]), mom))
+    torch.cuda.current_stream().wait_stream(s["stream"])
+    return out
+
+
+def work(c):
+    n3 = float(c["n_mesh"]) ** 3
+    p3 = float(c.get("n_part", 0)) ** 3
+    fft = 2.5 * n3 * math.log2(n3)                     # one real transform
+    lpt = 2.5 * p3 * math.log2(p3) if p3 else 0.0      # one real transform of the particle lattice
+    kind = c["kind"]
+    force = {"bytes": 32 * n3, "flops": 4 * fft}       # density and three force meshes, written and read
+    if kind in ("force", "pyramid"):
+        return {"bytes": force["bytes"] + 24.0 * c["np"], "flops": force["flops"] + 80.0 * c["np"]}
+    if kind == "paint":
+        return {"bytes": 4 * n3 + 12.0 * c["np"], "flops": 30.0 * c["np"]}
+    if kind == "power":
+        return {"bytes": 4 * n3, "flops": fft}
+    if kind == "fft":
+        return {"bytes": 16 * n3, "flops": 2 * fft}
+    n_lpt = 14 if c.get("order", 2) == 2 else 4
+    if kind == "lpt":
+        return {"bytes": 24 * p3, "flops": n_lpt * lpt}
+    if kind == "adjoint":   # density, force, cotangent meshes and the transposed force per checkpoint
+        k = c["steps"] + 1
+        return {"bytes": k * (2 * force["bytes"] + 12 * p3) + 4 * n3 + 32 * p3,
+                "flops": k * 2 * force["flops"] + 27 * lpt}
+    k = c["steps"] + 1
+    one = {"bytes": k * force["bytes"] + (c["steps"] * 48 + 24) * p3,
+           "flops": k * (force["flops"] + 80 * p3) + n_lpt * lpt}
+    return {x: v * c.get("members", 1) for x, v in one.items()}
+
+
+# ---- the same in float64 -----------------------------------------------------------
+OM = inputs.Cosmology().omega_m
+
+
+def _omega(n):
+    w = 2 * math.pi * torch.fft.fftfreq(n, device=DEV, dtype=torch.float64)
+    wz = 2 * math.pi * torch.fft.rfftfreq(n, device=DEV, dtype=torch.float64)
+    return w[:, None, None], w[None, :, None], wz[None, None, :]
+
+
+def _grad(w):
+    return (8 * torch.sin(w) - torch.sin(2 * w)) / 6
+
+
+def _inv_laplace(ws):
+    k2 = sum((2 * torch.sin(w / 2)) ** 2 for w in ws)
+    return torch.where(k2 > 0, 1 / torch.where(k2 > 0, k2, 1.0), 0.0)
+
+
+def _window(ws):
+    out = 1.0
+    for w in ws:
+        out = out * torch.sinc(w / (2 * math.pi)) ** 2
+    return out
+
+
+def _corners(x, n):
+    i = torch.floor(x.detach())
+    t, i = x - i, i.long() % n
+    for o in range(8):
+        e = (o & 1, o >> 1 & 1, o >> 2)
+        w, idx = 1.0, 0
+        for d in range(3):
+            w = w * (t[:, d] if e[d] else 1 - t[:, d])
+            idx = idx * n + (i[:, d] + e[d]) % n
+        yield idx, w
+
+
+def _paint64(x, n):
+    rho = torch.zeros(n ** 3, device=DEV, dtype=torch.float64)
+    for idx, w in _corners(x, n):
+        rho = rho.index_add(0, idx, w)
+    return (rho * (n ** 3 / x.shape[0]) - 1).reshape(n, n, n)
+
+
+def _force_meshes64(delta, deconv=0):
+    n = delta.shape[0]
+    ws = _omega(n)
+    dk = torch.fft.rfftn(delta) * (1.5 * OM * _inv_laplace(ws))
+    if deconv:
+        dk = dk / _window(ws) ** deconv
+    return [torch.fft.irfftn(dk * (1j * _grad(w)), s=(n, n, n)) for w in ws]
+
+
+def _reduce64(f, levels):
+    k = [1 / 64, 6 / 64, 15 / 64, 20 / 64, 15 / 64, 6 / 64, 1 / 64]
+    for _ in range(levels):
+        for ax in range(3):
+            f = sum(kt * torch.roll(f, 3 - t, ax) for t, kt in enumerate(k))
+            f = f.index_select(ax, torch.arange(0, f.shape[ax], 2, device=DEV))
+    return f
+
+
+def _expand64(f, levels):
+    k = [1 / 32, 6 / 32, 15 / 32, 20 / 32, 15 / 32, 6 / 32, 1 / 32]
+    for _ in range(levels):
+        for ax in range(3):
+            shape = list(f.shape)
+            shape[ax] *= 2
+            up = torch.zeros(shape, device=DEV, dtype=f.dtype)
+            up = up.index_copy(ax, torch.arange(0, shape[ax], 2, device=DEV), f)
+            f = sum(kt * torch.roll(up, 3 - t, ax) for t, kt in enumerate(k))
+    return f
+
+
+def _pyramid64(delta, levels):
+    long = _force_meshes64(_reduce64(delta, levels))
+    short = _force_meshes64(delta)
+    return [s + _expand64(2.0 ** levels * f - _reduce64(s, levels), levels) for f, s in zip(long, short)]
+
+
+def _read64(meshes, x):
+    n = meshes[0].shape[0]
+    flat = [m.reshape(-1) for m in meshes]
+    out = [0.0] * len(flat)
+    for idx, w in _corners(x, n):
+        out = [o + w * f[idx] for o, f in zip(out, flat)]
+    return torch.stack(out, 1)
+
+
+def _force64(x, n, deconv=0):
+    return _read64(_force_meshes64(_paint64(x, n), deconv), x)
+
+
+def _growth64(a_sorted):
+    """{a: (D1, f1 D1, D2, f2 D2, E)} for flat LCDM, D1(1) = 1 (Runge-Kutta in ln a)."""
+    def rhs(l, y):
+        m = OM / math.exp(3 * l)
+        om = m / (m + 1 - OM)
+        h = 2 - 1.5 * om
+        return np.array([y[1], -h * y[1] + 1.5 * om * y[0], y[3], -h * y[3] + 1.5 * om * (y[2] - y[0] ** 2)])
+    pts = sorted(set(a_sorted) | {1.0})
+    l, y, out = math.log(1e-5), np.array([1e-5, 1e-5, -3e-10 / 7, -6e-10 / 7]), {}
+    for a in pts:
+        steps = max(1, int(math.ceil((math.log(a) - l) / 2e-3)))
+        h = (math.log(a) - l) / steps
+        for _ in range(steps):
+            k1 = rhs(l, y)
+            k2 = rhs(l + h / 2, y + h / 2 * k1)
+            k3 = rhs(l + h / 2, y + h / 2 * k2)
+            k4 = rhs(l + h, y + h * k3)
+            y, l = y + h / 6 * (k1 + 2 * k2 + 2 * k3 + k4), l + h
+        out[a] = (y[0], y[1], y[2], y[3], math.sqrt(OM / a ** 3 + 1 - OM))
+    d = out[1.0][0]
+    return {a: (v[0] / d, v[1] / d, v[2] / d ** 2, v[3] / d ** 2, v[4]) for a, v in out.items()}
+
+
+def _factors64(a):
+    """Kick, drift, kick of every step (exact for linear growth)."""
+    half = [math.sqrt(x * y) for x, y in zip(a[:-1], a[1:])]
+    g = _growth64(list(a) + half)
+    gf = {x: x ** 2 * v[4] * v[1] for x, v in g.items()}
+    return [((gf[h] - gf[x]) / (1.5 * OM * g[x][0]), (g[y][0] - g[x][0]) / gf[h], (gf[y] - gf[h]) / (1.5 * OM * g[y][0]))
+            for x, h, y in zip(a[:-1], half, a[1:])]
+
+
+def _linear_power64(k):
+    """Eisenstein & Hu (1998) zero-wiggle P(k), normalised to sigma8."""
+    p = inputs.Cosmology()
+
+    def shape(k):
+        omh2, obh2, fb = p.omega_m * p.h ** 2, p.omega_b * p.h ** 2, p.omega_b / p.omega_m
+        s = 44.5 * math.log(9.83 / omh2) / math.sqrt(1 + 10 * obh2 ** 0.75)
+        al = 1 - 0.328 * math.log(431 * omh2) * fb + 0.38 * math.log(22.3 * omh2) * fb ** 2
+        q = k * (p.t_cmb / 2.7) ** 2 / (p.omega_m * p.h * (al + (1 - al) / (1 + (0.43 * k * p.h * s) ** 4)))
+        l0 = np.log(2 * math.e + 1.8 * q)
+        return k ** p.n_s * (l0 / (l0 + (14.2 + 731 / (1 + 62.5 * q)) * q ** 2)) ** 2
+    lk = np.linspace(math.log(1e-5), math.log(1e2), 400001)
+    kk = np.exp(lk)
+    x = 8 * kk
+    win = np.where(x < 1e-2, 1 - x ** 2 / 10, 3 * (np.sin(x) - x * np.cos(x)) / x ** 3)
+    f = kk ** 3 * shape(kk) * win ** 2 / (2 * math.pi ** 2)
+    s2 = float(np.sum((f[1:] + f[:-1]) / 2) * (lk[1] - lk[0]))
+    return p.sigma8 ** 2 / s2 * shape(k)
+
+
+def _noise64(seed, n):
+    """SplitMix64 of seed 2^40 + site, Box-Muller (cosine branch)."""
+    def signed(v):
+        v &= (1 << 64) - 1
+        return v - (1 << 64) if v >> 63 else v
+
+    def shr(z, b):
+        return (z >> b) & ((1 << (64 - b)) - 1)
+    z = torch.arange(n ** 3, device=DEV) + signed(seed * (1 << 40) + 0x9E3779B97F4A7C15)
+    z = (z ^ shr(z, 30)) * signed(0xBF58476D1CE4E5B9)
+    z = (z ^ shr(z, 27)) * signed(0x94D049BB133111EB)
+    z = z ^ shr(z, 31)
+    u1, u2 = (shr(z, 32).double() + 1) * 2.0 ** -32, (z & 0xFFFFFFFF).double() * 2.0 ** -32
+    return (torch.sqrt(-2 * torch.log(u1)) * torch.cos(2 * math.pi * u2)).reshape(n, n, n)
+
+
+def _lpt64(noise, c, a0):
+    """(unwrapped positions, momenta) of the Gen-IC start."""
+    n, b = c["n_part"], c["n_mesh"] // c["n_part"]
+    box = c["cell"] * c["n_mesh"]
+    ws = _omega(n)
+    n2 = sum((w * (n / (2 * math.pi))) ** 2 for w in ws).round().long()
+    pk = np.zeros(3 * (n // 2) ** 2 + 1)
+    pk[1:] = _linear_power64(2 * math.pi * np.sqrt(np.arange(1, len(pk))) / box)
+    amp = torch.from_numpy(np.sqrt(pk / (box / n) ** 3)).to(DEV)[n2]
+    inv, dk = _inv_laplace(ws), torch.fft.rfftn(noise) * amp
+    d = [_grad(w) for w in ws]
+    back = lambda f: torch.fft.irfftn(f, s=(n, n, n))  # noqa: E731
+    s1 = torch.stack([back(1j * w * inv * dk) for w in d], -1).reshape(-1, 3)
+    s2 = torch.zeros_like(s1)
+    if c.get("order", 2) == 2:
+        p = {(i, j): back(d[i] * d[j] * inv * dk) for i in range(3) for j in range(i, 3)}
+        d2 = sum(p[i, i] * p[j, j] - p[i, j] ** 2 for i in range(3) for j in range(i + 1, 3))
+        d2k = torch.fft.rfftn(d2)
+        s2 = torch.stack([back(-1j * w * inv * d2k) for w in d], -1).reshape(-1, 3)
+    d1, f1, dd2, f2, e = _growth64([a0])[a0]
+    return (_lattice(n, c["n_mesh"]).double() + b * (d1 * s1 + dd2 * s2), b * a0 ** 2 * e * (f1 * s1 + f2 * s2))
+
+
+def _run64(c, seed):
+    a, n = _a_list(c), c["n_mesh"]
+    x, p = _lpt64(_noise64(seed, c["n_part"]), c, a[0])
+    f = _force64(x, n, c.get("deconv", 0))
+    for k1, dr, k2 in _factors64(a):
+        p = p + k1 * f
+        x = torch.remainder(x + dr * p, n)
+        f = _force64(x, n, c.get("deconv", 0))
+        p = p + k2 * f
+    return _displacement(x, _lattice(c["n_part"], n).double(), n), p
+
+
+def _adjoint64(c, seed):
+    ck, noise, dbar = _trajectory(c, seed)
+    a, n, fac = _a_list(c), c["n_mesh"], _factors64(_a_list(c))
+    ns = c["steps"]
+
+    def vjp(fn, x, cot):
+        x = x.double().requires_grad_(True)
+        return torch.autograd.grad((fn(x) * cot).sum(), x)[0]
+    xb = vjp(lambda x: _paint64(x, n), ck[ns, 0], dbar.double())
+    pb = torch.zeros_like(xb)
+    for j in range(ns, -1, -1):
+        kj = (fac[j][0] if j < ns else 0.0) + (fac[j - 1][2] if j else 0.0)
+        xb = xb + vjp(lambda x: _force64(x, n, c["deconv"]), ck[j, 0], kj * pb)
+        if j:
+            pb = pb + fac[j - 1][1] * xb
+    w = noise.double().requires_grad_(True)
+    x, p = _lpt64(w, c, a[0])
+    return xb, pb, torch.autograd.grad((x * xb).sum() + (p * pb).sum(), w)[0]
+
+
+def _power64(delta, c):
+    n, box = c["n_mesh"], float(c["n_mesh"])
+    ws = _omega(n)
+    dk = torch.fft.rfftn(delta.double())
+    p = dk.real ** 2 + dk.imag ** 2
+    if c["deconv"]:
+        p = p / _window(ws) ** 2
+    f = [(w * (n / (2 * math.pi))).round() for w in ws]
+    mag = torch.sqrt(sum(v ** 2 for v in f))
+    wt = torch.full_like(mag, 2.0)
+    wt[:, :, 0] = wt[:, :, -1] = 1.0
+    if c["n_max"]:
+        for v in f:
+            wt = wt * (v.abs() < c["n_max"])
+    j = torch.floor(mag + 0.5).long()
+    wt = torch.where((j >= 1) & (j <= c["n_bins"]), wt, 0.0).reshape(-1)
+    j = torch.clamp(j, max=c["n_bins"]).reshape(-1)
+
+    def binned(v):
+        return torch.bincount(j, weights=wt * v, minlength=c["n_bins"] + 1)[1:].cpu().numpy()
+    sw, sk, sp = binned(torch.ones_like(wt)), binned(mag.reshape(-1)), binned(p.reshape(-1))
+    full = np.maximum(sw, 1.0)
+    return sk / full * 2 * math.pi / box, sp / full * box ** 3 / float(n) ** 6, sw
+
+
+def exact(c, seed):
+    kind, n = c["kind"], c["n_mesh"]
+    if kind == "force":
+        return _force64(_points(c, seed).double(), n, c["deconv"])
+    if kind == "paint":
+        return _paint64(_points(c, seed).double(), n)
+    if kind == "pyramid":
+        x = _points(c, seed).double()
+        return _read64(_pyramid64(_paint64(x, n), c["levels"]), x)
+    if kind == "power":
+        return _power64(_delta(n, seed), c)
+    if kind == "fft":
+        s = prepare(c, seed)
+        return torch.fft.rfftn(s["real"].double()), torch.fft.irfftn(s["spec"].to(torch.complex128), s=(n, n, n))
+    if kind == "lpt":
+        x, p = _lpt64(_noise64(seed, c["n_part"]), c, c["a0"])
+        return torch.remainder(x, n), p
+    if kind == "adjoint":
+        return _adjoint64(c, seed)
+    if kind == "run":   # the largest takes too long; the LPT-frame scheme has no plain form here
+        return _run64(c, seed) if n < 1024 and c["scheme"] == 0 else None
+    return [_run64(c, seed + 1000 * m) for m in range(c["members"])]
