@@ -77,8 +77,8 @@ def _draw(rng):
     if kind == "pyramid":
         n = mesh(64, 1024)
         return dict(kind=kind, n_mesh=n, np=ragged(min(n ** 3, 1 << 26)), points=points, levels=rng.randint(1, 3))
-    if kind == "power":
-        n = mesh(16, 1024)
+    if kind == "power":   # below 64^3 a bin holds too few modes to be measured in earnest
+        n = mesh(64, 1024)
         return dict(kind=kind, n_mesh=n, n_bins=rng.randint(n // 4, n // 2), n_max=rng.choice([0, 0, n // 4]),
                     deconv=rng.random() < 0.5)
     if kind == "fft":
