@@ -451,21 +451,17 @@ struct pm_ctx {
     op.scale = (float)scale;
     op.deconv = deconv;
     op.split = split;
-    // from 64^3 up F_y and F_z share one x transform (i g X) and get their
-    // D(w_y), D(w_z) in the y pass; smaller meshes take the fused x pass
-    const bool xs = n >= 64;
-    op.kind = xs ? pmk::OP_FORCE_XS : pmk::OP_FORCE;
-    op.n_out = xs ? 2 : 3;
-    const int dst[3] = {0, xs ? 2 : 1, 2};
+    // F_y and F_z share one x transform (i g X) and get their D(w_y), D(w_z)
+    // in the y pass
+    op.kind = pmk::OP_FORCE_XS;
+    op.n_out = 2;
+    const int dst[2] = {0, 2};
     for (int i = 0; i < op.n_out; ++i) {
       op.out_c[i] = f[dst[i]].c();
       op.out_q[i] = f[dst[i]].q;
     }
     tm_(PC_FFT_X_FORCE, [&] { pmk::fft_x_force(t, f[0], op, stream, bat); });
-    if (xs)
-      tm_(PC_FFT_Y_INV, [&] { pmk::fft_y_force(t, f, stream, bat); });
-    else
-      tm_(PC_FFT_Y_INV, [&] { pmk::fft_y(t, f, 3, 1, stream); });   // below 64^3: never batched
+    tm_(PC_FFT_Y_INV, [&] { pmk::fft_y_force(t, f, stream, bat); });
     tm_(PC_FFT_C2R_Z, [&] { pmk::fft_z_c2r_interleaved3(t, f, out, stream, bat); });
   }
 

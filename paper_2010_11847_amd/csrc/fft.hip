@@ -113,19 +113,32 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
   }
 }
 
+// Stages of the column passes.  Every size takes two: with a whole column of
+// N <= 32 in one thread, 16 lanes of a workgroup's 256 worked on a chain of
+// 32-point transforms (two 12.5 us x passes at 32^3, whose data is 0.1 us of
+// HBM time; the two-stage force x pass takes 5.1 us).
 template <int N> struct Split;
-template <> struct Split<4> { static constexpr int R1 = 4, R2 = 1; };
-template <> struct Split<8> { static constexpr int R1 = 8, R2 = 1; };
-template <> struct Split<16> { static constexpr int R1 = 16, R2 = 1; };
-template <> struct Split<32> { static constexpr int R1 = 32, R2 = 1; };
+template <> struct Split<8> { static constexpr int R1 = 4, R2 = 2; };
+template <> struct Split<16> { static constexpr int R1 = 4, R2 = 4; };
+template <> struct Split<32> { static constexpr int R1 = 8, R2 = 4; };
 template <> struct Split<64> { static constexpr int R1 = 8, R2 = 8; };
 template <> struct Split<128> { static constexpr int R1 = 16, R2 = 8; };
 template <> struct Split<256> { static constexpr int R1 = 16, R2 = 16; };
 template <> struct Split<512> { static constexpr int R1 = 32, R2 = 16; };
 template <> struct Split<1024> { static constexpr int R1 = 32, R2 = 32; };
 
-// Columns per workgroup tile of the strided passes.
-template <int N> struct Cols { static constexpr int M = N >= 1024 ? 8 : 16; };
+// Stages of a z line of H complex values: lines are many, so up to 32 points
+// stay in one thread's registers.
+template <int H> struct ZSplit {
+  static constexpr int R1 = H <= 32 ? H : Split<H>::R1, R2 = H / R1;
+};
+template <> struct ZSplit<4> { static constexpr int R1 = 4, R2 = 1; };
+template <> struct ZSplit<8> { static constexpr int R1 = 8, R2 = 1; };
+template <> struct ZSplit<16> { static constexpr int R1 = 16, R2 = 1; };
+template <> struct ZSplit<32> { static constexpr int R1 = 32, R2 = 1; };
+
+// Columns per workgroup tile of the strided passes (at most the N/2 of a row).
+template <int N> struct Cols { static constexpr int M = N >= 1024 ? 8 : (N >= 32 ? 16 : N / 2); };
 
 // Tile of a y pass (columns of 8-byte values, rows 4N values apart): 16
 // columns fill each row's 128-byte line, so that no line is written half by
@@ -195,7 +208,7 @@ struct ColLds {
   // exchange of the fused pass uses [l1'][l1][m] (R2 x R1)
   static constexpr int SA = R2 * M + M;
   static constexpr int SB = R1 * M + M;
-  static constexpr int size = (R2 > 1) ? (R1 * SA > R2 * SB ? R1 * SA : R2 * SB) : 1;
+  static constexpr int size = R1 * SA > R2 * SB ? R1 * SA : R2 * SB;
 };
 
 // One launch covers the main arrays (tiles [0, nb_main)) and the Nyquist
@@ -228,51 +241,35 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
   float2* base = data + b * g.sb + (long)c0 * CS;
   const int tid = threadIdx.x;
 
-  if constexpr (R2 == 1) {
+  constexpr int SA = ColLds<N, M>::SA;
 #pragma unroll
-    for (int i = 0; i < IA; ++i) {
-      const int it = tid + i * TH;
-      const int m = it % M;
-      if (it < M && c0 + m < g.ncols) {
-        float2 v[R1];
+  for (int i = 0; i < IA; ++i) {
+    const int it = tid + i * TH;
+    if (it < M * R2) {
+      const int m = it % M, j2 = it / M;
+      const bool ok = c0 + m < g.ncols;
+      float2 v[R1];
 #pragma unroll
-        for (int j = 0; j < R1; ++j) v[j] = base[row_off<BLK>(j, g.sn) + m * CS];
-        dft<R1, DIR>(v);
+      for (int j1 = 0; j1 < R1; ++j1)
+        v[j1] = ok ? base[row_off<BLK>(R2 * j1 + j2, g.sn) + m * CS] : make_float2(0.f, 0.f);
+      dft<R1, DIR>(v);
 #pragma unroll
-        for (int j = 0; j < R1; ++j) base[row_off<BLK>(j, g.sn) + m * CS] = v[j];
-      }
+      for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<DIR>(tw, j2 * l1));
     }
-  } else {
-    constexpr int SA = ColLds<N, M>::SA;
+  }
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < IA; ++i) {
-      const int it = tid + i * TH;
-      if (it < M * R2) {
-        const int m = it % M, j2 = it / M;
-        const bool ok = c0 + m < g.ncols;
-        float2 v[R1];
+  for (int i = 0; i < IB; ++i) {
+    const int it = tid + i * TH;
+    if (it < M * R1) {
+      const int m = it % M, l1 = it / M;
+      float2 v[R2];
 #pragma unroll
-        for (int j1 = 0; j1 < R1; ++j1)
-          v[j1] = ok ? base[row_off<BLK>(R2 * j1 + j2, g.sn) + m * CS] : make_float2(0.f, 0.f);
-        dft<R1, DIR>(v);
+      for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
+      dft<R2, DIR>(v);
+      if (c0 + m < g.ncols) {
 #pragma unroll
-        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<DIR>(tw, j2 * l1));
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < IB; ++i) {
-      const int it = tid + i * TH;
-      if (it < M * R1) {
-        const int m = it % M, l1 = it / M;
-        float2 v[R2];
-#pragma unroll
-        for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
-        dft<R2, DIR>(v);
-        if (c0 + m < g.ncols) {
-#pragma unroll
-          for (int l2 = 0; l2 < R2; ++l2) base[row_off<BLK>(l1 + R1 * l2, g.sn) + m * CS] = v[l2];
-        }
+        for (int l2 = 0; l2 < R2; ++l2) base[row_off<BLK>(l1 + R1 * l2, g.sn) + m * CS] = v[l2];
       }
     }
   }
@@ -292,7 +289,6 @@ __global__ __launch_bounds__(TH) void k_fft_cols_force(ColPass p, const float2* 
                                                              const float* __restrict__ dy_tab,
                                                              const float* __restrict__ dz_tab) {
   constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
-  static_assert(R2 > 1, "columns split over two stages");
   constexpr int IA = (M * R2 + TH - 1) / TH;
   constexpr int IB = (M * R1 + TH - 1) / TH;
   constexpr int SA = ColLds<N, M>::SA;
@@ -408,7 +404,7 @@ template <int N, int LINES>
 struct ZGeomL {
   static constexpr int NN = N;
   static constexpr int H = N / 2;
-  static constexpr int R1 = Split<H>::R1, R2 = Split<H>::R2;
+  static constexpr int R1 = ZSplit<H>::R1, R2 = ZSplit<H>::R2;
   static constexpr int L = LINES;
   static constexpr int LP = L + 1;                          // padded line stride of the exchange
   // padded natural-order Z: a row stride of 4 (mod 32) float2 puts lanes
@@ -692,7 +688,7 @@ struct FusedArgs {
   SpecOp op;
   ColGeom gm, gp;          // main array (mode 0) and Nyquist plane (mode 1)
   int nb_main;
-  int pbasis;              // the power of D(w_x) this launch handles (N > 32)
+  int pbasis;              // the power of D(w_x) this launch handles
   int first, last;         // fan-in: first / last basis launch of the op
   float2* park_main;       // fan-in: x-spectrum partial sum between launches
   float2* park_nyq;
@@ -714,7 +710,11 @@ __device__ __forceinline__ int sfreq(int n) { return n < N / 2 ? n : n - N; }
 // with the x transform, a fan-out op needs one inverse x transform per
 // distinct power p (force: 2, LPT: 3) and every output is a scaled copy of
 // one of them; a fan-in op (a transpose) combines its inputs of equal power
-// before one forward x transform each.
+// before one forward x transform each.  (The force ops run in kernels of
+// their own below.  Their rows stay in this switch and in common_factor's:
+// without them the compiler fuses other products of this pass, and a run
+// amplifies the changed last bits of its initial conditions to 1e-3 of a
+// momentum.)
 struct Term {
   int p;       // power of D(w_x)
   int sel;     // 0: 1, 1: D_y, 2: D_z, 3: D_y^2, 4: D_z^2, 5: D_y D_z
@@ -832,221 +832,158 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
     dz = t.dz[kz];
   };
 
-  if constexpr (R2 == 1) {
-    // N <= 32: a whole column fits in one thread's registers
+  // forward x transform of one (combined) input into X[item][l2], kx = l1 + R1*l2;
+  // the multiplied spectrum Y reuses the same registers
+  float2 X[IB][R2];
+  float2 (&Y)[IB][R2] = X;
+  auto forward = [&](int p) {
 #pragma unroll
     for (int i = 0; i < IA; ++i) {
-      const int m = tid + i * kThreads;
-      if (m < M && c0 + m < g.ncols) {
-        int ky, kz;
-        freq(m, ky, kz);
-        float dy, dz;
-        col_d(m, dy, dz);
-        float2 X[R1], Y[R1];
-#pragma unroll
-        for (int j = 0; j < R1; ++j) Y[j] = make_float2(0.f, 0.f);
+      const int it = tid + i * kThreads;
+      if (it < M * R2) {
+        const int m = it % M, j2 = it / M;
+        const bool ok = c0 + m < g.ncols;
+        float2 v[R1];
         if (FANIN) {
-          for (int p = 0; p < 3; ++p) {
-            if (!(pmask >> p & 1)) continue;
+          float dy, dz;
+          col_d(m, dy, dz);
 #pragma unroll
-            for (int j = 0; j < R1; ++j) X[j] = make_float2(0.f, 0.f);
-            for (int in = 0; in < nterm; ++in) {
-              const Term tm = op_term(kind, in);
-              if (tm.p != p) continue;
-              const float2 cf = coef_of(tm, dy, dz);
-              const float2* src = src_of(in);
+          for (int j1 = 0; j1 < R1; ++j1) v[j1] = make_float2(0.f, 0.f);
+#pragma unroll 1
+          for (int in = 0; in < nterm; ++in) {
+            const Term tm = op_term(kind, in);
+            if (tm.p != p || !ok) continue;
+            const float2 cf = coef_of(tm, dy, dz);
+            const float2* src = src_of(in);
 #pragma unroll
-              for (int j = 0; j < R1; ++j) X[j] = cadd(X[j], cmul(src[row_off<true>(j, g.sn) + m * 8], cf));
-            }
-            dft<R1, -1>(X);
-#pragma unroll
-            for (int kx = 0; kx < R1; ++kx) Y[kx] = cadd(Y[kx], cscale(X[kx], powp(t.dxy[kx], p)));
+            for (int j1 = 0; j1 < R1; ++j1) v[j1] = cadd(v[j1], cmul(src[row_off<true>(R2 * j1 + j2, g.sn) + m * 8], cf));
           }
-#pragma unroll
-          for (int kx = 0; kx < R1; ++kx) Y[kx] = cscale(Y[kx], common_factor<N>(op, t, kx, ky, kz));
-          dft<R1, 1>(Y);
-          float2* dst = dst_of(0);
-#pragma unroll
-          for (int j = 0; j < R1; ++j) dst[row_off<true>(j, g.sn) + m * 8] = Y[j];
         } else {
           const float2* src = src_of(0);
 #pragma unroll
-          for (int j = 0; j < R1; ++j) X[j] = src[row_off<true>(j, g.sn) + m * 8];
-          dft<R1, -1>(X);
+          for (int j1 = 0; j1 < R1; ++j1) v[j1] = ok ? src[row_off<true>(R2 * j1 + j2, g.sn) + m * 8] : make_float2(0.f, 0.f);
+        }
+        dft<R1, -1>(v);
 #pragma unroll
-          for (int kx = 0; kx < R1; ++kx) X[kx] = cscale(X[kx], common_factor<N>(op, t, kx, ky, kz));
-          {
-            const int p = a.pbasis;
+        for (int l1 = 0; l1 < R1; ++l1)
+          lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<-1>(t.tw_n, j2 * l1));
+      }
+    }
+    __syncthreads();
 #pragma unroll
-            for (int kx = 0; kx < R1; ++kx) Y[kx] = cscale(X[kx], powp(t.dxy[kx], p));
-            dft<R1, 1>(Y);
+    for (int i = 0; i < IB; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R1) {
+        const int m = it % M, l1 = it / M;
+#pragma unroll
+        for (int j2 = 0; j2 < R2; ++j2) X[i][j2] = lds[l1 * SA + j2 * M + m];
+        dft<R2, -1>(X[i]);
+      }
+    }
+    __syncthreads();
+  };
+  // inverse x transform of Y (spectral, item layout) and store with the
+  // coefficients of every output term of power p (fan-in: output 0)
+  auto inverse_store = [&](int p) {
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R1) {
+        const int m = it % M, l1 = it / M;
+        dft<R2, 1>(Y[i]);   // in place: Y is rebuilt before the next use
+#pragma unroll
+        for (int lp = 0; lp < R2; ++lp)
+          lds[lp * SB + l1 * M + m] = lp == 0 ? Y[i][lp] : cmul(Y[i][lp], tw_get<1>(t.tw_n, l1 * lp));
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R2) {
+        const int m = it % M, lp = it / M;
+        float2 v[R1];
+#pragma unroll
+        for (int l1 = 0; l1 < R1; ++l1) v[l1] = lds[lp * SB + l1 * M + m];
+        dft<R1, 1>(v);
+        if (c0 + m < g.ncols) {
+          if (FANIN) {
+            float2* dst = dst_of(0);
+#pragma unroll
+            for (int l2p = 0; l2p < R1; ++l2p) dst[row_off<true>(lp + R2 * l2p, g.sn) + m * 8] = v[l2p];
+          } else {
+            float dy, dz;
+            col_d(m, dy, dz);
+#pragma unroll 1
             for (int o = 0; o < nterm; ++o) {
               const Term tm = op_term(kind, o);
               if (tm.p != p) continue;
               const float2 cf = coef_of(tm, dy, dz);
               float2* dst = dst_of(o);
 #pragma unroll
-              for (int j = 0; j < R1; ++j) dst[row_off<true>(j, g.sn) + m * 8] = cmul(Y[j], cf);
+              for (int l2p = 0; l2p < R1; ++l2p) dst[row_off<true>(lp + R2 * l2p, g.sn) + m * 8] = cmul(v[l2p], cf);
             }
           }
         }
       }
     }
-    return;
-  } else {
-    // forward x transform of one (combined) input into X[item][l2], kx = l1 + R1*l2;
-    // the multiplied spectrum Y reuses the same registers
-    float2 X[IB][R2];
-    float2 (&Y)[IB][R2] = X;
-    auto forward = [&](int p) {
-#pragma unroll
-      for (int i = 0; i < IA; ++i) {
-        const int it = tid + i * kThreads;
-        if (it < M * R2) {
-          const int m = it % M, j2 = it / M;
-          const bool ok = c0 + m < g.ncols;
-          float2 v[R1];
-          if (FANIN) {
-            float dy, dz;
-            col_d(m, dy, dz);
-#pragma unroll
-            for (int j1 = 0; j1 < R1; ++j1) v[j1] = make_float2(0.f, 0.f);
-#pragma unroll 1
-            for (int in = 0; in < nterm; ++in) {
-              const Term tm = op_term(kind, in);
-              if (tm.p != p || !ok) continue;
-              const float2 cf = coef_of(tm, dy, dz);
-              const float2* src = src_of(in);
-#pragma unroll
-              for (int j1 = 0; j1 < R1; ++j1) v[j1] = cadd(v[j1], cmul(src[row_off<true>(R2 * j1 + j2, g.sn) + m * 8], cf));
-            }
-          } else {
-            const float2* src = src_of(0);
-#pragma unroll
-            for (int j1 = 0; j1 < R1; ++j1) v[j1] = ok ? src[row_off<true>(R2 * j1 + j2, g.sn) + m * 8] : make_float2(0.f, 0.f);
-          }
-          dft<R1, -1>(v);
-#pragma unroll
-          for (int l1 = 0; l1 < R1; ++l1)
-            lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<-1>(t.tw_n, j2 * l1));
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        const int it = tid + i * kThreads;
-        if (it < M * R1) {
-          const int m = it % M, l1 = it / M;
-#pragma unroll
-          for (int j2 = 0; j2 < R2; ++j2) X[i][j2] = lds[l1 * SA + j2 * M + m];
-          dft<R2, -1>(X[i]);
-        }
-      }
-      __syncthreads();
-    };
-    // inverse x transform of Y (spectral, item layout) and store with the
-    // coefficients of every output term of power p (fan-in: output 0)
-    auto inverse_store = [&](int p) {
-#pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        const int it = tid + i * kThreads;
-        if (it < M * R1) {
-          const int m = it % M, l1 = it / M;
-          dft<R2, 1>(Y[i]);   // in place: Y is rebuilt before the next use
-#pragma unroll
-          for (int lp = 0; lp < R2; ++lp)
-            lds[lp * SB + l1 * M + m] = lp == 0 ? Y[i][lp] : cmul(Y[i][lp], tw_get<1>(t.tw_n, l1 * lp));
-        }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < IA; ++i) {
-        const int it = tid + i * kThreads;
-        if (it < M * R2) {
-          const int m = it % M, lp = it / M;
-          float2 v[R1];
-#pragma unroll
-          for (int l1 = 0; l1 < R1; ++l1) v[l1] = lds[lp * SB + l1 * M + m];
-          dft<R1, 1>(v);
-          if (c0 + m < g.ncols) {
-            if (FANIN) {
-              float2* dst = dst_of(0);
-#pragma unroll
-              for (int l2p = 0; l2p < R1; ++l2p) dst[row_off<true>(lp + R2 * l2p, g.sn) + m * 8] = v[l2p];
-            } else {
-              float dy, dz;
-              col_d(m, dy, dz);
-#pragma unroll 1
-              for (int o = 0; o < nterm; ++o) {
-                const Term tm = op_term(kind, o);
-                if (tm.p != p) continue;
-                const float2 cf = coef_of(tm, dy, dz);
-                float2* dst = dst_of(o);
-#pragma unroll
-                for (int l2p = 0; l2p < R1; ++l2p) dst[row_off<true>(lp + R2 * l2p, g.sn) + m * 8] = cmul(v[l2p], cf);
-              }
-            }
-          }
-        }
-      }
-      __syncthreads();
-    };
+    __syncthreads();
+  };
 
-    if (FANIN) {
-      // one launch per basis power p (increasing): the inputs of power p are
-      // combined and forward transformed, scaled by c(k) D(w_x)^p and added
-      // to the partial sum of the earlier bases.  The partial sum is parked
-      // in x-spectral order in this tile's region of an input of the first
-      // basis (read by this tile before it is written); the last launch
-      // inverse transforms the total into output 0.
-      const int p = a.pbasis;
-      forward(p);
-      float2* park = (mode == 0 ? a.park_main : a.park_nyq) + off;
+  if (FANIN) {
+    // one launch per basis power p (increasing): the inputs of power p are
+    // combined and forward transformed, scaled by c(k) D(w_x)^p and added
+    // to the partial sum of the earlier bases.  The partial sum is parked
+    // in x-spectral order in this tile's region of an input of the first
+    // basis (read by this tile before it is written); the last launch
+    // inverse transforms the total into output 0.
+    const int p = a.pbasis;
+    forward(p);
+    float2* park = (mode == 0 ? a.park_main : a.park_nyq) + off;
 #pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        const int it = tid + i * kThreads;
-        if (it < M * R1) {
-          const int m = it % M, l1 = it / M;
-          int ky, kz;
-          freq(m, ky, kz);
-#pragma unroll
-          for (int l2 = 0; l2 < R2; ++l2) {
-            const int kx = l1 + R1 * l2;
-            float2 v = cscale(X[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p));
-            if (!a.first && c0 + m < g.ncols) v = cadd(v, park[row_off<true>(kx, g.sn) + m * 8]);
-            Y[i][l2] = v;
-          }
-          if (!a.last && c0 + m < g.ncols) {
-#pragma unroll
-            for (int l2 = 0; l2 < R2; ++l2) park[row_off<true>(l1 + R1 * l2, g.sn) + m * 8] = Y[i][l2];
-          }
-        }
-      }
-      if (a.last) inverse_store(0);
-    } else {
-      // fan-out: this launch handles the outputs of one basis power p: the
-      // input tile is transformed, scaled by c(k) D(w_x)^p and inverse
-      // transformed.  The host launches the bases in increasing p (one
-      // launch each, so that the register arrays of one basis are all that
-      // is live); an output that aliases the input has the highest p of its
-      // op, so the input is intact for every earlier basis.
-      const int p = a.pbasis;
-      forward(0);
-#pragma unroll
-      for (int i = 0; i < IB; ++i) {
-        const int it = tid + i * kThreads;
+    for (int i = 0; i < IB; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R1) {
         const int m = it % M, l1 = it / M;
         int ky, kz;
         freq(m, ky, kz);
 #pragma unroll
         for (int l2 = 0; l2 < R2; ++l2) {
           const int kx = l1 + R1 * l2;
-          Y[i][l2] = it < M * R1 ? cscale(X[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
-                                 : make_float2(0.f, 0.f);
+          float2 v = cscale(X[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p));
+          if (!a.first && c0 + m < g.ncols) v = cadd(v, park[row_off<true>(kx, g.sn) + m * 8]);
+          Y[i][l2] = v;
+        }
+        if (!a.last && c0 + m < g.ncols) {
+#pragma unroll
+          for (int l2 = 0; l2 < R2; ++l2) park[row_off<true>(l1 + R1 * l2, g.sn) + m * 8] = Y[i][l2];
         }
       }
-      inverse_store(p);
     }
+    if (a.last) inverse_store(0);
+  } else {
+    // fan-out: this launch handles the outputs of one basis power p: the
+    // input tile is transformed, scaled by c(k) D(w_x)^p and inverse
+    // transformed.  The host launches the bases in increasing p (one
+    // launch each, so that the register arrays of one basis are all that
+    // is live); an output that aliases the input has the highest p of its
+    // op, so the input is intact for every earlier basis.
+    const int p = a.pbasis;
+    forward(0);
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int it = tid + i * kThreads;
+      const int m = it % M, l1 = it / M;
+      int ky, kz;
+      freq(m, ky, kz);
+#pragma unroll
+      for (int l2 = 0; l2 < R2; ++l2) {
+        const int kx = l1 + R1 * l2;
+        Y[i][l2] = it < M * R1 ? cscale(X[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
+                               : make_float2(0.f, 0.f);
+      }
+    }
+    inverse_store(p);
   }
 }
 
@@ -1095,7 +1032,7 @@ __device__ __forceinline__ void force_factors(const FftTables& t, const SpecOp& 
   }
 }
 
-// The force's whole x pass in one tile (OP_FORCE_XS, N >= 64): the forward
+// The force's whole x pass in one tile (OP_FORCE_XS): the forward
 // x transform, times c(k), then two inverse x transforms, each output times
 // i: D(w_x) c X into out[0] (F_x, over the input) and c X into out[1] (the
 // factor F_y and F_z share).  The forward transform leaves item (m, l1)
@@ -1109,7 +1046,6 @@ __device__ __forceinline__ void force_factors(const FftTables& t, const SpecOp& 
 template <int N, int M>
 __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
   constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
-  static_assert(R2 > 1, "columns split over two stages");
   constexpr int IA = (M * R2 + kThreads - 1) / kThreads;   // forward stage A, inverse stage B
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;   // forward stage B, inverse stage A
   constexpr int SA = ColLds<N, M>::SA, SB = ColLds<N, M>::SB;
@@ -1246,7 +1182,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
 }
 
 
-// The transposed force's whole x pass (OP_FORCE_T, N >= 64) in one tile:
+// The transposed force's whole x pass (OP_FORCE_T) in one tile:
 // with Y_d the forward-(z, y) spectra of the three painted channels, the
 // result is the inverse x transform of -i g(k) times the forward x
 // transform of
@@ -1264,7 +1200,6 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
 template <int N, int M, bool FILT>
 __global__ __launch_bounds__(kThreads) void k_fft_x_force_t(FusedArgs a) {
   constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
-  static_assert(R2 > 1, "columns split over two stages");
   static_assert(N * M <= ColLds<N, M>::size, "the staging copy fits the exchange buffer");
   constexpr int IA = (M * R2 + kThreads - 1) / kThreads;   // forward stage A, inverse stage B
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;   // forward stage B, inverse stage A
@@ -1510,10 +1445,6 @@ void xfused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s
   const int nterm = fan_in ? op.n_in : op.n_out;
   int pmask = 0, first_in = -1;
   for (int o = 0; o < nterm; ++o) pmask |= 1 << op_term(op.kind, o).p;
-  if (fan_in && Split<N>::R2 == 1) {   // whole columns in registers: all bases in one launch
-    hipLaunchKernelGGL((k_fft_x_fused<N, M, true>), grid, dim3(kThreads), 0, s, a);
-    return;
-  }
   const int pfirst = __builtin_ctz(pmask), plast = 31 - __builtin_clz(pmask);
   if (fan_in) {
     for (int o = 0; o < nterm && first_in < 0; ++o)
@@ -1533,31 +1464,25 @@ void xfused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s
   }
 }
 
-// The force's x pass: for N >= 64 (OP_FORCE_XS) one launch of
-// k_fft_x_force, for N <= 32 (OP_FORCE, whole columns in registers) the
-// fused register pass.
+// The force's x pass: one launch of k_fft_x_force.
 template <int N>
 void xforce(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s, const BatchArg& bat = BatchArg()) {
   constexpr int M = Cols<N>::M;
-  if constexpr (Split<N>::R2 == 1) {
-    xfused<N>(t, in, op, s);
-  } else {
-    FusedArgs a;
-    a.op = op;
-    a.t = t;
-    a.in_main = in.c();
-    a.in_nyq = in.q;
-    a.gm = ColGeom{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)};
-    a.gp = ColGeom{0, 8L * N, N, cdiv(N, M)};
-    a.nb_main = N * a.gm.ntc;
-    a.first = a.last = 1;
-    a.park_main = nullptr;
-    a.park_nyq = nullptr;
-    a.pbasis = 0;
-    a.bat = bat;
-    const dim3 grid(a.nb_main + a.gp.ntc, 1, bat.n);
-    hipLaunchKernelGGL((k_fft_x_force<N, M>), grid, dim3(kThreads), 0, s, a);
-  }
+  FusedArgs a;
+  a.op = op;
+  a.t = t;
+  a.in_main = in.c();
+  a.in_nyq = in.q;
+  a.gm = ColGeom{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)};
+  a.gp = ColGeom{0, 8L * N, N, cdiv(N, M)};
+  a.nb_main = N * a.gm.ntc;
+  a.first = a.last = 1;
+  a.park_main = nullptr;
+  a.park_nyq = nullptr;
+  a.pbasis = 0;
+  a.bat = bat;
+  const dim3 grid(a.nb_main + a.gp.ntc, 1, bat.n);
+  hipLaunchKernelGGL((k_fft_x_force<N, M>), grid, dim3(kThreads), 0, s, a);
 }
 
 // The transposed force's x pass (one launch of k_fft_x_force_t) over
@@ -1565,52 +1490,48 @@ void xforce(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s
 // replaces f[0], f[1] and f[2] are left as they were.
 template <int N>
 void xforce_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s) {
-  if constexpr (Split<N>::R2 > 1) {
-    constexpr int M = Cols<N>::M;
-    FusedArgs a;
-    a.op = op;
-    a.t = t;
-    a.gm = ColGeom{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)};
-    a.gp = ColGeom{0, 8L * N, N, cdiv(N, M)};
-    a.nb_main = N * a.gm.ntc;
-    a.first = a.last = 1;
-    a.park_main = nullptr;
-    a.park_nyq = nullptr;
-    a.pbasis = 0;
-    for (int d = 0; d < 3; ++d) {
-      a.op.in_c[d] = f[d].c();
-      a.op.in_q[d] = f[d].q;
-    }
-    a.op.out_c[0] = f[0].c();
-    a.op.out_q[0] = f[0].q;
-    a.in_main = f[0].c();
-    a.in_nyq = f[0].q;
-    const dim3 grid(a.nb_main + a.gp.ntc);
-    if (op.deconv || op.split)
-      hipLaunchKernelGGL((k_fft_x_force_t<N, M, true>), grid, dim3(kThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_fft_x_force_t<N, M, false>), grid, dim3(kThreads), 0, s, a);
+  constexpr int M = Cols<N>::M;
+  FusedArgs a;
+  a.op = op;
+  a.t = t;
+  a.gm = ColGeom{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)};
+  a.gp = ColGeom{0, 8L * N, N, cdiv(N, M)};
+  a.nb_main = N * a.gm.ntc;
+  a.first = a.last = 1;
+  a.park_main = nullptr;
+  a.park_nyq = nullptr;
+  a.pbasis = 0;
+  for (int d = 0; d < 3; ++d) {
+    a.op.in_c[d] = f[d].c();
+    a.op.in_q[d] = f[d].q;
   }
+  a.op.out_c[0] = f[0].c();
+  a.op.out_q[0] = f[0].q;
+  a.in_main = f[0].c();
+  a.in_nyq = f[0].q;
+  const dim3 grid(a.nb_main + a.gp.ntc);
+  if (op.deconv || op.split)
+    hipLaunchKernelGGL((k_fft_x_force_t<N, M, true>), grid, dim3(kThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_fft_x_force_t<N, M, false>), grid, dim3(kThreads), 0, s, a);
 }
 
 template <int N>
 void yforce(const FftTables& t, Field* f, hipStream_t s, const BatchArg& bat = BatchArg()) {
-  if constexpr (Split<N>::R2 > 1) {
-    constexpr int M = YTile<N>::M, TH = YTile<N>::TH;
-    ColPass p;
-    const int order[3] = {0, 2, 1};   // F_x, shared factor (F_z), F_y
-    for (int i = 0; i < 3; ++i) {
-      p.main[i] = f[order[i]].c();
-      p.plane[i] = f[order[i]].q;
-    }
-    // geometry of ypass: main c[xb][y][kz][xi], Nyquist plane q[xb][y][xi]
-    p.gm = ColGeom{4L * N * N, 4L * N, 4 * N, cdiv(4 * N, M)};
-    p.gp = ColGeom{8L * N, 8, 8, cdiv(8, M)};
-    p.nb_main = (N / 8) * p.gm.ntc;
-    p.bat = bat;
-    const dim3 grid(p.nb_main + (N / 8) * p.gp.ntc, 2, bat.n);
-    hipLaunchKernelGGL((k_fft_cols_force<N, M, TH>), grid, dim3(TH), 0, s, p, t.tw_n, t.dxy, t.dz);
+  constexpr int M = YTile<N>::M, TH = YTile<N>::TH;
+  ColPass p;
+  const int order[3] = {0, 2, 1};   // F_x, shared factor (F_z), F_y
+  for (int i = 0; i < 3; ++i) {
+    p.main[i] = f[order[i]].c();
+    p.plane[i] = f[order[i]].q;
   }
+  // geometry of ypass: main c[xb][y][kz][xi], Nyquist plane q[xb][y][xi]
+  p.gm = ColGeom{4L * N * N, 4L * N, 4 * N, cdiv(4 * N, M)};
+  p.gp = ColGeom{8L * N, 8, 8, cdiv(8, M)};
+  p.nb_main = (N / 8) * p.gm.ntc;
+  p.bat = bat;
+  const dim3 grid(p.nb_main + (N / 8) * p.gp.ntc, 2, bat.n);
+  hipLaunchKernelGGL((k_fft_cols_force<N, M, TH>), grid, dim3(TH), 0, s, p, t.tw_n, t.dxy, t.dz);
 }
 
 // chunks of at most 3 fields per launch (blockIdx.y selects the field)
@@ -1695,10 +1616,6 @@ void fft_x_force(const FftTables& t, const Field& in, const SpecOp& op, hipStrea
 }
 
 void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s) {
-  if (t.n < 64) {   // whole columns in registers: the fused fan-in pass
-    fft_x_fused(t, f[0], op, s);
-    return;
-  }
 #define CALL(N) xforce_t<N>(t, f, op, s)
   PM_FFT_SWITCH(t.n, CALL)
 #undef CALL

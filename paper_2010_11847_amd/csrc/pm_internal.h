@@ -55,8 +55,8 @@ enum SpecOpKind : int {
   OP_LPT2 = 3,       // 3 outputs: -i D_d / K^2 X * scale
   OP_LINEAR = 4,     // 1 output: X * pk[n^2]
   OP_LPT_PHI = 5,    // 6 outputs: phi_ij of delta_L = X * pk[n^2] (xx, yy, zz, xy, xz, yz)
-  OP_FORCE_XS = 6,   // 2 outputs after the x pass: i D_x g X (F_x) and i g X, the factor
-                     // F_y and F_z share until their y and z passes (N >= 64 only)
+  OP_FORCE_XS = 6,   // 2 outputs after the x pass, g = scale W^-n S / K^2: i D_x g X (F_x) and i g X,
+                     // the factor F_y and F_z share until their y and z passes
   OP_FORCE_T = 16,   // fan-in 3: sum_d conj(i D_d g) X_d
   OP_LPT2_T = 17,    // fan-in 3: sum_d conj(-i D_d scale / K^2) X_d
   OP_LPT1_T = 18,    // fan-in 9: pk[n^2] (sum_d conj(i D_d / K^2) X_d + sum_ij D_i D_j / K^2 X_ij)
@@ -91,22 +91,20 @@ void fft_x_forward(const FftTables& t, Field* f, int nf, hipStream_t s);
 // transforms written to op.out_*.  `in` may alias out[0].
 void fft_x_fused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s);
 // The force's x pass in one launch: forward x transform of `in`, times the
-// Green's function, inverse x transforms into op.out_* (out[0] may alias
-// `in`).  N >= 64 takes OP_FORCE_XS (out[0] = F_x, out[1] = the factor F_y
-// and F_z share), smaller meshes OP_FORCE (three components).
-// Batched launches (bat.d != null) cover every member of a plan; they need
-// N >= 64, as do the batched forms of the passes below.
+// Green's function, inverse x transforms into op.out_* (OP_FORCE_XS: out[0] =
+// F_x, which may alias `in`, out[1] = the factor F_y and F_z share).
+// Batched launches (bat.d != null) cover every member of a plan, as do the
+// batched forms of the passes below.
 void fft_x_force(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s,
                  const BatchArg& bat = BatchArg());
 // Inverse y pass of the three force meshes after an OP_FORCE_XS x pass:
 // f[0] holds F_x, f[2] the shared factor i g X.  f[2] becomes F_z times
 // D(w_z) in place and f[1] receives F_y = transform of D(w_y) i g X; one
-// read of the shared factor feeds both.  N >= 64.
+// read of the shared factor feeds both.
 void fft_y_force(const FftTables& t, Field* f, hipStream_t s, const BatchArg& bat = BatchArg());
 // x pass of the transposed force (OP_FORCE_T: op.scale, deconv, split) over
 // the forward-(z, y) spectra f[0..2] of its x, y, z inputs; the result (the
-// fan-in, inverse-x transformed) replaces f[0]; below 64^3 the other two
-// inputs may be overwritten as well.
+// fan-in, inverse-x transformed) replaces f[0].
 void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s);
 // Single passes (the composites above call these).
 void fft_z_r2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg());
