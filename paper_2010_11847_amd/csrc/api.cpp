@@ -398,6 +398,26 @@ struct pm_ctx {
     if (e != hipSuccess) return fail(PM_EHIP, std::string(where) + ": " + hipGetErrorString(e));
     return PM_OK;
   }
+  // z pass of a caller's plain [x][y][z] mesh into / out of an x-blocked
+  // field; a mesh off the 16-byte grid goes through a relayout copy
+  void z_r2c_from(const FftTables& t, const float* d, const Field& f) {
+    Field g = f;
+    if ((uintptr_t)d % 16) {
+      pmk::launch_relayout(d, g.r, t.n, true, stream);
+      pmk::fft_z_r2c(t, &g, 1, stream);
+    } else {
+      pmk::fft_z_r2c_std(t, d, g, stream);
+    }
+  }
+  void z_c2r_to(const FftTables& t, const Field& f, float* d) {
+    Field g = f;
+    if ((uintptr_t)d % 16) {
+      pmk::fft_z_c2r(t, &g, 1, stream);
+      pmk::launch_relayout(g.r, d, t.n, false, stream);
+    } else {
+      pmk::fft_z_c2r_std(t, g, d, stream);
+    }
+  }
   Field lat(int i) const {
     Field f;
     char* b = ws + L.lat0 + (size_t)i * field_bytes(npart);
@@ -806,13 +826,18 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
   Field f[10];
   for (int i = 0; i < 10; ++i) f[i] = c.lat(i);
   // the lattice fields are x-blocked; the caller's noise is [x][y][z]
-  if (d_noise_in)
-    pmk::launch_relayout(d_noise_in, f[0].r, c.npart, true, c.stream);
-  else
-    pmk::launch_noise(seed, c.npart, f[0].r, true, c.stream);
-  if (d_noise_out) pmk::launch_relayout(f[0].r, d_noise_out, c.npart, false, c.stream);
+  if (d_noise_in && !d_noise_out) {
+    c.z_r2c_from(c.tl, d_noise_in, f[0]);
+  } else {
+    if (d_noise_in)
+      pmk::launch_relayout(d_noise_in, f[0].r, c.npart, true, c.stream);
+    else
+      pmk::launch_noise(seed, c.npart, f[0].r, true, c.stream);
+    if (d_noise_out) pmk::launch_relayout(f[0].r, d_noise_out, c.npart, false, c.stream);
+    pmk::fft_z_r2c(c.tl, &f[0], 1, c.stream);
+  }
+  pmk::fft_y(c.tl, &f[0], 1, -1, c.stream);
   const int order = c.cfg.lpt_order;
-  pmk::fft_r2c_zy(c.tl, &f[0], 1, c.stream);
   pmk::SpecOp op;
   op.kind = pmk::OP_LPT1;
   op.n_out = order >= 2 ? 9 : 3;
@@ -1294,7 +1319,6 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
   const int order = c.cfg.lpt_order;
   Field f[13];
   for (int i = 0; i < 13; ++i) f[i] = c.lat(i);
-  pmk::launch_relayout(d_noise, f[0].r, c.npart, true, c.stream);
   double g[6];
   c.cosmo.growth(h_a[0], g);
   const double a0 = h_a[0], b = c.ratio;
@@ -1306,7 +1330,8 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
   int n_in = 3;
   if (order >= 2) {
     // phi_ij of the linear field
-    pmk::fft_r2c_zy(c.tl, &f[0], 1, c.stream);
+    c.z_r2c_from(c.tl, d_noise, f[0]);
+    pmk::fft_y(c.tl, &f[0], 1, -1, c.stream);
     pmk::SpecOp op;
     op.kind = pmk::OP_LPT_PHI;
     op.n_out = 6;
@@ -1352,8 +1377,8 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
   o1.out_c[0] = f[0].c();
   o1.out_q[0] = f[0].q;
   pmk::fft_x_fused(c.tl, f[0], o1, c.stream);
-  pmk::fft_c2r_yz(c.tl, &f[0], 1, c.stream);
-  pmk::launch_relayout(f[0].r, d_grad_noise, c.npart, false, c.stream);
+  pmk::fft_y(c.tl, &f[0], 1, 1, c.stream);
+  c.z_c2r_to(c.tl, f[0], d_grad_noise);
   return c.check("pm_run_adjoint");
 }
 
@@ -1453,11 +1478,9 @@ int pm_power(pm_ctx* ctx, const float* d_delta, int n_bins, int n_max, int decon
   if (!ctx || !d_delta || !h_k || !h_pk || !h_nmodes) return PM_EINVAL;
   pm_ctx& c = *ctx;
   if (n_bins < 1 || n_bins > c.L.n_bins_max) return c.fail(PM_EINVAL, "n_bins must be in [1, n_mesh/2]");
-  pmk::launch_relayout(d_delta, c.mesh[0].r, c.ng, true, c.stream);
-  pmk::fft_r2c_zy(c.tm, &c.mesh[0], 1, c.stream);
-  pmk::fft_x_forward(c.tm, &c.mesh[0], 1, c.stream);
+  c.z_r2c_from(c.tm, d_delta, c.mesh[0]);
+  pmk::fft_y(c.tm, &c.mesh[0], 1, -1, c.stream);
   pmk::PowerArgs a;
-  a.n = c.ng;
   a.n_bins = n_bins;
   a.n_max = n_max;
   a.deconv = deconv;
@@ -1466,7 +1489,8 @@ int pm_power(pm_ctx* ctx, const float* d_delta, int n_bins, int n_max, int decon
   a.wxy = c.tm.wxy;
   a.wz = c.tm.wz;
   a.partial = c.pw_partial;
-  pmk::launch_power(a, c.pw_out, c.stream);
+  a.out = c.pw_out;
+  pmk::launch_power(c.tm, a, c.stream);
   std::vector<double> h(3 * (size_t)n_bins);
   hipError_t e = hipMemcpyAsync(h.data(), c.pw_out, h.size() * 8, hipMemcpyDeviceToHost, c.stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c.stream);
@@ -1486,10 +1510,9 @@ int pm_power(pm_ctx* ctx, const float* d_delta, int n_bins, int n_max, int decon
 int pm_rfft(pm_ctx* ctx, const float* d_real, float* d_spec) {
   if (!ctx || !d_real || !d_spec) return PM_EINVAL;
   pm_ctx& c = *ctx;
-  pmk::launch_relayout(d_real, c.mesh[0].r, c.ng, true, c.stream);
-  pmk::fft_r2c_zy(c.tm, &c.mesh[0], 1, c.stream);
-  pmk::fft_x_forward(c.tm, &c.mesh[0], 1, c.stream);
-  pmk::launch_spec_to_numpy(c.mesh[0].c(), c.mesh[0].q, reinterpret_cast<float2*>(d_spec), c.ng, 1.f, c.stream);
+  c.z_r2c_from(c.tm, d_real, c.mesh[0]);
+  pmk::fft_y(c.tm, &c.mesh[0], 1, -1, c.stream);
+  pmk::fft_x_forward_np(c.tm, c.mesh[0], reinterpret_cast<float2*>(d_spec), c.stream);
   return c.check("pm_rfft");
 }
 
@@ -1497,11 +1520,9 @@ int pm_irfft(pm_ctx* ctx, const float* d_spec, float* d_real) {
   if (!ctx || !d_real || !d_spec) return PM_EINVAL;
   pm_ctx& c = *ctx;
   const long n3 = (long)c.ng * c.ng * c.ng;
-  pmk::launch_spec_from_numpy(reinterpret_cast<const float2*>(d_spec), c.mesh[0].c(), c.mesh[0].q, c.ng,
-                              (float)(1.0 / (double)n3), c.stream);
-  pmk::fft_x_inverse(c.tm, &c.mesh[0], 1, c.stream);
-  pmk::fft_c2r_yz(c.tm, &c.mesh[0], 1, c.stream);
-  pmk::launch_relayout(c.mesh[0].r, d_real, c.ng, false, c.stream);
+  pmk::fft_x_inverse_np(c.tm, reinterpret_cast<const float2*>(d_spec), c.mesh[0], (float)(1.0 / (double)n3), c.stream);
+  pmk::fft_y(c.tm, &c.mesh[0], 1, 1, c.stream);
+  c.z_c2r_to(c.tm, c.mesh[0], d_real);
   return c.check("pm_irfft");
 }
 

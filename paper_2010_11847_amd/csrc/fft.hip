@@ -214,6 +214,10 @@ struct ColLds {
 // One launch covers the main arrays (tiles [0, nb_main)) and the Nyquist
 // planes (the remaining tiles) of up to three fields (blockIdx.y).
 struct ColPass {
+  // x pass with NP: one field's other side is a caller's numpy-layout half
+  // spectrum [kx][ky][kz], kz = 0 .. N/2 (DIR < 0 writes it, DIR > 0 reads it)
+  float2* np = nullptr;
+  float scale = 1.f;
   float2* main[3];
   float2* plane[3];
   ColGeom gm, gp;
@@ -222,7 +226,12 @@ struct ColPass {
   BatchArg bat; // batched launches: blockIdx.z selects the member
 };
 
-template <int N, int M, int DIR, bool BLK, int TH = kThreads>
+// NP (x pass, one field): a pass between the numpy layout and the x-blocked
+// one cost another read and write of the spectrum in 8-byte pieces (100 us of
+// 130 us at 256^3).  Its tiles walk columns fastest: a numpy row's 128-byte
+// pieces are unaligned ((N/2 + 1)-element rows), and the tiles that share
+// their lines then follow each other on one XCD.
+template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false>
 __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __restrict__ tw) {
   constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
   constexpr int CS = BLK ? 8 : 1;
@@ -237,9 +246,24 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
   if (bo < 0) return;
   float2* data = byte_adv(is_plane ? p.plane[blockIdx.y] : p.main[blockIdx.y], bo);
   int b, c0;
-  tile_bc<BLK>(tile, is_plane ? ((int)gridDim.x - p.nb_main) / g.ntc : p.nb_main / g.ntc, g.ntc, M, b, c0);
+  tile_bc<BLK && !NP>(tile, is_plane ? ((int)gridDim.x - p.nb_main) / g.ntc : p.nb_main / g.ntc, g.ntc, M, b, c0);
   float2* base = data + b * g.sb + (long)c0 * CS;
   const int tid = threadIdx.x;
+  // row n (x or kx) of column m in the numpy layout
+  auto np_off = [&](int n, int m) {
+    constexpr long H1 = N / 2 + 1;
+    return is_plane ? ((long)n * N + c0 + m) * H1 + N / 2 : ((long)n * N + b) * H1 + c0 + m;
+  };
+  auto load = [&](int n, int m) {
+    if constexpr (NP && DIR > 0) return cscale(p.np[np_off(n, m)], p.scale);
+    return base[row_off<BLK>(n, g.sn) + m * CS];
+  };
+  auto store = [&](int n, int m, float2 v) {
+    if constexpr (NP && DIR < 0)
+      p.np[np_off(n, m)] = v;
+    else
+      base[row_off<BLK>(n, g.sn) + m * CS] = v;
+  };
 
   constexpr int SA = ColLds<N, M>::SA;
 #pragma unroll
@@ -251,7 +275,7 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       float2 v[R1];
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1)
-        v[j1] = ok ? base[row_off<BLK>(R2 * j1 + j2, g.sn) + m * CS] : make_float2(0.f, 0.f);
+        v[j1] = ok ? load(R2 * j1 + j2, m) : make_float2(0.f, 0.f);
       dft<R1, DIR>(v);
 #pragma unroll
       for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<DIR>(tw, j2 * l1));
@@ -269,7 +293,7 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       dft<R2, DIR>(v);
       if (c0 + m < g.ncols) {
 #pragma unroll
-        for (int l2 = 0; l2 < R2; ++l2) base[row_off<BLK>(l1 + R1 * l2, g.sn) + m * CS] = v[l2];
+        for (int l2 = 0; l2 < R2; ++l2) store(l1 + R1 * l2, m, v[l2]);
       }
     }
   }
@@ -448,6 +472,47 @@ __device__ __forceinline__ void copy16(float4* __restrict__ dst, const float4* _
   }
 }
 
+// Lines l0 .. l0+L-1 of a caller's plain [x][y][z] mesh <-> LDS, line m at
+// m*ZP complex, its reals z = 2j, 2j+1 in complex j (16-byte global accesses;
+// the callers check the mesh's alignment).
+template <class G>
+__device__ __forceinline__ long std_line(long l0, int m) {   // first element of line m
+  constexpr int N = G::NN;
+  const long row = (l0 + m) >> 3;   // (x/8, y) row, N = 2^k
+  const long x = (row / N) * 8 + (m & 7), y = row % N;
+  return (x * N + y) * N;
+}
+
+template <class G>
+__device__ __forceinline__ void std_load(float2* __restrict__ lds, const float* __restrict__ in, long l0) {
+  constexpr int N = G::NN, Q = N / 4, W = G::L * Q, ZP = G::ZP;
+  constexpr int K = (W + kThreads - 1) / kThreads;
+  float4 t[K];   // all loads first, as copy16
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = threadIdx.x + k * kThreads;
+    if (W % kThreads == 0 || i < W) t[k] = *reinterpret_cast<const float4*>(in + std_line<G>(l0, i / Q) + 4 * (i % Q));
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = threadIdx.x + k * kThreads;
+    if (W % kThreads == 0 || i < W) {
+      float2* d = lds + (i / Q) * ZP + 2 * (i % Q);
+      d[0] = make_float2(t[k].x, t[k].y);
+      d[1] = make_float2(t[k].z, t[k].w);
+    }
+  }
+}
+
+template <class G>
+__device__ __forceinline__ void std_store(const float2* __restrict__ lds, float* __restrict__ out, long l0) {
+  constexpr int N = G::NN, Q = N / 4, W = G::L * Q, ZP = G::ZP;
+  for (int i = threadIdx.x; i < W; i += kThreads) {
+    const float2* v = lds + (i / Q) * ZP + 2 * (i % Q);
+    *reinterpret_cast<float4*>(out + std_line<G>(l0, i / Q) + 4 * (i % Q)) = make_float4(v[0].x, v[0].y, v[1].x, v[1].y);
+  }
+}
+
 // Length-H complex transform of the L lines of a workgroup.  load(m, n)
 // returns element n of line m (it may read the staged region in lds: every
 // load happens before the first write to lds).  On return Z[m][k] is in lds
@@ -530,13 +595,17 @@ __device__ __forceinline__ void zline_transform(float2* lds, const float2* __res
 }
 
 // Real-to-complex along z, in place: the N reals of each line become
-// X[0..N/2-1] (region) and X[N/2] (Nyquist plane, q[l]).
-template <int N>
+// X[0..N/2-1] (region) and X[N/2] (Nyquist plane, q[l]).  STD reads the reals
+// of one field from a caller's plain [x][y][z] mesh instead: a copy into the
+// x-blocked layout first cost one more read and write of the mesh (43 us of
+// the pass pair's 79 us at 256^3).
+template <int N, bool STD>
 __global__ __launch_bounds__(kThreads) void k_r2c_z(float* __restrict__ r0, float* __restrict__ r1,
                                                      float* __restrict__ r2, float2* __restrict__ q0,
                                                      float2* __restrict__ q1, float2* __restrict__ q2,
                                                      const float2* __restrict__ twh,
-                                                     const float2* __restrict__ twn, BatchArg bat) {
+                                                     const float2* __restrict__ twn, BatchArg bat,
+                                                     const float* __restrict__ std_in) {
   using G = ZGeom<N>;
   constexpr int H = G::H, L = G::L, ZP = G::ZP;
   __shared__ float2 lds[G::size];
@@ -546,10 +615,14 @@ __global__ __launch_bounds__(kThreads) void k_r2c_z(float* __restrict__ r0, floa
   float2* q = byte_adv(blockIdx.y == 0 ? q0 : (blockIdx.y == 1 ? q1 : q2), bo);
   const long l0 = (long)xcd_tile(blockIdx.x, gridDim.x) * L;
   float2* reg = reinterpret_cast<float2*>(r) + l0 * H;   // region: L*H complex = L*N floats
-  copy16<L * H / 2>(reinterpret_cast<float4*>(lds), reinterpret_cast<const float4*>(reg));
+  if constexpr (STD)
+    std_load<G>(lds, std_in, l0);
+  else
+    copy16<L * H / 2>(reinterpret_cast<float4*>(lds), reinterpret_cast<const float4*>(reg));
   __syncthreads();
   const float* lf = reinterpret_cast<const float*>(lds);
   zline_transform<G, -1>(lds, twh, [&](int m, int n) {
+    if constexpr (STD) return lds[m * ZP + n];
     const int o = (m >> 3) * 8 * N + 16 * n + (m & 7);
     return make_float2(lf[o], lf[o + 8]);
   });
@@ -575,13 +648,14 @@ __global__ __launch_bounds__(kThreads) void k_r2c_z(float* __restrict__ r0, floa
 }
 
 // Complex-to-real along z (unnormalised), in place: X[0..N/2] -> N reals.
-// The imaginary parts of X[0] and X[N/2] are discarded.
-template <int N>
+// The imaginary parts of X[0] and X[N/2] are discarded.  STD writes the reals
+// of one field to a caller's plain [x][y][z] mesh.
+template <int N, bool STD>
 __global__ __launch_bounds__(kThreads) void k_c2r_z(float* __restrict__ r0, float* __restrict__ r1,
                                                      float* __restrict__ r2, const float2* __restrict__ q0,
                                                      const float2* __restrict__ q1, const float2* __restrict__ q2,
                                                      const float2* __restrict__ twh,
-                                                     const float2* __restrict__ twn) {
+                                                     const float2* __restrict__ twn, float* __restrict__ std_out) {
   using G = ZGeom<N>;
   constexpr int H = G::H, L = G::L, ZP = G::ZP;
   __shared__ float2 lds[G::size];
@@ -605,6 +679,10 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z(float* __restrict__ r0, floa
     const float2 o = cmulc(csub(a, b), twn[k]);     // (a - b) exp(+2 pi i k / N)
     return make_float2(e.x - o.y, e.y + o.x);       // e + i o
   });
+  if constexpr (STD) {
+    std_store<G>(lds, std_out, l0);
+    return;
+  }
   // region float e = rr*8N + z*8 + xi holds component z&1 of Z[rr*8 + xi][z/2]
   const float* lf = reinterpret_cast<const float*>(lds);
   float4* o4 = reinterpret_cast<float4*>(reg);
@@ -988,6 +1066,137 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
 }
 
 
+// most workgroups of the power kernel: two per CU (their exchange and sums
+// take 76-80 KB of LDS)
+constexpr int kPowerBlocks = 512;
+
+// ---- binned power spectrum -------------------------------------------------
+// The forward x pass with the binning on its output: the spectrum is read
+// once and never written (a plain x pass, then a binning pass over its
+// output, took 262 + 347 us at 512^3).  A workgroup walks tiles and keeps its
+// bin sums in LDS; the sums of the workgroups are reduced by k_power_reduce.
+// Bin j holds |n| in [j - 1/2, j + 1/2), i.e. j^2 - j < |n|^2 <= j^2 + j in
+// integers, found from a float32 root and corrected exactly.  The number of
+// modes and the sum of |n| of a bin do not depend on the signs of n_x and n_y,
+// so only the quadrant n_x, n_y >= 0 adds them, with its multiplicity: 1.5
+// float64 LDS atomics per mode instead of 3.
+template <int N, int M>
+__global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, int nb_main, int ntiles,
+                                                      const float2* __restrict__ tw, PowerArgs a) {
+  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2, H = N / 2;
+  constexpr int IA = (M * R2 + kThreads - 1) / kThreads;
+  constexpr int IB = (M * R1 + kThreads - 1) / kThreads;
+  constexpr int SA = R2 * M + M;
+  __shared__ float2 lds[R1 * SA];
+  __shared__ double sk[H], sp[H];
+  __shared__ uint32_t sw[H];
+  __shared__ double iw[H];   // (CIC window)^-2 of kx = 1 .. N/2, or 1
+  const int tid = threadIdx.x;
+  for (int i = tid; i < H; i += kThreads) {
+    sk[i] = sp[i] = 0.0;
+    sw[i] = 0u;
+    const double w = a.deconv ? (double)a.wxy[i + 1] : 1.0;
+    iw[i] = 1.0 / (w * w);
+  }
+  __syncthreads();
+  for (int t0 = blockIdx.x; t0 < ntiles; t0 += gridDim.x) {
+    const bool is_plane = t0 >= nb_main;
+    const int tile = is_plane ? t0 - nb_main : t0;
+    const ColGeom& g = is_plane ? gp : gm;
+    int b, c0;
+    tile_bc<true>(tile, is_plane ? (ntiles - nb_main) / g.ntc : nb_main / g.ntc, g.ntc, M, b, c0);
+    const float2* base = (is_plane ? a.q : a.c) + b * g.sb + (long)c0 * 8;
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R2) {
+        const int m = it % M, j2 = it / M;
+        const bool ok = c0 + m < g.ncols;
+        float2 v[R1];
+#pragma unroll
+        for (int j1 = 0; j1 < R1; ++j1)
+          v[j1] = ok ? base[row_off<true>(R2 * j1 + j2, g.sn) + m * 8] : make_float2(0.f, 0.f);
+        dft<R1, -1>(v);
+#pragma unroll
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<-1>(tw, j2 * l1));
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < IB; ++i) {
+      const int it = tid + i * kThreads;
+      if (it < M * R1) {
+        const int m = it % M, l1 = it / M;
+        float2 v[R2];
+#pragma unroll
+        for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
+        dft<R2, -1>(v);
+        // back into the slots this item read (no other thread's), so that the
+        // binning below is a loop: unrolled over registers it needed more
+        // than 256 of them and left one wave per SIMD
+#pragma unroll
+        for (int l2 = 0; l2 < R2; ++l2) lds[l1 * SA + l2 * M + m] = v[l2];
+        const int ky = is_plane ? c0 + m : b, kz = is_plane ? H : c0 + m;
+        const int fy = ky < H ? ky : ky - N;
+        const int nmax = a.n_max > 0 ? a.n_max : N;
+        if (c0 + m < g.ncols && abs(fy) < nmax && kz < nmax) {
+          const double wz = kz == 0 || kz == H ? 1.0 : 2.0;
+          double iyz = wz;   // mode weight over the window of (ky, kz)
+          if (a.deconv) {
+            const double w = (double)a.wxy[ky] * a.wz[kz];
+            iyz /= w * w;
+          }
+          const bool quad = fy >= 0 || fy == -H;
+          const uint32_t my = (fy == 0 || fy == -H ? 1u : 2u) * (uint32_t)wz;
+          const int ryz = fy * fy + kz * kz;
+#pragma unroll 2
+          for (int l2 = 0; l2 < R2; ++l2) {
+            const int kx = l1 + R1 * l2;
+            const float2 x = lds[l1 * SA + l2 * M + m];
+            const int ax = kx <= H ? kx : N - kx;   // |n_x|
+            const int n2 = ax * ax + ryz;
+            int j = (int)(__builtin_amdgcn_sqrtf((float)n2) + 0.5f);
+            if (n2 > j * j + j) ++j;
+            if (n2 <= j * j - j) --j;
+            if (j < 1 || j > a.n_bins || ax >= nmax) continue;
+            const double px = (double)x.x * x.x + (double)x.y * x.y;
+            atomicAdd(&sp[j - 1], px * (ax ? iyz * iw[ax - 1] : iyz));
+            if (quad && kx <= H) {
+              const uint32_t mult = my * (kx == 0 || kx == H ? 1u : 2u);
+              atomicAdd(&sw[j - 1], mult);
+              atomicAdd(&sk[j - 1], (double)mult * sqrt((double)n2));
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();   // the exchange is reused; the sums are complete
+  }
+  double* out = a.partial + (long)blockIdx.x * 3 * a.n_bins;
+  for (int i = tid; i < a.n_bins; i += kThreads) {
+    out[i] = (double)sw[i];
+    out[a.n_bins + i] = sk[i];
+    out[2 * a.n_bins + i] = sp[i];
+  }
+}
+
+// out[i] = sum over the workgroups' partial sums, one workgroup per sum: its
+// threads take every 256th partial (one thread for all of them, a serial
+// chain of 1024 loads, took 254 us)
+__global__ __launch_bounds__(kThreads) void k_power_reduce(const double* __restrict__ partial, int nblocks, int n3,
+                                                           double* __restrict__ out) {
+  __shared__ double red[kThreads];
+  const int tid = threadIdx.x;
+  double s = 0.0;
+  for (int b = tid; b < nblocks; b += kThreads) s += partial[(long)b * n3 + blockIdx.x];
+  red[tid] = s;
+  for (int o = kThreads / 2; o > 0; o >>= 1) {
+    __syncthreads();
+    if (tid < o) red[tid] += red[tid + o];
+  }
+  if (tid == 0) out[blockIdx.x] = red[0];
+}
+
 // The force's common factor c(k) = scale W(k)^-n S(k) / K^2(k) at
 // kx = l1 + R1 l2 for every l2 of one stage-B item (column (ky, kz)).  The
 // per-kx table values are loaded together and pinned before use: a table
@@ -1356,9 +1565,10 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force_t(FusedArgs a) {
 // ---------------------------------------------------------------------------
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-template <int N, int DIR, bool BLK>
+template <int N, int DIR, bool BLK, bool NP = false>
 void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int nbm, ColGeom gp, int nbp,
-                 const float2* tw, hipStream_t s, const BatchArg& bat = BatchArg()) {
+                 const float2* tw, hipStream_t s, const BatchArg& bat = BatchArg(), float2* np = nullptr,
+                 float scale = 1.f) {
   constexpr int M = BLK ? Cols<N>::M : YTile<N>::M;
   constexpr int TH = BLK ? kThreads : YTile<N>::TH;
   ColPass p;
@@ -1373,8 +1583,10 @@ void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int n
   p.nb_main = nbm * gm.ntc;
   p.ntiles = p.nb_main + nbp * gp.ntc;
   p.bat = bat;
+  p.np = np;
+  p.scale = scale;
   dim3 grid(p.ntiles, nf, bat.n);
-  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH>), grid, dim3(TH), 0, s, p, tw);
+  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH, NP>), grid, dim3(TH), 0, s, p, tw);
 }
 
 // y pass over the main arrays and the Nyquist planes of nf fields
@@ -1389,24 +1601,47 @@ void ypass(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& 
                              ColGeom{8L * N, 8, 8, 0}, N / 8, t.tw_n, s, bat);
 }
 
+// x pass of one field between its x-blocked spectrum and a caller's
+// numpy-layout half spectrum
 template <int N, int DIR>
-void xpass(const FftTables& t, Field* f, int nf, hipStream_t s) {
-  float2* dm[3];
-  float2* dq[3];
-  for (int i = 0; i < nf; ++i) { dm[i] = f[i].c(); dq[i] = f[i].q; }
+void xpass_np(const FftTables& t, const Field& f, float2* np, float scale, hipStream_t s) {
+  float2* const dm[1] = {f.c()};
+  float2* const dq[1] = {f.q};
   // main c[xb][y][kz][xi]: (b = y, n = x, c = kz): sb = 4N, row(x) = xb*4N^2 + xi, column stride 8
   // Nyquist plane q[xb][y][xi]: (b = 0, n = x, c = y): row(x) = xb*8N + xi, column stride 8
-  launch_cols<N, DIR, true>(dm, dq, nf, ColGeom{4L * N, 4L * N * N, N / 2, 0}, N, ColGeom{0, 8L * N, N, 0}, 1,
-                            t.tw_n, s);
+  launch_cols<N, DIR, true, true>(dm, dq, 1, ColGeom{4L * N, 4L * N * N, N / 2, 0}, N, ColGeom{0, 8L * N, N, 0}, 1,
+                                  t.tw_n, s, BatchArg(), np, scale);
+}
+
+template <int N>
+void power_x(const FftTables& t, const PowerArgs& a, hipStream_t s) {
+  constexpr int M = Cols<N>::M;
+  const ColGeom gm{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)}, gp{0, 8L * N, N, cdiv(N, M)};
+  const int nb_main = N * gm.ntc, ntiles = nb_main + gp.ntc;
+  const int nwg = ntiles < kPowerBlocks ? ntiles : kPowerBlocks;
+  hipLaunchKernelGGL((k_power_x<N, M>), dim3(nwg), dim3(kThreads), 0, s, gm, gp, nb_main, ntiles, t.tw_n, a);
+  hipLaunchKernelGGL(k_power_reduce, dim3(3 * a.n_bins), dim3(kThreads), 0, s, a.partial, nwg, 3 * a.n_bins, a.out);
 }
 
 template <int N>
 void zr2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg()) {
   using G = ZGeom<N>;
   dim3 grid((N * N) / G::L, nf, bat.n);
-  hipLaunchKernelGGL((k_r2c_z<N>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
+  hipLaunchKernelGGL((k_r2c_z<N, false>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
                      nf > 2 ? f[2].r : f[0].r, f[0].q, nf > 1 ? f[1].q : f[0].q, nf > 2 ? f[2].q : f[0].q,
-                     t.tw_h, t.tw_n, bat);
+                     t.tw_h, t.tw_n, bat, nullptr);
+}
+
+template <int N>
+void zr2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s) {
+  hipLaunchKernelGGL((k_r2c_z<N, true>), dim3((N * N) / ZGeom<N>::L), dim3(kThreads), 0, s, f.r, f.r, f.r, f.q, f.q,
+                     f.q, t.tw_h, t.tw_n, BatchArg(), in);
+}
+
+template <int N>
+void zc2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s) {
+  hipLaunchKernelGGL((k_c2r_z<N, true>), dim3((N * N) / ZGeom<N>::L), dim3(kThreads), 0, s, f.r, f.r, f.r, f.q, f.q,
+                     f.q, t.tw_h, t.tw_n, out);
 }
 
 template <int N>
@@ -1420,9 +1655,9 @@ template <int N>
 void zc2r(const FftTables& t, Field* f, int nf, hipStream_t s) {
   using G = ZGeom<N>;
   dim3 grid((N * N) / G::L, nf);
-  hipLaunchKernelGGL((k_c2r_z<N>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
+  hipLaunchKernelGGL((k_c2r_z<N, false>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
                      nf > 2 ? f[2].r : f[0].r, f[0].q, nf > 1 ? f[1].q : f[0].q, nf > 2 ? f[2].q : f[0].q,
-                     t.tw_h, t.tw_n);
+                     t.tw_h, t.tw_n, nullptr);
 }
 
 template <int N>
@@ -1587,20 +1822,36 @@ void fft_z_c2r(const FftTables& t, Field* f, int nf, hipStream_t s) {
   });
 }
 
-void fft_x_forward(const FftTables& t, Field* f, int nf, hipStream_t s) {
-  by3(f, nf, [&](Field* g, int k) {
-#define CALL(N) xpass<N, -1>(t, g, k, s)
-    PM_FFT_SWITCH(t.n, CALL)
+void fft_z_r2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s) {
+#define CALL(N) zr2c_std<N>(t, in, f, s)
+  PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
-  });
 }
 
-void fft_x_inverse(const FftTables& t, Field* f, int nf, hipStream_t s) {
-  by3(f, nf, [&](Field* g, int k) {
-#define CALL(N) xpass<N, 1>(t, g, k, s)
-    PM_FFT_SWITCH(t.n, CALL)
+void fft_z_c2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s) {
+#define CALL(N) zc2r_std<N>(t, f, out, s)
+  PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
-  });
+}
+
+void fft_x_forward_np(const FftTables& t, const Field& f, float2* spec, hipStream_t s) {
+#define CALL(N) xpass_np<N, -1>(t, f, spec, 1.f, s)
+  PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
+}
+
+void fft_x_inverse_np(const FftTables& t, const float2* spec, const Field& f, float scale, hipStream_t s) {
+#define CALL(N) xpass_np<N, 1>(t, f, const_cast<float2*>(spec), scale, s)
+  PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
+}
+
+long power_partial_doubles(int n_bins) { return (long)kPowerBlocks * 3 * n_bins; }
+
+void launch_power(const FftTables& t, const PowerArgs& a, hipStream_t s) {
+#define CALL(N) power_x<N>(t, a, s)
+  PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
 }
 
 void fft_x_fused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s) {

@@ -113,18 +113,6 @@ struct ReadoutArgs {
   BatchArg bat;
 };
 
-struct PowerArgs {
-  int n = 0;
-  int n_bins = 0;
-  int n_max = 0;
-  int deconv = 0;
-  const float2* c = nullptr;
-  const float2* q = nullptr;
-  const float* wxy = nullptr;
-  const float* wz = nullptr;
-  double* partial = nullptr;
-};
-
 // white noise of n_side^3 sites; blocked: x-blocked layout, else [x][y][z]
 void launch_noise(uint64_t seed, int n_side, float* out, bool blocked, hipStream_t s);
 // plain [x][y][z] <-> x-blocked copy of a real n_side^3 mesh (out != in)
@@ -164,9 +152,6 @@ void launch_kick_drift(float* pos, float* mom, const float* f, long np, float ki
 // change between the full and the LPT-frame momentum)
 void launch_frame_shift(float* mom, const uint32_t* id, const float* psi1, const float* psi2, long np, float u1,
                         float u2, hipStream_t s);
-void launch_spec_to_numpy(const float2* c, const float2* q, float2* out, int n, float scale, hipStream_t s);
-void launch_spec_from_numpy(const float2* in, float2* c, float2* q, int n, float scale, hipStream_t s);
-void launch_scale(float* p, long n, float v, hipStream_t s);
 // adjoint kernels (adjoint.hip)
 void launch_readout_grad3(const float* pos, const uint32_t* id, long np, int n, const float* fi, const float* pbar,
                           float k, float* xbar, hipStream_t s);
@@ -181,8 +166,5 @@ void launch_axpy(float* y, const float* x, float a, long n, hipStream_t s);
 void launch_lpt_sbar(const float* xbar, const float* pbar, long n3, float cx1, float cp1, float cx2, float cp2,
                      float* const* s1, float* const* s2, hipStream_t s);
 void launch_lpt_phibar(float* const* phi6, const float* d2b, long n3, hipStream_t s);
-int power_max_bins();
-long power_partial_doubles(int n_bins);
-void launch_power(const PowerArgs& a, double* out3, hipStream_t s);
 
 }  // namespace pmk

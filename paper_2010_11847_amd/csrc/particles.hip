@@ -845,90 +845,6 @@ __global__ void k_kick_drift(float* __restrict__ pos, float* __restrict__ mom, c
   }
 }
 
-// ---- power spectrum --------------------------------------------------------------
-constexpr int kPowerBins = 512;
-constexpr int kPowerBlocks = 1024;
-
-__global__ __launch_bounds__(kThreads) void k_power_bins(PowerArgs a) {
-  __shared__ double sw[kPowerBins], sk[kPowerBins], sp[kPowerBins];
-  for (int i = threadIdx.x; i < a.n_bins; i += kThreads) sw[i] = sk[i] = sp[i] = 0.0;
-  __syncthreads();
-  const int n = a.n, h = n / 2;
-  const int ln = __builtin_ctz(n), lh = ln - 1;
-  const long nmain = (long)n * n * h;
-  const long ntot = nmain + (long)n * n;
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < ntot; i += stride) {
-    int kx, ky, kz;
-    float2 v;
-    if (i < nmain) {   // x-blocked c[kx/8][ky][kz][kx%8]; n, h = n/2 powers of two
-      const long r = i >> 3;
-      kz = (int)(r & (h - 1));
-      ky = (int)((r >> lh) & (n - 1));
-      kx = (int)((r >> (lh + ln)) << 3) + (int)(i & 7);
-      v = a.c[i];
-    } else {           // q[kx/8][ky][kx%8]
-      const long j = i - nmain, r = j >> 3;
-      ky = (int)(r & (n - 1));
-      kx = (int)((r >> ln) << 3) + (int)(j & 7);
-      kz = h;
-      v = a.q[j];
-    }
-    const int fx = kx < h ? kx : kx - n, fy = ky < h ? ky : ky - n;
-    if (a.n_max > 0 && (abs(fx) >= a.n_max || abs(fy) >= a.n_max || kz >= a.n_max)) continue;
-    const int n2 = fx * fx + fy * fy + kz * kz;
-    const double mag = sqrt((double)n2);
-    const int bin = (int)floor(mag + 0.5);
-    if (bin < 1 || bin > a.n_bins) continue;
-    const double w = (kz == 0 || kz == h) ? 1.0 : 2.0;
-    double p = (double)v.x * v.x + (double)v.y * v.y;
-    if (a.deconv) {
-      const double win = (double)a.wxy[kx] * a.wxy[ky] * a.wz[kz];
-      p /= win * win;
-    }
-    atomicAdd(&sw[bin - 1], w);
-    atomicAdd(&sk[bin - 1], w * mag);
-    atomicAdd(&sp[bin - 1], w * p);
-  }
-  __syncthreads();
-  double* out = a.partial + (long)blockIdx.x * 3 * a.n_bins;
-  for (int i = threadIdx.x; i < a.n_bins; i += kThreads) {
-    out[i] = sw[i];
-    out[a.n_bins + i] = sk[i];
-    out[2 * a.n_bins + i] = sp[i];
-  }
-}
-
-__global__ void k_power_reduce(const double* __restrict__ partial, int nblocks, int n_bins, double* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 3 * n_bins) return;
-  double s = 0.0;
-  for (int b = 0; b < nblocks; ++b) s += partial[(long)b * 3 * n_bins + i];
-  out[i] = s;
-}
-
-// [n][n][n/2] + Nyquist plane  <->  [n][n][n/2+1] (numpy rfftn layout)
-__global__ void k_spec_pack(const float2* __restrict__ c, const float2* __restrict__ q, float2* __restrict__ out,
-                            int n, float scale, int to_numpy) {
-  const int h = n / 2;
-  const long total = (long)n * n * (h + 1);
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-    const int kz = (int)(i % (h + 1));
-    const long line = i / (h + 1);
-    const int kx = (int)(line / n), ky = (int)(line % n);
-    const long ec = blk_spec(kx, ky, kz < h ? kz : 0, n), eq = blk_nyq(kx, ky, n);
-    if (to_numpy) {
-      const float2 v = kz < h ? c[ec] : q[eq];
-      out[i] = make_float2(v.x * scale, v.y * scale);
-    } else {
-      float2* dst = kz < h ? const_cast<float2*>(c) + ec : const_cast<float2*>(q) + eq;
-      const float2 v = out[i];
-      *dst = make_float2(v.x * scale, v.y * scale);
-    }
-  }
-}
-
 // bits of max_i |v_i| (non-negative floats order like their bit patterns);
 // NaNs are ignored by fmaxf
 // (16-byte loads; one atomic per workgroup: the atomics on the one word
@@ -972,11 +888,6 @@ __global__ void k_relayout(const float* __restrict__ in, float* __restrict__ out
       out[e] = in[blk_real(x, y, z, 1 << ln)];
     }
   }
-}
-
-__global__ void k_scale(float* __restrict__ p, long n, float s) {
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] *= s;
 }
 
 inline int grid_for(long n, int per = kThreads, int cap = 65536) {
@@ -1118,30 +1029,6 @@ void launch_step_inc(uint32_t* ctr, hipStream_t s) {
 void launch_kick_drift(float* pos, float* mom, const float* f, long np, float kick, float drift, float nmesh,
                        hipStream_t s) {
   hipLaunchKernelGGL(k_kick_drift, dim3(grid_for(np)), dim3(kThreads), 0, s, pos, mom, f, np, kick, drift, nmesh);
-}
-
-void launch_spec_to_numpy(const float2* c, const float2* q, float2* out, int n, float scale, hipStream_t s) {
-  const long total = (long)n * n * (n / 2 + 1);
-  hipLaunchKernelGGL(k_spec_pack, dim3(grid_for(total)), dim3(kThreads), 0, s, c, q, out, n, scale, 1);
-}
-
-void launch_spec_from_numpy(const float2* in, float2* c, float2* q, int n, float scale, hipStream_t s) {
-  const long total = (long)n * n * (n / 2 + 1);
-  hipLaunchKernelGGL(k_spec_pack, dim3(grid_for(total)), dim3(kThreads), 0, s, c, q, const_cast<float2*>(in), n,
-                     scale, 0);
-}
-
-void launch_scale(float* p, long n, float v, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale, dim3(grid_for(n)), dim3(kThreads), 0, s, p, n, v);
-}
-
-int power_max_bins() { return kPowerBins; }
-long power_partial_doubles(int n_bins) { return (long)kPowerBlocks * 3 * n_bins; }
-
-void launch_power(const PowerArgs& a, double* out3, hipStream_t s) {
-  hipLaunchKernelGGL(k_power_bins, dim3(kPowerBlocks), dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(k_power_reduce, dim3((3 * a.n_bins + 255) / 256), dim3(256), 0, s, a.partial, kPowerBlocks,
-                     a.n_bins, out3);
 }
 
 }  // namespace pmk

@@ -85,8 +85,6 @@ struct SpecOp {
 // ---- FFT launchers (fft.hip) ---------------------------------------------
 // Forward r2c: z pass (real -> complex + Nyquist plane), then y pass.
 void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s);
-// Forward x pass only (complex, in place), for spectra that are measured.
-void fft_x_forward(const FftTables& t, Field* f, int nf, hipStream_t s);
 // Fused x pass: forward x transform of `in`, spectral op, inverse x
 // transforms written to op.out_*.  `in` may alias out[0].
 void fft_x_fused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s);
@@ -118,7 +116,29 @@ void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipS
                             const BatchArg& bat = BatchArg());
 // Inverse: y pass then z pass (complex + Nyquist plane -> real), unnormalised.
 void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s);
-// Plain inverse x pass (complex, in place).
-void fft_x_inverse(const FftTables& t, Field* f, int nf, hipStream_t s);
+// z passes whose real side is a caller's plain [x][y][z] mesh (16-byte aligned).
+void fft_z_r2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s);
+void fft_z_c2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s);
+// x passes whose spectral side is a caller's numpy-layout half spectrum
+// [kx][ky][kz], kz = 0 .. N/2: forward to it, inverse of scale times it.
+void fft_x_forward_np(const FftTables& t, const Field& f, float2* spec, hipStream_t s);
+void fft_x_inverse_np(const FftTables& t, const float2* spec, const Field& f, float scale, hipStream_t s);
+
+// Binned power spectrum of a field whose z and y transforms are done: forward
+// x transform and binning in one pass.  out holds per bin j = 1 .. n_bins the
+// number of modes, the sum of |n| and the sum of |X|^2, n_bins values each.
+struct PowerArgs {
+  int n_bins = 0;
+  int n_max = 0;                 // > 0: only modes with every |n_d| < n_max
+  int deconv = 0;                // divide |X|^2 by the CIC window squared
+  const float2* c = nullptr;
+  const float2* q = nullptr;
+  const float* wxy = nullptr;
+  const float* wz = nullptr;
+  double* partial = nullptr;     // power_partial_doubles(n_bins) of scratch
+  double* out = nullptr;
+};
+long power_partial_doubles(int n_bins);
+void launch_power(const FftTables& t, const PowerArgs& a, hipStream_t s);
 
 }  // namespace pmk
