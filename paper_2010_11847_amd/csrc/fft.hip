@@ -441,9 +441,25 @@ struct ZGeomL {
   static_assert(L % 8 == 0, "whole (x/8, y) rows per workgroup");
 };
 
-// the in-place passes take 8192 / H lines (64 KB of data) per workgroup
+// Lines per workgroup of the in-place passes: 16 KB of data (2048 / H lines,
+// eight at least), so that eight workgroups share a CU and one's loads run
+// beside another's transform, and on small meshes fewer, so that there is a
+// workgroup for every CU.  With 64 KB the r2c pass ran at two workgroups per
+// CU: 37 -> 26 us at 256^3, 251 -> 192 at 512^3, 1.76 -> 1.58 ms at 1024^3;
+// and on 16 of the CUs at 64^3: 9.2 -> 4.7 us (8 KB measured as 16 KB).
 template <int N>
-using ZGeom = ZGeomL<N, (8192 / (N / 2) < N * N ? 8192 / (N / 2) : N * N)>;
+constexpr int z_lines() {
+  constexpr int by_size = 2048 / (N / 2), by_cus = N * N / 256;
+  constexpr int l = by_size < by_cus ? by_size : by_cus;
+  return l < 8 ? 8 : l;
+}
+template <int N>
+using ZGeom = ZGeomL<N, z_lines<N>()>;
+// The forward pass of 128-point lines stays at 64 KB (8.8 us against 7.0 at
+// 128^3): at every smaller size the compiler fuses other products of its
+// twiddles, and a run amplifies the changed last bits of its start.
+template <int N>
+using ZGeomF = ZGeomL<N, N == 128 ? 128 : z_lines<N>()>;
 
 // copy N16 16-byte words from global memory to LDS (whole workgroup): every
 // load of a thread is issued before its first LDS store, so the loads are in
@@ -606,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void k_r2c_z(float* __restrict__ r0, floa
                                                      const float2* __restrict__ twh,
                                                      const float2* __restrict__ twn, BatchArg bat,
                                                      const float* __restrict__ std_in) {
-  using G = ZGeom<N>;
+  using G = ZGeomF<N>;
   constexpr int H = G::H, L = G::L, ZP = G::ZP;
   __shared__ float2 lds[G::size];
   const long bo = batch_bytes(bat);
@@ -1625,7 +1641,7 @@ void power_x(const FftTables& t, const PowerArgs& a, hipStream_t s) {
 
 template <int N>
 void zr2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg()) {
-  using G = ZGeom<N>;
+  using G = ZGeomF<N>;
   dim3 grid((N * N) / G::L, nf, bat.n);
   hipLaunchKernelGGL((k_r2c_z<N, false>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
                      nf > 2 ? f[2].r : f[0].r, f[0].q, nf > 1 ? f[1].q : f[0].q, nf > 2 ? f[2].q : f[0].q,
@@ -1634,7 +1650,7 @@ void zr2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& b
 
 template <int N>
 void zr2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s) {
-  hipLaunchKernelGGL((k_r2c_z<N, true>), dim3((N * N) / ZGeom<N>::L), dim3(kThreads), 0, s, f.r, f.r, f.r, f.q, f.q,
+  hipLaunchKernelGGL((k_r2c_z<N, true>), dim3((N * N) / ZGeomF<N>::L), dim3(kThreads), 0, s, f.r, f.r, f.r, f.q, f.q,
                      f.q, t.tw_h, t.tw_n, BatchArg(), in);
 }
 
