@@ -24,8 +24,8 @@ struct TileGeom {
   int lnx = 0, lny = 0, lnz = 0;     // log2 of ntx, nty, ntz
 };
 
-// Paint/sort tiles of the n^3 mesh: 16^3 cells, or n/2 per side below 32^3
-// (at least two tiles per side, so that a particle's 7 upper CIC neighbours
+// Paint/sort tiles of the n^3 mesh: 16^3 cells, 8^3 up to 64^3, n/2 per side
+// below 16^3 (at least two tiles per side, so that a particle's 7 upper CIC neighbours
 // never wrap into its own tile).
 TileGeom make_tile_geom(int n);
 

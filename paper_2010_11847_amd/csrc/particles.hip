@@ -901,7 +901,13 @@ inline int grid_for(long n, int per = kThreads, int cap = 65536) {
 TileGeom make_tile_geom(int n) {
   TileGeom g;
   g.n = n;
-  g.tx = g.ty = g.tz = n / 2 < 16 ? n / 2 : 16;
+  // 16^3 tiles of a 64^3 mesh are 64 workgroups of paint, of a 32^3 mesh 8:
+  // 8^3 tiles fill the chip there (paint 13.5 -> 5.0 us at 32^3, 22.4 -> 16.8
+  // for four 64^3 members).  From 128^3 on their boundary, 1.42 deposits per
+  // deposit instead of 1.20, costs more than it gives (four 128^3 members:
+  // 55.6 us with 16^3 tiles, 71.1 with 8^3).
+  const int t = n <= 64 ? 8 : 16;
+  g.tx = g.ty = g.tz = n / 2 < t ? n / 2 : t;
   g.ntx = n / g.tx;
   g.nty = n / g.ty;
   g.ntz = n / g.tz;
