@@ -68,6 +68,7 @@ struct Layout {
   size_t count = 0, off = 0, bsum = 0;
   size_t pw_partial = 0, pw_out = 0;
   size_t misc = 0;   // small device words (the adjoint paint's max |weight|)
+  size_t part = 0;   // the partition's flag and histograms
   size_t steps = 0;  // a run's step loop: counter, checkpoint base, factor table
   size_t red = 0;    // float64 partial sums of the chi^2 reduction
   size_t desc = 0;   // a batch plan's device descriptor table (member 0's)
@@ -150,6 +151,7 @@ Layout make_layout(const pm_config* c) {
   L.pw_partial = take((size_t)pmk::power_partial_doubles(L.n_bins_max) * 8);
   L.pw_out = take((size_t)3 * L.n_bins_max * 8);
   L.misc = take(256);
+  L.part = take((size_t)pmk::kPartitionWords * 4);
   L.steps = take(256 + (size_t)kMaxSteps * 16);
   L.red = take((size_t)(pmk::kReducePartials + 2) * 8);
   L.desc = take((size_t)PM_MAX_BATCH * sizeof(pm_req_desc));
@@ -285,6 +287,7 @@ struct pm_ctx {
   const FftTables& tl_c() const { return tc; }
   float* force_c = nullptr;   // interleaved coarse force, fine-cell units
   uint32_t* misc = nullptr;   // small device words
+  uint32_t* part = nullptr;   // the partition's flag and histograms
   // the step loop of a run: step counter, checkpoint base and per-step
   // factors in device memory, and the captured graphs of one step starting
   // from either ping-pong buffer
@@ -435,6 +438,33 @@ struct pm_ctx {
     timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream); });
     timed(PC_KEYS, [&] { pmk::launch_keys(pos, np, tg, key, count, stream, lat_ln); });
     finish_sort(pos, mom, id, np, dst, lat_ln);
+  }
+  // counting sort of a caller's np positions alone into buffer 0 (with_id:
+  // and their indices).  np != n_part^3 particles may come in any order: from
+  // kPartitionMin up they go through launch_partition, whose copy lies in
+  // mom_s[0], its ids in id_s[1].
+  void sort_positions(const float* pos, long np, bool with_id) {
+    const int lat_ln = np == np3 ? __builtin_ctz((unsigned)npart) : -1;
+    pmk::ScatterArgs a;
+    a.np = np;
+    a.pos = pos;
+    a.key = key;
+    a.cursor = count;
+    a.pos_out = pos_s[0];
+    a.id_out = with_id ? id_s[0] : nullptr;
+    a.lat_ln = lat_ln;
+    if (lat_ln < 0 && np >= pmk::kPartitionMin) {
+      a.part = part;
+      a.part_pos = mom_s[0];
+      a.part_id = with_id ? id_s[1] : nullptr;
+      timed(PC_KEYS, [&] {
+        pmk::launch_partition(pos, np, tg, part, mom_s[0], with_id ? id_s[1] : nullptr, off, a.pos_out, a.id_out, stream);
+      });
+    }
+    timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream); });
+    timed(PC_KEYS, [&] { pmk::launch_keys(pos, np, tg, key, count, stream, lat_ln, a.part, a.part_pos); });
+    timed(PC_SCAN, [&] { pmk::launch_scan(count, L.n_keys, off, bsum, stream, pmk::BatchArg(), a.part); });
+    timed(PC_SCATTER, [&] { pmk::launch_scatter(a, stream); });
   }
   // scan + scatter once the keys and their counts are known
   void finish_sort(const float* pos, const float* mom, const uint32_t* id, long np, int dst, int lat_ln = -1) {
@@ -720,6 +750,7 @@ int create_one(const pm_config* cfg, char* ws, const Layout& L, void* stream, pm
   }
   c->force_i = reinterpret_cast<float*>(w + L.force_i);
   c->misc = reinterpret_cast<uint32_t*>(w + L.misc);
+  c->part = reinterpret_cast<uint32_t*>(w + L.part);
   c->step_ctr = reinterpret_cast<uint32_t*>(w + L.steps);
   c->ckpt_base_dev = reinterpret_cast<float**>(w + L.steps + 64);
   c->step_tab = reinterpret_cast<float4*>(w + L.steps + 256);
@@ -892,7 +923,7 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
 int pm_paint(pm_ctx* ctx, const float* d_pos, int64_t np, float* d_delta) {
   if (!ctx || !d_pos || !d_delta || np < 1 || np > ctx->L.cap) return PM_EINVAL;
   pm_ctx& c = *ctx;
-  c.sort(d_pos, nullptr, nullptr, np, 0);
+  c.sort_positions(d_pos, np, false);
   c.paint(0, np, d_delta, true);
   return c.check("pm_paint");
 }
@@ -900,7 +931,7 @@ int pm_paint(pm_ctx* ctx, const float* d_pos, int64_t np, float* d_delta) {
 int pm_force(pm_ctx* ctx, const float* d_pos, int64_t np, float* d_force) {
   if (!ctx || !d_pos || !d_force || np < 1 || np > ctx->L.cap) return PM_EINVAL;
   pm_ctx& c = *ctx;
-  c.sort(d_pos, nullptr, nullptr, np, 0);
+  c.sort_positions(d_pos, np, true);
   c.paint(0, np, c.mesh[0].r);
   c.force_meshes();
   pmk::ReadoutArgs a = c.readout_args(0, np);

@@ -56,6 +56,9 @@ struct ScatterArgs {
   float* mom_out = nullptr;
   uint32_t* id_out = nullptr;
   int lat_ln = -1;                 // >= 0: the source is in lattice order over 2^(3 lat_ln) particles
+  const uint32_t* part = nullptr;        // the partition's work words (part_mode below)
+  const float* part_pos = nullptr;       // the source in PART_MOVED mode, ids part_id
+  const uint32_t* part_id = nullptr;
   BatchArg bat;                    // batched: every pointer is a workspace pointer of member 0
 };
 
@@ -123,13 +126,31 @@ void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, const Batch
 // tile keys of np particles, counted per key into count (zeroed first)
 // lat_ln >= 0: the np = 2^(3 lat_ln) particles are in lattice order, and the
 // pass walks them brick by brick (lattice_order in pm_device.h)
+// part, part_pos: as in ScatterArgs
 void launch_keys(const float* pos, long np, const TileGeom& g, uint32_t* key, uint32_t* count, hipStream_t s,
-                 int lat_ln = -1);
+                 int lat_ln = -1, const uint32_t* part = nullptr, const float* part_pos = nullptr);
+// Sort of np >= kPartitionMin particles in an unknown order, by a partition
+// into buckets (runs of tiles along their curve).  The device decides the
+// mode and leaves it in `work` (kPartitionWords words of scratch):
+//   PART_NONE    the order is local: nothing is done, the key, scan and
+//                scatter passes that follow sort the particles;
+//   PART_SORTED  scattered, buckets of like size: the whole sort is done
+//                (pos_out, id_out, the offsets off), those passes return;
+//   PART_MOVED   scattered, a bucket too large for one workgroup: the
+//                particles are moved bucket by bucket to part_pos (indices to
+//                part_id), and those passes sort them from there.
+// part_id and id_out are both null or both given.
+enum PartMode : uint32_t { PART_NONE = 0, PART_SORTED = 1, PART_MOVED = 2 };
+constexpr long kPartitionMin = 1L << 17;
+constexpr int kPartitionBuckets = 1024;   // at most
+constexpr int kPartitionWords = 64 + 2 * kPartitionBuckets;
+void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos,
+                      uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s);
 long scan_scratch_words(long n);
 // off = exclusive scan of count[0..n), off[n] = total; count[0..n) is then
 // overwritten with a copy of off[0..n) (the scatter's cursors)
 void launch_scan(uint32_t* count, long n, uint32_t* off, uint32_t* bsum, hipStream_t s,
-                 const BatchArg& bat = BatchArg());
+                 const BatchArg& bat = BatchArg(), const uint32_t* part = nullptr);
 void launch_scatter(const ScatterArgs& a, hipStream_t s);
 // std_layout: write [x][y][z] instead of the x-blocked layout
 void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& g, float* out, float scale,

@@ -91,6 +91,9 @@ __global__ void k_lpt_particles(LptParticleArgs a) {
 }
 
 // ---- counting sort -------------------------------------------------------------
+// mode that launch_partition left in its work words (null: no partition)
+__device__ __forceinline__ uint32_t part_mode(const uint32_t* __restrict__ work) { return work ? work[0] * work[1] : PART_NONE; }
+
 __global__ void k_fill_u32(uint32_t* __restrict__ p, long n, uint32_t v, BatchArg bat) {
   const long bo = batch_bytes(bat);
   if (bo < 0) return;
@@ -104,21 +107,28 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, long n, uint32_t v, BatchAr
 // brick by brick, so that a wave holds a few keys instead of eight tiles'.
 __global__ __launch_bounds__(kThreads) void k_keys(const float* __restrict__ pos, long np, TileGeom g,
                                                    uint32_t* __restrict__ key, uint32_t* __restrict__ count,
-                                                   int lat_ln) {
-  const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool valid = t < np;
-  const long i = valid && lat_ln >= 0 ? lattice_order(t, lat_ln) : t;
-  uint32_t k = 0;
-  if (valid) {
-    int ix, iy, iz;
-    float t;
-    cic_base(pos[3 * i + 0], g.n, ix, t);
-    cic_base(pos[3 * i + 1], g.n, iy, t);
-    cic_base(pos[3 * i + 2], g.n, iz, t);
-    k = tile_key(ix, iy, iz, g);
+                                                   int lat_ln, const uint32_t* __restrict__ part,
+                                                   const float* __restrict__ part_pos) {
+  const uint32_t mode = part_mode(part);   // uniform
+  if (mode == PART_SORTED) return;
+  if (mode == PART_MOVED) pos = part_pos;
+  const long stride = (long)gridDim.x * blockDim.x;
+  for (long b0 = (long)xcd_tile(blockIdx.x, gridDim.x) * blockDim.x; b0 < np; b0 += stride) {
+    const long t = b0 + threadIdx.x;
+    const bool valid = t < np;
+    const long i = valid && lat_ln >= 0 ? lattice_order(t, lat_ln) : t;
+    uint32_t k = 0;
+    if (valid) {
+      int ix, iy, iz;
+      float t;
+      cic_base(pos[3 * i + 0], g.n, ix, t);
+      cic_base(pos[3 * i + 1], g.n, iy, t);
+      cic_base(pos[3 * i + 2], g.n, iz, t);
+      k = tile_key(ix, iy, iz, g);
+    }
+    agg_count(count, k, valid);
+    if (valid) key[i] = k;
   }
-  agg_count(count, k, valid);
-  if (valid) key[i] = k;
 }
 
 // Exclusive scan of count[0..n) into off[0..n], off[n] = total.
@@ -143,7 +153,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* s
 
 __global__ __launch_bounds__(kThreads) void k_scan_local(const uint32_t* __restrict__ cnt, long n,
                                                          uint32_t* __restrict__ off, uint32_t* __restrict__ bsum,
-                                                         BatchArg bat) {
+                                                         BatchArg bat, const uint32_t* __restrict__ part) {
+  if (part_mode(part) == PART_SORTED) return;   // uniform
   __shared__ uint32_t sh[kThreads];
   const long bo = batch_bytes(bat);
   if (bo < 0) return;
@@ -168,7 +179,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_local(const uint32_t* __restr
   if (threadIdx.x == 0) bsum[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kThreads) void k_scan_top(uint32_t* __restrict__ bsum, int nb, BatchArg bat) {
+__global__ __launch_bounds__(kThreads) void k_scan_top(uint32_t* __restrict__ bsum, int nb, BatchArg bat, const uint32_t* __restrict__ part) {
+  if (part_mode(part) == PART_SORTED) return;   // uniform
   __shared__ uint32_t sh[kThreads];
   const long bo = batch_bytes(bat);
   if (bo < 0) return;
@@ -189,7 +201,8 @@ __global__ __launch_bounds__(kThreads) void k_scan_top(uint32_t* __restrict__ bs
 // the scatter's per-key cursors
 __global__ __launch_bounds__(kThreads) void k_scan_add(uint32_t* __restrict__ off, uint32_t* __restrict__ cursor,
                                                        long n, const uint32_t* __restrict__ bsum, int nb,
-                                                       BatchArg bat) {
+                                                       BatchArg bat, const uint32_t* __restrict__ part) {
+  if (part_mode(part) == PART_SORTED) return;   // uniform
   const long bo = batch_bytes(bat);
   if (bo < 0) return;
   off = byte_adv(off, bo);
@@ -204,6 +217,240 @@ __global__ __launch_bounds__(kThreads) void k_scan_add(uint32_t* __restrict__ of
       cursor[base + j] = v;
     }
   if (blockIdx.x == 0 && threadIdx.x == 0) off[n] = bsum[nb];
+}
+
+// ---- sort of scattered particles ------------------------------------------------
+// A caller's particles may come in any order.  Sorted straight from a random
+// order, each particle costs a count atomic, a cursor atomic and a write, each
+// to a memory line of its own, and device-wide atomics run at about 21 per ns
+// whatever they hit: 127 us per million particles at 512^3.  Instead the
+// particles are moved into buckets (runs of tiles along their curve) in runs
+// of a chunk's particles of one bucket, and one workgroup then sorts each
+// bucket, its counts and cursors in LDS: 26 us per million (counting 4,
+// moving 8, sorting 14: the windows that an XCD's workgroups fill at a time
+// exceed its L2).  Whether the order is scattered is decided on the device
+// from a sample, since an ordered catalogue is sorted faster by the passes
+// below.
+//
+// B buckets, and as many threads per workgroup in the first passes: 1024 keep
+// the windows of the last pass smaller (30 million particles: 536 -> 424 us
+// of it), 512 and half the chunk fill the chip with fewer particles (the
+// three passes at 0.2 million: 24.3 us against 32.3).
+constexpr int kPartItems = 8;                               // particles per thread of a chunk
+constexpr int kPartHist = 64, kPartFill = kPartHist + kPartitionBuckets;   // word offsets in `work`
+constexpr int kPartSortThreads = 1024;
+// grid of the key and scatter passes behind a partition: they mostly return
+// at once, and 117000 empty workgroups take 27 us in each
+constexpr int kPartGrid = 16384;
+
+// sort key of a position; the bucket is the key without its low `kbits`
+__device__ __forceinline__ uint32_t part_key(const float* x, const TileGeom& g) {
+  int ix, iy, iz;
+  float t;
+  cic_base(x[0], g.n, ix, t);
+  cic_base(x[1], g.n, iy, t);
+  cic_base(x[2], g.n, iz, t);
+  return tile_key(ix, iy, iz, g);
+}
+
+// exclusive scan over the workgroup's threads (one value each)
+__device__ __forceinline__ uint32_t part_scan(uint32_t v, uint32_t* wsum) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t s = v;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t t = __shfl_up(s, d, 64);
+    if (lane >= d) s += t;
+  }
+  __syncthreads();   // wsum may still be read from an earlier scan
+  if (lane == 63) wsum[w] = s;
+  __syncthreads();
+  for (int i = 0; i < w; ++i) s += wsum[i];
+  return s - v;
+}
+
+// one workgroup: clears the histograms and samples 16 runs of 64 consecutive
+// particles; scattered: neighbours lie in different buckets more often than
+// every fourth time (of particles in lattice order at most every eighth)
+__global__ __launch_bounds__(1024) void k_part_sample(const float* __restrict__ pos, long np, TileGeom g, int kbits,
+                                                      uint32_t* __restrict__ work) {
+  __shared__ uint32_t changes;
+  const int lane = threadIdx.x & 63;
+  const long j = (np - 64) / 15 * (threadIdx.x >> 6) + lane;   // np >= kPartitionMin
+  const float x[3] = {pos[3 * j], pos[3 * j + 1], pos[3 * j + 2]};
+  if (threadIdx.x == 0) changes = 0;
+  for (int i = threadIdx.x; i < 2 * kPartitionBuckets; i += 1024) work[kPartHist + i] = 0u;
+  __syncthreads();
+  const uint32_t b = part_key(x, g) >> kbits;
+  const uint64_t m = __ballot(lane > 0 && b != (uint32_t)__shfl_up((int)b, 1, 64));
+  if (lane == 0) atomicAdd(&changes, (uint32_t)__popcll(m));
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    work[0] = changes > 16 * 16 ? 1u : 0u;
+    work[1] = PART_NONE;
+  }
+}
+
+template <int B>
+__global__ __launch_bounds__(B) void k_part_hist(const float* __restrict__ pos, long np, TileGeom g,
+                                                            int kbits, uint32_t* __restrict__ work) {
+  if (!work[0]) return;   // uniform
+  __shared__ uint32_t h[B];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+  const long stride = (long)gridDim.x * B;
+  for (long i = (long)blockIdx.x * B + threadIdx.x; i < np; i += stride) {
+    const float x[3] = {pos[3 * i], pos[3 * i + 1], pos[3 * i + 2]};
+    atomicAdd(&h[part_key(x, g) >> kbits], 1u);
+  }
+  __syncthreads();
+  const uint32_t c = h[threadIdx.x];
+  if (c) atomicAdd(&work[kPartHist + threadIdx.x], c);
+}
+
+// A chunk of B * kPartItems particles per workgroup: ranked by bucket in LDS,
+// room reserved with one global atomic per bucket and chunk, and written out
+// in runs of the chunk's particles of one bucket.  Workgroup 0 also settles
+// the mode: a bucket of more than four times the mean would keep one
+// workgroup of the next pass busy longer than the rest together.
+template <int B, bool ID>
+__global__ __launch_bounds__(B) void k_part_move(const float* __restrict__ pos, long np, TileGeom g,
+                                                            int kbits, uint32_t* __restrict__ work,
+                                                            float* __restrict__ part_pos,
+                                                            uint32_t* __restrict__ part_id) {
+  if (!work[0]) return;   // uniform
+  constexpr int kPartChunk = B * kPartItems;
+  __shared__ float xs[3 * kPartChunk];
+  __shared__ uint32_t src[ID ? kPartChunk : 1];
+  __shared__ uint16_t bs[kPartChunk];
+  __shared__ uint32_t h[B], start[B], wsum[B / 64];
+  const int tid = threadIdx.x;
+  const long j0 = (long)blockIdx.x * kPartChunk;
+  const int cnt = (int)(np - j0 < kPartChunk ? np - j0 : kPartChunk);
+  h[tid] = 0u;
+  float x[kPartItems][3];
+#pragma unroll
+  for (int k = 0; k < kPartItems; ++k) {
+    const int i = tid + k * B;
+    const long j = j0 + (i < cnt ? i : cnt - 1);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[k][d] = pos[3 * j + d];
+  }
+  const uint32_t total = work[kPartHist + tid];
+  if (blockIdx.x == 0) {
+    const bool large = __syncthreads_or(total > (uint32_t)(np / (B / 4) + 32768));
+    if (tid == 0) work[1] = large ? PART_MOVED : PART_SORTED;
+  }
+  const uint32_t gstart = part_scan(total, wsum);   // first slot of bucket tid (its barriers also order h)
+  uint32_t rank[kPartItems], b[kPartItems];
+#pragma unroll
+  for (int k = 0; k < kPartItems; ++k) {
+    b[k] = part_key(x[k], g) >> kbits;
+    rank[k] = tid + k * B < cnt ? atomicAdd(&h[b[k]], 1u) : 0u;
+  }
+  __syncthreads();
+  const uint32_t c = h[tid];
+  const uint32_t lstart = part_scan(c, wsum);
+  start[tid] = lstart;
+  // slot of the chunk's element e, if it is of bucket tid: h + e (mod 2^32)
+  h[tid] = gstart + (c ? atomicAdd(&work[kPartFill + tid], c) : 0u) - lstart;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kPartItems; ++k) {
+    const int i = tid + k * B;
+    if (i < cnt) {
+      const uint32_t e = start[b[k]] + rank[k];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) xs[3 * e + d] = x[k][d];
+      if (ID) src[e] = (uint32_t)(j0 + i);
+      bs[e] = (uint16_t)b[k];
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < cnt; e += B) {
+    const long d = (long)(uint32_t)(h[bs[e]] + (uint32_t)e);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) part_pos[3 * d + q] = xs[3 * e + q];
+    if (ID) part_id[d] = src[e];
+  }
+}
+
+// One workgroup per bucket: keys counted in LDS, scanned into the offsets of
+// the bucket's 2^kbits keys and the cursors, and the particles written to
+// their places (a window that the XCD's L2 holds while it fills).
+template <bool ID>
+__global__ __launch_bounds__(kPartSortThreads) void k_part_sort(const float* __restrict__ part_pos,
+                                                                const uint32_t* __restrict__ part_id, long np,
+                                                                TileGeom g, int kbits,
+                                                                const uint32_t* __restrict__ work,
+                                                                uint32_t* __restrict__ off,
+                                                                float* __restrict__ pos_out,
+                                                                uint32_t* __restrict__ id_out) {
+  if (part_mode(work) != PART_SORTED) return;   // uniform
+  extern __shared__ uint32_t hist[];            // 2^kbits counts, then cursors
+  __shared__ uint32_t wsum[kPartSortThreads / 64], bounds[2];
+  const int tid = threadIdx.x, bucket = xcd_tile(blockIdx.x, gridDim.x);
+  const uint32_t nk = 1u << kbits;
+  {
+    const uint32_t v = tid < kPartitionBuckets ? work[kPartHist + tid] : 0u;
+    const uint32_t s = part_scan(v, wsum);
+    if (tid == bucket) {
+      bounds[0] = s;
+      bounds[1] = s + v;
+    }
+  }
+  for (uint32_t k = tid; k < nk; k += kPartSortThreads) hist[k] = 0u;
+  __syncthreads();
+  const uint32_t j0 = bounds[0], j1 = bounds[1];
+  constexpr int U = 4;   // particles per thread in flight
+  for (uint32_t b = j0; b < j1; b += U * kPartSortThreads) {
+    float x[U][3];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = b + u * kPartSortThreads + tid;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) x[u][d] = part_pos[3 * (long)(j < j1 ? j : j1 - 1) + d];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b + u * kPartSortThreads + tid < j1) atomicAdd(&hist[part_key(x[u], g) & (nk - 1)], 1u);
+  }
+  __syncthreads();
+  // a thread scans nk / 1024 consecutive counts (one if there are fewer)
+  const uint32_t per = nk > kPartSortThreads ? nk / kPartSortThreads : 1u;
+  uint32_t sum = 0;
+  if (tid * per < nk)
+    for (uint32_t k = 0; k < per; ++k) sum += hist[tid * per + k];
+  uint32_t run = j0 + part_scan(sum, wsum);
+  if (tid * per < nk)
+    for (uint32_t k = 0; k < per; ++k) {
+      const uint32_t c = hist[tid * per + k];
+      hist[tid * per + k] = run;
+      run += c;
+    }
+  __syncthreads();
+  for (uint32_t k = tid; k < nk; k += kPartSortThreads) off[(long)bucket * nk + k] = hist[k];
+  if (bucket == (int)gridDim.x - 1 && tid == 0) off[(long)gridDim.x * nk] = (uint32_t)np;
+  __syncthreads();   // the offsets are out before the cursors move
+  for (uint32_t b = j0; b < j1; b += U * kPartSortThreads) {
+    float x[U][3];
+    uint32_t id[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t j = b + u * kPartSortThreads + tid, jc = j < j1 ? j : j1 - 1;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) x[u][d] = part_pos[3 * (long)jc + d];
+      if (ID) id[u] = part_id[jc];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b + u * kPartSortThreads + tid < j1) {
+        const long d = atomicAdd(&hist[part_key(x[u], g) & (nk - 1)], 1u);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) pos_out[3 * d + q] = x[u][q];
+        if (ID) id_out[d] = id[u];
+      }
+  }
 }
 
 // Each particle's destination is reserved at its key's cursor (one atomic
@@ -226,6 +473,12 @@ __global__ void k_scatter(ScatterArgs a) {
     a.pos_out = byte_adv(a.pos_out, bo);
     a.mom_out = byte_adv(a.mom_out, bo);
     a.id_out = byte_adv(a.id_out, bo);
+  }
+  const uint32_t mode = part_mode(a.part);   // uniform
+  if (mode == PART_SORTED) return;
+  if (mode == PART_MOVED) {
+    a.pos = a.part_pos;
+    a.id = a.part_id;
   }
   // consecutive blocks of particles on one XCD: their destinations form
   // runs that continue from block to block, and the partial cache lines at
@@ -948,24 +1201,52 @@ void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, const Batch
 }
 
 void launch_keys(const float* pos, long np, const TileGeom& g, uint32_t* key, uint32_t* count,
-                 hipStream_t s, int lat_ln) {
-  const int grid = (int)((np + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL(k_keys, dim3(grid), dim3(kThreads), 0, s, pos, np, g, key, count, lat_ln);
+                 hipStream_t s, int lat_ln, const uint32_t* part, const float* part_pos) {
+  const int grid = grid_for(np, kThreads, part ? kPartGrid : 1 << 30);
+  hipLaunchKernelGGL(k_keys, dim3(grid), dim3(kThreads), 0, s, pos, np, g, key, count, lat_ln, part, part_pos);
+}
+
+namespace {
+template <int B, bool ID>
+void partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos, uint32_t* part_id,
+               uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s) {
+  int kbits = 6, nb = g.ntiles;   // at most B buckets of 2^kbits keys (64 per tile)
+  for (; nb > B; nb >>= 1) ++kbits;
+  hipLaunchKernelGGL(k_part_sample, dim3(1), dim3(1024), 0, s, pos, np, g, kbits, work);
+  hipLaunchKernelGGL(k_part_hist<B>, dim3(grid_for(np, B * 16, 512 * 1024 / B)), dim3(B), 0, s, pos, np, g, kbits, work);
+  hipLaunchKernelGGL((k_part_move<B, ID>), dim3(grid_for(np, B * kPartItems, 1 << 30)), dim3(B), 0, s, pos, np, g,
+                     kbits, work, part_pos, part_id);
+  // LDS: the bucket's keys, at most 64 KB (kbits = 14 at 1024^3 and B = 512)
+  hipLaunchKernelGGL(k_part_sort<ID>, dim3(nb), dim3(kPartSortThreads), (size_t)4 << kbits, s, part_pos, part_id, np,
+                     g, kbits, work, off, pos_out, id_out);
+}
+}  // namespace
+
+void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos,
+                      uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s) {
+  const bool large = np >= (1L << 23);
+  if (part_id)
+    large ? partition<1024, true>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s)
+          : partition<512, true>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s);
+  else
+    large ? partition<1024, false>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s)
+          : partition<512, false>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s);
 }
 
 long scan_scratch_words(long n) { return (n + kScanBlock - 1) / kScanBlock + 1; }
 
-void launch_scan(uint32_t* count, long n, uint32_t* off, uint32_t* bsum, hipStream_t s, const BatchArg& bat) {
+void launch_scan(uint32_t* count, long n, uint32_t* off, uint32_t* bsum, hipStream_t s, const BatchArg& bat,
+                 const uint32_t* part) {
   const int nb = (int)((n + kScanBlock - 1) / kScanBlock);
-  hipLaunchKernelGGL(k_scan_local, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, count, n, off, bsum, bat);
-  hipLaunchKernelGGL(k_scan_top, dim3(1, 1, bat.n), dim3(kThreads), 0, s, bsum, nb, bat);
-  hipLaunchKernelGGL(k_scan_add, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, off, count, n, bsum, nb, bat);
+  hipLaunchKernelGGL(k_scan_local, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, count, n, off, bsum, bat, part);
+  hipLaunchKernelGGL(k_scan_top, dim3(1, 1, bat.n), dim3(kThreads), 0, s, bsum, nb, bat, part);
+  hipLaunchKernelGGL(k_scan_add, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, off, count, n, bsum, nb, bat, part);
 }
 
 void launch_scatter(const ScatterArgs& a, hipStream_t s) {
   // one particle per thread: the key -> cursor -> store chain of each
   // particle is latency bound, so many short waves overlap it best
-  hipLaunchKernelGGL(k_scatter, dim3(grid_for(a.np, kThreads, 1 << 30), 1, a.bat.n), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(k_scatter, dim3(grid_for(a.np, kThreads, a.part ? kPartGrid : 1 << 30), 1, a.bat.n), dim3(kThreads), 0, s, a);
 }
 
 void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& g, float* out, float scale,
