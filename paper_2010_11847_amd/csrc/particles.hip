@@ -239,9 +239,10 @@ __global__ __launch_bounds__(kThreads) void k_scan_add(uint32_t* __restrict__ of
 constexpr int kPartItems = 8;                               // particles per thread of a chunk
 constexpr int kPartHist = 64, kPartFill = kPartHist + kPartitionBuckets;   // word offsets in `work`
 constexpr int kPartSortThreads = 1024;
-// grid of the key and scatter passes behind a partition: they mostly return
-// at once, and 117000 empty workgroups take 27 us in each
-constexpr int kPartGrid = 16384;
+// most workgroups of the key and scatter passes behind a partition: they
+// mostly return at once (117000 empty workgroups take 27 us in each), but an
+// ordered set needs them in flight (16384 made its scatter 10% slower)
+constexpr int kPartGrid = 65536;
 
 // sort key of a position; the bucket is the key without its low `kbits`
 __device__ __forceinline__ uint32_t part_key(const float* x, const TileGeom& g) {
