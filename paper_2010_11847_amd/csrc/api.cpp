@@ -45,6 +45,7 @@ struct Range {
 constexpr double kPi = 3.14159265358979323846;
 constexpr size_t kAlign = 256;
 constexpr int kMaxSteps = 65536;   // steps per run (the device step table)
+constexpr int kTabHead = 16;       // float4 of the step table's header (counter, checkpoint base)
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
@@ -152,7 +153,7 @@ Layout make_layout(const pm_config* c) {
   L.pw_out = take((size_t)3 * L.n_bins_max * 8);
   L.misc = take(256);
   L.part = take((size_t)pmk::kPartitionWords * 4);
-  L.steps = take(256 + (size_t)kMaxSteps * 16);
+  L.steps = take((size_t)(kTabHead + kMaxSteps) * 16);
   L.red = take((size_t)(pmk::kReducePartials + 2) * 8);
   L.desc = take((size_t)PM_MAX_BATCH * sizeof(pm_req_desc));
   L.cola = take((size_t)kMaxSteps * 16);
@@ -366,7 +367,7 @@ struct pm_ctx {
     bool active = false;
     int ns = 0, step = 0, cur = 0;
     std::vector<double> k1, dr, k2;
-    std::vector<float4> tab;   // host copy of the device step table
+    std::vector<float4> tab;   // host copy of the device step table and its header
     float *pos = nullptr, *mom = nullptr, *ckpt = nullptr;
     bool fck = false;          // force meshes go to the checkpoint slots
     std::vector<float4> cola_tab;                 // COLA: host copy of the frame factors
@@ -394,7 +395,25 @@ struct pm_ctx {
 
   int fail(int code, const std::string& m) {
     err = m;
+    if (code == PM_EHIP) (plan ? plan : this)->counts_dirty = true;   // a sequence may have ended between its sort and its paint
     return code;
+  }
+  // The sort's counts are zero between calls: pm_create clears them and the
+  // paint behind every sort does (a fill of its own cost 5 us a step).  After
+  // an error, noted on the plan that owns the workspace, all of its members'
+  // are cleared again; a clear that is only being recorded into a caller's
+  // graph leaves the flag set.
+  bool counts_dirty = false;
+  void clear_counts() {
+    timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream); });
+  }
+  void check_counts() {
+    pm_ctx* o = plan ? plan : this;
+    if (!o->counts_dirty) return;
+    if (o->members.empty()) o->clear_counts();
+    for (pm_ctx* m : o->members) m->clear_counts();
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    o->counts_dirty = hipStreamIsCapturing(stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone;
   }
   int check(const char* where) {
     const hipError_t e = hipGetLastError();
@@ -435,7 +454,7 @@ struct pm_ctx {
   // by brick)
   void sort(const float* pos, const float* mom, const uint32_t* id, long np, int dst) {
     const int lat_ln = np == np3 ? __builtin_ctz((unsigned)npart) : -1;
-    timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream); });
+    check_counts();
     timed(PC_KEYS, [&] { pmk::launch_keys(pos, np, tg, key, count, stream, lat_ln); });
     finish_sort(pos, mom, id, np, dst, lat_ln);
   }
@@ -461,14 +480,16 @@ struct pm_ctx {
         pmk::launch_partition(pos, np, tg, part, mom_s[0], with_id ? id_s[1] : nullptr, off, a.pos_out, a.id_out, stream);
       });
     }
-    timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream); });
+    check_counts();
     timed(PC_KEYS, [&] { pmk::launch_keys(pos, np, tg, key, count, stream, lat_ln, a.part, a.part_pos); });
     timed(PC_SCAN, [&] { pmk::launch_scan(count, L.n_keys, off, bsum, stream, pmk::BatchArg(), a.part); });
     timed(PC_SCATTER, [&] { pmk::launch_scatter(a, stream); });
   }
   // scan + scatter once the keys and their counts are known
-  void finish_sort(const float* pos, const float* mom, const uint32_t* id, long np, int dst, int lat_ln = -1) {
-    timed(PC_SCAN, [&] { pmk::launch_scan(count, L.n_keys, off, bsum, stream); });
+  // (ctr: a step counter that the scan advances)
+  void finish_sort(const float* pos, const float* mom, const uint32_t* id, long np, int dst, int lat_ln = -1,
+                   uint32_t* ctr = nullptr) {
+    timed(PC_SCAN, [&] { pmk::launch_scan(count, L.n_keys, off, bsum, stream, pmk::BatchArg(), nullptr, ctr); });
     pmk::ScatterArgs a;
     a.np = np;
     a.pos = pos;
@@ -486,7 +507,7 @@ struct pm_ctx {
   // mesh instead of the internal x-blocked one
   void paint(int cur, long np, float* out, bool std_layout = false) {
     const double scale = (double)ng * ng * ng / (double)np;
-    timed(PC_PAINT, [&] { pmk::launch_paint(pos_s[cur], off, tg, out, (float)scale, -1.f, std_layout, stream); });
+    timed(PC_PAINT, [&] { pmk::launch_paint(pos_s[cur], off, tg, out, (float)scale, -1.f, count, std_layout, stream); });
   }
   // force meshes of an n^3 grid (tables t, fields f[0..2], overdensity in
   // f[0].r, overwritten) into the interleaved mesh out; scale multiplies the
@@ -600,7 +621,6 @@ struct pm_ctx {
     bat.stride = (long)mstride;
     bat.n = n;
     const long np = np3;
-    timed(PC_FILL, [&] { pmk::launch_fill_u32(count, L.n_keys, 0u, stream, bat); });
     pmk::ReadoutArgs a = readout_args(0, np);
     a.fi = force_i;
     a.flags = pmk::RO_KICK | pmk::RO_DRIFT | pmk::RO_KEYS | pmk::RO_TO_ALT;
@@ -624,7 +644,7 @@ struct pm_ctx {
     timed(PC_SCATTER, [&] { pmk::launch_scatter(sa, stream); });
     const double scale = (double)ng * ng * ng / (double)np;
     timed(PC_PAINT, [&] {
-      pmk::launch_paint(pos_s[0], off, tg, mesh[0].r, (float)scale, -1.f, false, stream, bat);
+      pmk::launch_paint(pos_s[0], off, tg, mesh[0].r, (float)scale, -1.f, count, false, stream, bat);
     });
     const double g = 1.5 * cfg.cosmo.omega_m;
     force_on(tm, mesh, force_i, ng, g / ((double)ng * ng * ng), cfg.deconv_order, cfg.split_mode, -1, bat);
@@ -786,6 +806,7 @@ int create_one(const pm_config* cfg, char* ws, const Layout& L, void* stream, pm
       pk[n2] = n2 == 0 ? 0.f : (float)(std::sqrt(c->cosmo.pk(k) / vcell) / n3);
     }
   }
+  // (the copy covers the sort's counts, which start at zero)
   hipError_t e = hipMemcpyAsync(w, host.data(), L.mesh[0], hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) {
@@ -973,9 +994,11 @@ int pm_run_begin(pm_ctx* ctx, const double* h_a, int n_a, float* d_pos, float* d
     if (d_ckpt) return c.fail(PM_EINVAL, "pm_run_begin: no checkpoints with the COLA integrator");
   }
   c.factors(h_a, n_a, r.k1.data(), r.dr.data(), r.k2.data());
-  r.tab.resize(r.ns);
+  // step counter (0), checkpoint base and factors, as they lie in the workspace
+  r.tab.assign(kTabHead + r.ns, make_float4(0.f, 0.f, 0.f, 0.f));
+  std::memcpy(reinterpret_cast<char*>(r.tab.data()) + 64, &d_ckpt, sizeof(float*));
   for (int i = 0; i < r.ns; ++i)
-    r.tab[i] = make_float4(i ? (float)r.k2[i - 1] : 0.f, (float)r.k1[i], (float)r.dr[i], 0.f);
+    r.tab[kTabHead + i] = make_float4(i ? (float)r.k2[i - 1] : 0.f, (float)r.k1[i], (float)r.dr[i], 0.f);
   r.pos = d_pos;
   r.mom = d_mom;
   r.ckpt = d_ckpt;
@@ -983,12 +1006,10 @@ int pm_run_begin(pm_ctx* ctx, const double* h_a, int n_a, float* d_pos, float* d
   r.step = 0;
   const long np = c.np3;
   if (r.ns > 0) {
-    hipError_t e = hipMemcpyAsync(c.step_tab, r.tab.data(), (size_t)r.ns * sizeof(float4), hipMemcpyHostToDevice,
-                                  c.stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(c.ckpt_base_dev, &r.ckpt, sizeof(float*), hipMemcpyHostToDevice, c.stream);
+    const hipError_t e = hipMemcpyAsync(c.step_ctr, r.tab.data(), r.tab.size() * sizeof(float4), hipMemcpyHostToDevice,
+                                        c.stream);
     if (e != hipSuccess) return c.fail(PM_EHIP, std::string("pm_run_begin: ") + hipGetErrorString(e));
   }
-  pmk::launch_fill_u32(c.step_ctr, 1, 0u, c.stream);
   r.fck = c.fck && n_a <= c.fck_slots;
   Range rg("pm_run_begin");
   c.sort(d_pos, d_mom, nullptr, np, r.cur);
@@ -1028,7 +1049,6 @@ int pm_run_advance(pm_ctx* ctx, int max_steps, int* h_remaining) {
   // from the device step table at the device step counter
   auto enqueue_step = [&](int cur, int i) {
     Range rg("pm_kdk_step", i);
-    c.timed(PC_FILL, [&] { pmk::launch_fill_u32(c.count, c.L.n_keys, 0u, c.stream); });
     pmk::ReadoutArgs a = c.readout_args(cur, np);
     a.flags = pmk::RO_KICK | pmk::RO_DRIFT | pmk::RO_WRITE_SORTED | pmk::RO_KEYS | (r.ckpt ? pmk::RO_CKPT : 0);
     if (c.cola()) {
@@ -1042,11 +1062,11 @@ int pm_run_advance(pm_ctx* ctx, int max_steps, int* h_remaining) {
     a.ckpt_base = c.ckpt_base_dev;
     a.ckpt_stride = np * 3;
     c.readout(a);
-    c.finish_sort(c.pos_s[cur], c.mom_s[cur], c.id_s[cur], np, 1 - cur);
+    c.finish_sort(c.pos_s[cur], c.mom_s[cur], c.id_s[cur], np, 1 - cur, -1, c.step_ctr);
     c.paint(1 - cur, np, c.mesh[0].r);
     c.force_meshes(r.fck ? c.fck_slot(i + 1) : nullptr);
-    pmk::launch_step_inc(c.step_ctr, c.stream);
   };
+  c.check_counts();
   // (force checkpoints move the output every step: launched eagerly)
   const bool graphs = c.use_graphs && !c.prof.on && !r.fck;
   if (graphs && (c.g_np != np || c.g_ckpt != (r.ckpt != nullptr))) {
@@ -1129,6 +1149,7 @@ int pm_kdk_step_batched(pm_ctx* plan, const pm_req_desc* d_descs, int n) {
   if (!plan) return PM_EINVAL;
   if (plan->batch < 2 || plan->plan) return plan->fail(PM_EINVAL, "pm_kdk_step_batched: not a batch plan");
   if (!d_descs || n < 1 || n > plan->batch) return plan->fail(PM_EINVAL, "pm_kdk_step_batched: bad descriptors");
+  plan->check_counts();
   plan->batched_step(d_descs, n);
   return plan->check("pm_kdk_step_batched");
 }
@@ -1161,9 +1182,9 @@ int pm_batch_advance(pm_ctx* plan, int* h_stepped) {
     const int i = r.step;
     const size_t ck = (size_t)p.np3 * 3;
     d.member = m;
-    d.kick_close = r.tab[i].x;
-    d.kick_open = r.tab[i].y;
-    d.drift = r.tab[i].z;
+    d.kick_close = r.tab[kTabHead + i].x;
+    d.kick_open = r.tab[kTabHead + i].y;
+    d.drift = r.tab[kTabHead + i].z;
     if (r.ckpt) {
       d.flags = PM_REQ_CKPT;
       d.ckpt_x = r.ckpt + (2 * (size_t)i) * ck;
@@ -1173,6 +1194,7 @@ int pm_batch_advance(pm_ctx* plan, int* h_stepped) {
   }
   if (h_stepped) *h_stepped = k;
   if (!k) return PM_OK;
+  p.check_counts();
   // pageable source: the copy has left desc_host when the call returns
   hipError_t e = hipMemcpyAsync(p.desc_dev, p.desc_host.data(), (size_t)k * sizeof(pm_req_desc),
                                 hipMemcpyHostToDevice, p.stream);
@@ -1237,7 +1259,9 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
   auto ckpt_x = [&](int i) { return d_ckpt + 2 * (size_t)i * ck; };
   const double s = (double)c.ng * c.ng * c.ng / (double)np;
   // loss on the final overdensity: x_bar += paint^T-gradient of s * delta_bar
+  bool sorted = false;   // the final positions are sorted, with no paint behind the sort yet
   if (d_grad_delta_final) {
+    sorted = true;
     c.sort(ckpt_x(ns), nullptr, nullptr, np, 0);
     pmk::launch_readout_grad1(c.pos_s[0], c.id_s[0], np, c.ng, d_grad_delta_final, (float)s, xbar, true,
                               c.stream);
@@ -1249,7 +1273,9 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
     Range rg("pm_adjoint_step", j);
     const double kj = (j < ns ? k1[j] : 0.0) + (j > 0 ? k2[j - 1] : 0.0);
     if (kj != 0.0) {
-      c.sort(ckpt_x(j), nullptr, nullptr, np, 0);
+      if (sorted && j < ns) c.clear_counts();
+      if (!sorted || j < ns) c.sort(ckpt_x(j), nullptr, nullptr, np, 0);
+      sorted = false;
       const float* fmesh = c.force_i;
       if (use_fck) {
         fmesh = c.fck_slot(j);
@@ -1267,7 +1293,7 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
       pmk::launch_absmax(pbar, 3 * np, c.misc, c.stream);
       // the three channels in one launch (the meshes are equally spaced)
       pmk::launch_paint_weighted(c.pos_s[0], c.id_s[0], c.off, c.tg, pbar, -1, (float)kj, c.misc, c.mesh[0].r,
-                                 c.stream, (long)(c.mesh[1].r - c.mesh[0].r));
+                                 c.count, c.stream, (long)(c.mesh[1].r - c.mesh[0].r));
       // pyramid force: F_d^T m = G_d^T (m - E R m) + 2^f E G_c,d^T R m
       // (R = REDUCE, E = EXPAND); the interleaved force mesh, read by term A
       // above, is free scratch here
@@ -1335,6 +1361,7 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
     }
     if (j > 0) pmk::launch_axpy(pbar, xbar, (float)dr[j - 1], (long)ck, c.stream);
   }
+  if (sorted) c.clear_counts();   // no step, so no paint behind the sort
   if (!d_grad_noise) return c.check("pm_run_adjoint");
 
   // Gen-IC: noise_bar from (x0_bar, p0_bar)

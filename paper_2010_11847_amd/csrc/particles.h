@@ -123,7 +123,7 @@ void launch_relayout(const float* in, float* out, int n_side, bool to_blocked, h
 void launch_lpt_delta2(float* const* phi6, long n, float* out, hipStream_t s);
 void launch_lpt_particles(const LptParticleArgs& a, hipStream_t s);
 void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, const BatchArg& bat = BatchArg());
-// tile keys of np particles, counted per key into count (zeroed first)
+// tile keys of np particles, counted per key into count (all zero before)
 // lat_ln >= 0: the np = 2^(3 lat_ln) particles are in lattice order, and the
 // pass walks them brick by brick (lattice_order in pm_device.h)
 // part, part_pos: as in ScatterArgs
@@ -148,16 +148,17 @@ void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* wo
                       uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s);
 long scan_scratch_words(long n);
 // off = exclusive scan of count[0..n), off[n] = total; count[0..n) is then
-// overwritten with a copy of off[0..n) (the scatter's cursors)
+// overwritten with a copy of off[0..n) (the scatter's cursors); *step_ctr += 1
+// when given (the step counter of a run's device-side step loop)
 void launch_scan(uint32_t* count, long n, uint32_t* off, uint32_t* bsum, hipStream_t s,
-                 const BatchArg& bat = BatchArg(), const uint32_t* part = nullptr);
+                 const BatchArg& bat = BatchArg(), const uint32_t* part = nullptr, uint32_t* step_ctr = nullptr);
 void launch_scatter(const ScatterArgs& a, hipStream_t s);
-// std_layout: write [x][y][z] instead of the x-blocked layout
+// std_layout: write [x][y][z] instead of the x-blocked layout.  Every paint
+// zeroes clear[0 .. 64 ntiles): the counts of the sort before it, which the
+// scatter has used up, so that the next sort counts into zeroes.
 void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& g, float* out, float scale,
-                  float offset, bool std_layout, hipStream_t s, const BatchArg& bat = BatchArg());
+                  float offset, uint32_t* clear, bool std_layout, hipStream_t s, const BatchArg& bat = BatchArg());
 void launch_readout(const ReadoutArgs& a, hipStream_t s);
-// *ctr += 1 (the step counter of a run's device-side step loop)
-void launch_step_inc(uint32_t* ctr, hipStream_t s);
 // *bits = bit pattern of max_i |v_i| over n floats
 void launch_absmax(const float* v, long n, uint32_t* bits, hipStream_t s);
 // x-blocked paint of signed masses wts[3 id + comp] * k (the adjoint's
@@ -165,8 +166,8 @@ void launch_absmax(const float* v, long n, uint32_t* bits, hipStream_t s);
 // comp < 0: the three components in one launch, component d into
 // out + d * out_stride.
 void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, const uint32_t* off, const TileGeom& g,
-                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, hipStream_t s,
-                           long out_stride = 0);
+                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, uint32_t* clear,
+                           hipStream_t s, long out_stride = 0);
 void launch_kick_drift(float* pos, float* mom, const float* f, long np, float kick, float drift, float nmesh,
                        hipStream_t s);
 // mom[j] += u1 psi1[id[j]] + u2 psi2[id[j]] over np sorted particles (the

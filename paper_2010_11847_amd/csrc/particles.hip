@@ -131,92 +131,132 @@ __global__ __launch_bounds__(kThreads) void k_keys(const float* __restrict__ pos
   }
 }
 
-// Exclusive scan of count[0..n) into off[0..n], off[n] = total.
-constexpr int kScanItems = 8;
-constexpr int kScanBlock = kThreads * kScanItems;
+// Exclusive scan of count[0..n) into off[0..n], off[n] = total; the counts
+// become a copy of the offsets, the scatter's per-key cursors.  A workgroup
+// takes C chunks of four keys per thread, all its loads in flight at once.
+// Up to kScanOne keys (meshes up to 128^3) one workgroup scans them all;
+// larger arrays take a pass of block sums, which every block of the second
+// pass adds up for itself.  (Three launches, local scan, scan of the sums, add:
+// 14 us a step at any mesh up to 256^3, all of it launch and round trips.)
+// The scan runs once per step of a run and also advances its step counter.
+constexpr int kScanOneThreads = 1024, kScanThreads = 256, kScanChunks = 8;
+constexpr long kScanOne = 4L * kScanOneThreads * kScanChunks;      // 32768 keys
+constexpr long kScanBlock = 4L * kScanThreads * kScanChunks;       // 8192 keys
 
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* sh, uint32_t& total) {
-  const int tid = threadIdx.x;
-  sh[tid] = v;
-  __syncthreads();
-  for (int o = 1; o < kThreads; o <<= 1) {
-    const uint32_t add = tid >= o ? sh[tid - o] : 0u;
-    __syncthreads();
-    sh[tid] += add;
-    __syncthreads();
+template <int TH>
+__device__ __forceinline__ void scan_load(const uint32_t* __restrict__ cnt, long base, long n, uint4 (&v)[kScanChunks]) {
+#pragma unroll
+  for (int c = 0; c < kScanChunks; ++c) {
+    const long i = base + 4L * (c * TH + (int)threadIdx.x);   // n is a multiple of 64
+    v[c] = i < n ? *reinterpret_cast<const uint4*>(cnt + i) : make_uint4(0u, 0u, 0u, 0u);
   }
-  total = sh[kThreads - 1];
-  const uint32_t incl = sh[tid];
-  __syncthreads();
-  return incl - v;
 }
 
-__global__ __launch_bounds__(kThreads) void k_scan_local(const uint32_t* __restrict__ cnt, long n,
-                                                         uint32_t* __restrict__ off, uint32_t* __restrict__ bsum,
-                                                         BatchArg bat, const uint32_t* __restrict__ part) {
+// scans a workgroup's keys, `first` before them
+template <int TH>
+__device__ __forceinline__ void scan_store(const uint4 (&v)[kScanChunks], uint32_t first, uint32_t* __restrict__ off,
+                                               uint32_t* __restrict__ cursor, long base, long n) {
+  constexpr int NW = TH / 64, NS = NW * kScanChunks;   // waves, wave sums
+  __shared__ uint32_t ws[NS];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t ex[kScanChunks];
+#pragma unroll
+  for (int c = 0; c < kScanChunks; ++c) {
+    const uint32_t s = v[c].x + v[c].y + v[c].z + v[c].w;
+    uint32_t incl = s;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t t = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += t;
+    }
+    ex[c] = incl - s;
+    if (lane == 63) ws[c * NW + w] = incl;
+  }
+  __syncthreads();
+  if (threadIdx.x < 64) {   // exclusive scan of the NS <= 128 wave sums, two per lane
+    const uint32_t a = 2 * lane < NS ? ws[2 * lane] : 0u, b = 2 * lane + 1 < NS ? ws[2 * lane + 1] : 0u;
+    uint32_t incl = a + b;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t t = __shfl_up(incl, d, 64);
+      if (lane >= d) incl += t;
+    }
+    if (2 * lane < NS) ws[2 * lane] = incl - a - b;
+    if (2 * lane + 1 < NS) ws[2 * lane + 1] = incl - b;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < kScanChunks; ++c) {
+    const long i = base + 4L * (c * TH + (int)threadIdx.x);
+    if (i < n) {
+      uint4 o;
+      o.x = first + ws[c * NW + w] + ex[c];
+      o.y = o.x + v[c].x;
+      o.z = o.y + v[c].y;
+      o.w = o.z + v[c].z;
+      *reinterpret_cast<uint4*>(off + i) = o;
+      *reinterpret_cast<uint4*>(cursor + i) = o;
+      if (i + 4 == n) off[n] = o.w + v[c].w;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kScanOneThreads) void k_scan_one(uint32_t* __restrict__ cnt, long n,
+                                                              uint32_t* __restrict__ off, uint32_t* __restrict__ ctr,
+                                                              BatchArg bat, const uint32_t* __restrict__ part) {
   if (part_mode(part) == PART_SORTED) return;   // uniform
-  __shared__ uint32_t sh[kThreads];
+  const long bo = batch_bytes(bat);
+  if (bo < 0) return;
+  cnt = byte_adv(cnt, bo);
+  off = byte_adv(off, bo);
+  if (ctr && threadIdx.x == 0) *ctr += 1u;
+  uint4 v[kScanChunks];
+  scan_load<kScanOneThreads>(cnt, 0, n, v);
+  scan_store<kScanOneThreads>(v, 0u, off, cnt, 0, n);
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t* __restrict__ cnt, long n,
+                                                            uint32_t* __restrict__ bsum, BatchArg bat,
+                                                            const uint32_t* __restrict__ part) {
+  if (part_mode(part) == PART_SORTED) return;   // uniform
+  __shared__ uint32_t red[kScanThreads / 64];
+  const long bo = batch_bytes(bat);
+  if (bo < 0) return;
+  cnt = byte_adv(cnt, bo);
+  bsum = byte_adv(bsum, bo);
+  uint4 v[kScanChunks];
+  scan_load<kScanThreads>(cnt, (long)blockIdx.x * kScanBlock, n, v);
+  uint32_t s = 0;
+#pragma unroll
+  for (int c = 0; c < kScanChunks; ++c) s += v[c].x + v[c].y + v[c].z + v[c].w;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) bsum[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restrict__ cnt, long n,
+                                                             uint32_t* __restrict__ off,
+                                                             const uint32_t* __restrict__ bsum,
+                                                             uint32_t* __restrict__ ctr, BatchArg bat,
+                                                             const uint32_t* __restrict__ part) {
+  if (part_mode(part) == PART_SORTED) return;   // uniform
+  __shared__ uint32_t red[kScanThreads / 64];
   const long bo = batch_bytes(bat);
   if (bo < 0) return;
   cnt = byte_adv(cnt, bo);
   off = byte_adv(off, bo);
   bsum = byte_adv(bsum, bo);
-  const long base = (long)blockIdx.x * kScanBlock + (long)threadIdx.x * kScanItems;
-  uint32_t v[kScanItems];
-  uint32_t s = 0;
-#pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    v[j] = base + j < n ? cnt[base + j] : 0u;
-    s += v[j];
-  }
-  uint32_t total;
-  uint32_t run = block_exclusive_scan(s, sh, total);
-#pragma unroll
-  for (int j = 0; j < kScanItems; ++j) {
-    if (base + j < n) off[base + j] = run;
-    run += v[j];
-  }
-  if (threadIdx.x == 0) bsum[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(kThreads) void k_scan_top(uint32_t* __restrict__ bsum, int nb, BatchArg bat, const uint32_t* __restrict__ part) {
-  if (part_mode(part) == PART_SORTED) return;   // uniform
-  __shared__ uint32_t sh[kThreads];
-  const long bo = batch_bytes(bat);
-  if (bo < 0) return;
-  bsum = byte_adv(bsum, bo);
-  uint32_t carry = 0;
-  for (int c0 = 0; c0 < nb; c0 += kThreads) {
-    const int i = c0 + threadIdx.x;
-    const uint32_t v = i < nb ? bsum[i] : 0u;
-    uint32_t total;
-    const uint32_t ex = block_exclusive_scan(v, sh, total);
-    if (i < nb) bsum[i] = carry + ex;
-    carry += total;
-  }
-  if (threadIdx.x == 0) bsum[nb] = carry;
-}
-
-// adds the block carries and copies the offsets into the (consumed) counts:
-// the scatter's per-key cursors
-__global__ __launch_bounds__(kThreads) void k_scan_add(uint32_t* __restrict__ off, uint32_t* __restrict__ cursor,
-                                                       long n, const uint32_t* __restrict__ bsum, int nb,
-                                                       BatchArg bat, const uint32_t* __restrict__ part) {
-  if (part_mode(part) == PART_SORTED) return;   // uniform
-  const long bo = batch_bytes(bat);
-  if (bo < 0) return;
-  off = byte_adv(off, bo);
-  cursor = byte_adv(cursor, bo);
-  bsum = byte_adv(bsum, bo);
+  if (ctr && blockIdx.x == 0 && threadIdx.x == 0) *ctr += 1u;
   const long base = (long)blockIdx.x * kScanBlock;
-  const uint32_t add = bsum[blockIdx.x];
-  for (int j = threadIdx.x; j < kScanBlock; j += kThreads)
-    if (base + j < n) {
-      const uint32_t v = off[base + j] + add;
-      off[base + j] = v;
-      cursor[base + j] = v;
-    }
-  if (blockIdx.x == 0 && threadIdx.x == 0) off[n] = bsum[nb];
+  uint4 v[kScanChunks];
+  scan_load<kScanThreads>(cnt, base, n, v);
+  uint32_t s = 0;   // keys before this block
+  for (int b = threadIdx.x; b < (int)blockIdx.x; b += kScanThreads) s += bsum[b];
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  scan_store<kScanThreads>(v, red[0] + red[1] + red[2] + red[3], off, cnt, base, n);
 }
 
 // ---- sort of scattered particles ------------------------------------------------
@@ -549,7 +589,7 @@ constexpr int kPaintPersistentGroups = 1024;
 template <bool STD, bool WT>
 __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict__ pos, const uint32_t* __restrict__ off,
                                                     TileGeom g, float* __restrict__ out, float scale, float offset,
-                                                    PaintWeights pw, BatchArg bat) {
+                                                    PaintWeights pw, BatchArg bat, uint32_t* __restrict__ clear) {
   __shared__ __align__(16) unsigned long long acc[kTileCells];
   __shared__ RangeTable rt;
   {
@@ -558,7 +598,10 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
     pos = byte_adv(pos, bo);
     off = byte_adv(off, bo);
     out = byte_adv(out, bo);
+    clear = byte_adv(clear, bo);
   }
+  // the sort's spent cursors, the counts of the next sort
+  if (blockIdx.y == 0 && threadIdx.x < 64) clear[(long)blockIdx.x * 64 + threadIdx.x] = 0u;
   if (WT && pw.comp < 0) {   // uniform: one component per blockIdx.y
     pw.comp = (int)blockIdx.y;
     out += blockIdx.y * pw.out_stride;
@@ -701,7 +744,7 @@ template <bool STD>
 __global__ __launch_bounds__(kPaintThreads) void k_paint_p(const float* __restrict__ pos,
                                                            const uint32_t* __restrict__ off, TileGeom g,
                                                            float* __restrict__ out, float scale, float offset,
-                                                           BatchArg bat) {
+                                                           BatchArg bat, uint32_t* __restrict__ clear) {
   __shared__ __align__(16) unsigned long long acc[kTileCells];
   __shared__ RangeTable rt[2];
   {
@@ -710,8 +753,13 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint_p(const float* __restri
     pos = byte_adv(pos, bo);
     off = byte_adv(off, bo);
     out = byte_adv(out, bo);
+    clear = byte_adv(clear, bo);
   }
   const int n = g.n;
+  // the sort's spent cursors, the counts of the next sort (64 per tile)
+  for (long i = ((long)blockIdx.x * kPaintThreads + threadIdx.x) * 4; i < (long)g.ntiles * 64;
+       i += (long)gridDim.x * kPaintThreads * 4)
+    *reinterpret_cast<uint4*>(clear + i) = make_uint4(0u, 0u, 0u, 0u);
   // tiles: XCD x (= blockIdx.x % 8) takes the contiguous eighth of the
   // tiles [x cnt, (x + 1) cnt) and its nslot workgroups take every nslot-th
   // of them (gridDim.x is a multiple of 8, at most ntiles)
@@ -1080,10 +1128,6 @@ __global__ void k_frame_shift(float* __restrict__ mom, const uint32_t* __restric
   }
 }
 
-__global__ void k_step_inc(uint32_t* ctr) {
-  if (threadIdx.x == 0) atomicAdd(ctr, 1u);
-}
-
 // elementwise kick + drift with a given per-particle force (first half of a
 // standalone KDK step)
 __global__ void k_kick_drift(float* __restrict__ pos, float* __restrict__ mom, const float* __restrict__ f,
@@ -1234,14 +1278,17 @@ void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* wo
           : partition<512, false>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s);
 }
 
-long scan_scratch_words(long n) { return (n + kScanBlock - 1) / kScanBlock + 1; }
+long scan_scratch_words(long n) { return (n + kScanBlock - 1) / kScanBlock; }
 
 void launch_scan(uint32_t* count, long n, uint32_t* off, uint32_t* bsum, hipStream_t s, const BatchArg& bat,
-                 const uint32_t* part) {
-  const int nb = (int)((n + kScanBlock - 1) / kScanBlock);
-  hipLaunchKernelGGL(k_scan_local, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, count, n, off, bsum, bat, part);
-  hipLaunchKernelGGL(k_scan_top, dim3(1, 1, bat.n), dim3(kThreads), 0, s, bsum, nb, bat, part);
-  hipLaunchKernelGGL(k_scan_add, dim3(nb, 1, bat.n), dim3(kThreads), 0, s, off, count, n, bsum, nb, bat, part);
+                 const uint32_t* part, uint32_t* step_ctr) {
+  if (n <= kScanOne) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1, 1, bat.n), dim3(kScanOneThreads), 0, s, count, n, off, step_ctr, bat, part);
+    return;
+  }
+  const dim3 grid((unsigned)scan_scratch_words(n), 1, bat.n);
+  hipLaunchKernelGGL(k_scan_sums, grid, dim3(kScanThreads), 0, s, count, n, bsum, bat, part);
+  hipLaunchKernelGGL(k_scan_apply, grid, dim3(kScanThreads), 0, s, count, n, off, bsum, step_ctr, bat, part);
 }
 
 void launch_scatter(const ScatterArgs& a, hipStream_t s) {
@@ -1251,26 +1298,26 @@ void launch_scatter(const ScatterArgs& a, hipStream_t s) {
 }
 
 void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& g, float* out, float scale,
-                  float offset, bool std_layout, hipStream_t s, const BatchArg& bat) {
+                  float offset, uint32_t* clear, bool std_layout, hipStream_t s, const BatchArg& bat) {
   const PaintWeights pw;
   if (g.tx * g.ty * g.tz == kTileCells && g.ntiles >= 8) {
     // persistent: up to four workgroups per CU of 256 CUs, a multiple of 8
     const int nwg = g.ntiles < kPaintPersistentGroups ? g.ntiles : kPaintPersistentGroups;
     if (std_layout)
       hipLaunchKernelGGL(k_paint_p<true>, dim3(nwg, 1, bat.n), dim3(kPaintThreads), 0, s, pos_sorted, off, g, out,
-                         scale, offset, bat);
+                         scale, offset, bat, clear);
     else
       hipLaunchKernelGGL(k_paint_p<false>, dim3(nwg, 1, bat.n), dim3(kPaintThreads), 0, s, pos_sorted, off, g, out,
-                         scale, offset, bat);
+                         scale, offset, bat, clear);
     return;
   }
   const dim3 grid(g.ntiles, 1, bat.n);
   if (std_layout)
     hipLaunchKernelGGL((k_paint<true, false>), grid, dim3(kPaintThreads), 0, s, pos_sorted, off, g, out, scale,
-                       offset, pw, bat);
+                       offset, pw, bat, clear);
   else
     hipLaunchKernelGGL((k_paint<false, false>), grid, dim3(kPaintThreads), 0, s, pos_sorted, off, g, out,
-                       scale, offset, pw, bat);
+                       scale, offset, pw, bat, clear);
 }
 
 void launch_absmax(const float* v, long n, uint32_t* bits, hipStream_t s) {
@@ -1280,8 +1327,8 @@ void launch_absmax(const float* v, long n, uint32_t* bits, hipStream_t s) {
 }
 
 void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, const uint32_t* off, const TileGeom& g,
-                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, hipStream_t s,
-                           long out_stride) {
+                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, uint32_t* clear,
+                           hipStream_t s, long out_stride) {
   PaintWeights pw;
   pw.id = id_sorted;
   pw.wts = wts;
@@ -1290,7 +1337,7 @@ void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, c
   pw.k = k;
   pw.maxbits = maxbits;
   hipLaunchKernelGGL((k_paint<false, true>), dim3(g.ntiles, comp < 0 ? 3 : 1), dim3(kPaintThreads), 0, s, pos_sorted,
-                     off, g, out, 1.f, 0.f, pw, BatchArg());
+                     off, g, out, 1.f, 0.f, pw, BatchArg(), clear);
 }
 
 void launch_readout(const ReadoutArgs& a, hipStream_t s) {
@@ -1308,10 +1355,6 @@ void launch_readout(const ReadoutArgs& a, hipStream_t s) {
 void launch_frame_shift(float* mom, const uint32_t* id, const float* psi1, const float* psi2, long np, float u1,
                         float u2, hipStream_t s) {
   hipLaunchKernelGGL(k_frame_shift, dim3(grid_for(np)), dim3(kThreads), 0, s, mom, id, psi1, psi2, np, u1, u2);
-}
-
-void launch_step_inc(uint32_t* ctr, hipStream_t s) {
-  hipLaunchKernelGGL(k_step_inc, dim3(1), dim3(64), 0, s, ctr);
 }
 
 void launch_kick_drift(float* pos, float* mom, const float* f, long np, float kick, float drift, float nmesh,
