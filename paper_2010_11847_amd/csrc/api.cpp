@@ -891,11 +891,10 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
     op.out_q[i] = f[1 + i].q;
   }
   pmk::fft_x_fused(c.tl, f[0], op, c.stream);
-  pmk::fft_c2r_yz(c.tl, &f[1], op.n_out, c.stream);
+  pmk::fft_y(c.tl, &f[1], op.n_out, 1, c.stream);
   if (order >= 2) {
-    float* phi[6] = {f[4].r, f[5].r, f[6].r, f[7].r, f[8].r, f[9].r};
-    pmk::launch_lpt_delta2(phi, n3, f[0].r, c.stream);
-    pmk::fft_r2c_zy(c.tl, &f[0], 1, c.stream);
+    pmk::launch_lpt_delta2(c.tl, &f[4], f[0], c.stream);
+    pmk::fft_y(c.tl, &f[0], 1, -1, c.stream);
     pmk::SpecOp op2;
     op2.kind = pmk::OP_LPT2;
     op2.n_out = 3;
@@ -905,7 +904,7 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
       op2.out_q[i] = f[4 + i].q;
     }
     pmk::fft_x_fused(c.tl, f[0], op2, c.stream);
-    pmk::fft_c2r_yz(c.tl, &f[4], 3, c.stream);
+    pmk::fft_y(c.tl, &f[4], 3, 1, c.stream);
   }
   double g[6];
   c.cosmo.growth(a0, g);
@@ -916,20 +915,23 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
   a.ratio = c.ratio;
   a.shift = (float)c.cfg.lattice_shift;
   a.nmesh = (float)c.ng;
+  a.inv_nmesh = 1.f / a.nmesh;
   a.cx1 = (float)(b * d1);
   a.cx2 = (float)(b * d2);
   a.cp1 = (float)(b * a0 * a0 * e * f1 * d1);
   a.cp2 = (float)(b * a0 * a0 * e * f2 * d2);
   for (int d = 0; d < 3; ++d) {
     a.s1[d] = f[1 + d].r;
+    a.s1q[d] = f[1 + d].q;
     a.s2[d] = f[4 + d].r;
+    a.s2q[d] = f[4 + d].q;
   }
   a.has_s2 = order >= 2 ? 1 : 0;
   a.pos = d_pos;
   a.mom = d_mom;
   a.psi1 = c.psi1;   // the LPT frame, when set: B s1, B s2
   a.psi2 = c.psi2;
-  pmk::launch_lpt_particles(a, c.stream);
+  pmk::launch_lpt_particles(c.tl, a, c.stream);
   return c.check("pm_init_lpt");
 }
 

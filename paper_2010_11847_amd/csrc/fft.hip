@@ -23,10 +23,18 @@
 // transform of each output (the Green's-function/gradient kernel of the
 // force, the LPT kernels), so the spectrum is read once per basis power of
 // the gradient symbol and the product spectra are never written.
+#include "particles.h"
+#include "pm_device.h"
 #include "pm_internal.h"
 
 namespace pmk {
 namespace {
+struct LptDelta2Args {
+  const float* phi[6];     // xx yy zz xy xz yz, z spectra in the fields' regions
+  const float2* phi_q[6];
+  float* out;
+  float2* out_q;
+};
 
 constexpr int kThreads = 256;
 
@@ -455,6 +463,9 @@ constexpr int z_lines() {
 }
 template <int N>
 using ZGeom = ZGeomL<N, z_lines<N>()>;
+// One (x/8, y) row per workgroup.
+template <int N>
+using Z3Geom = ZGeomL<N, 8>;
 // The forward pass of 128-point lines stays at 64 KB (8.8 us against 7.0 at
 // 128^3): at every smaller size the compiler fuses other products of its
 // twiddles, and a run amplifies the changed last bits of its start.
@@ -610,6 +621,69 @@ __device__ __forceinline__ void zline_transform(float2* lds, const float2* __res
   __syncthreads();
 }
 
+// Packed value k of line m for the inverse transform, from the spectrum
+// staged in lds: X[0..H-1] there, X[H] in q (the block's first line's).
+template <class G>
+__device__ __forceinline__ float2 c2r_pack(const float2* lds, const float2* __restrict__ q,
+                                           const float2* __restrict__ twn, int m, int k) {
+  constexpr int N = G::NN, H = G::H;
+  const float2* line = lds + (m >> 3) * 4 * N + (m & 7);
+  float2 a, b;
+  if (k == 0) {
+    a = make_float2(line[0].x, 0.f);
+    b = make_float2(q[m].x, 0.f);
+  } else {
+    a = line[8 * k];
+    b = cconj(line[8 * (H - k)]);
+  }
+  const float2 e = cadd(a, b);
+  const float2 o = cmulc(csub(a, b), twn[k]);     // (a - b) exp(+2 pi i k / N)
+  return make_float2(e.x - o.y, e.y + o.x);       // e + i o
+}
+
+// Reals of the lines, Z[m][z/2] in lds, to their x-blocked region: float
+// e = rr*8N + z*8 + xi holds component z&1 of Z[rr*8 + xi][z/2].
+template <class G>
+__device__ __forceinline__ void c2r_store(const float2* lds, float2* __restrict__ reg) {
+  constexpr int N = G::NN, L = G::L, ZP = G::ZP;
+  const float* lf = reinterpret_cast<const float*>(lds);
+  float4* o4 = reinterpret_cast<float4*>(reg);
+  for (int i = threadIdx.x; i < L * N / 4; i += kThreads) {
+    const int e = 4 * i;
+    const int xi = e & 7, z = (e >> 3) & (N - 1), rr = e / (8 * N);
+    const int zo = 2 * (z >> 1) + (z & 1);
+    const float* zl = lf + 2 * ((rr * 8 + xi) * ZP) + zo;
+    o4[i] = make_float4(zl[0], zl[2 * ZP], zl[4 * ZP], zl[6 * ZP]);
+  }
+}
+
+// Spectrum of the lines from the packed transform Z[m][k] in lds:
+// X[k] = E + w^k O, X[H-k] = conj(E - w^k O); line m fastest.  reg and q are
+// the block's.
+template <class G>
+__device__ __forceinline__ void r2c_post(const float2* lds, float2* __restrict__ reg, float2* __restrict__ q,
+                                         const float2* __restrict__ twn) {
+  constexpr int N = G::NN, H = G::H, L = G::L, ZP = G::ZP;
+  constexpr int NK = H / 2 + 1;
+  for (int it = threadIdx.x; it < L * NK; it += kThreads) {
+    const int m = it % L, k = it / L;
+    const float2 zk = lds[m * ZP + k];
+    const float2 zm = cconj(lds[m * ZP + ((H - k) & (H - 1))]);
+    const float2 e = cscale(cadd(zk, zm), 0.5f);
+    const float2 dif = csub(zk, zm);
+    const float2 o = make_float2(0.5f * dif.y, -0.5f * dif.x);   // (zk - zm) / (2i)
+    const float2 t = cmul(o, twn[k]);
+    float2* out = reg + (m >> 3) * 4 * N + (m & 7);
+    if (k == 0) {
+      out[0] = make_float2(e.x + t.x, 0.f);
+      q[m] = make_float2(e.x - t.x, 0.f);
+    } else {
+      out[8 * k] = cadd(e, t);
+      if (k != H - k) out[8 * (H - k)] = cconj(csub(e, t));
+    }
+  }
+}
+
 // Real-to-complex along z, in place: the N reals of each line become
 // X[0..N/2-1] (region) and X[N/2] (Nyquist plane, q[l]).  STD reads the reals
 // of one field from a caller's plain [x][y][z] mesh instead: a copy into the
@@ -642,25 +716,7 @@ __global__ __launch_bounds__(kThreads) void k_r2c_z(float* __restrict__ r0, floa
     const int o = (m >> 3) * 8 * N + 16 * n + (m & 7);
     return make_float2(lf[o], lf[o + 8]);
   });
-  // post-processing: X[k] = E + w^k O, X[H-k] = conj(E - w^k O); line m fastest
-  constexpr int NK = H / 2 + 1;
-  for (int it = threadIdx.x; it < L * NK; it += kThreads) {
-    const int m = it % L, k = it / L;
-    const float2 zk = lds[m * ZP + k];
-    const float2 zm = cconj(lds[m * ZP + ((H - k) & (H - 1))]);
-    const float2 e = cscale(cadd(zk, zm), 0.5f);
-    const float2 dif = csub(zk, zm);
-    const float2 o = make_float2(0.5f * dif.y, -0.5f * dif.x);   // (zk - zm) / (2i)
-    const float2 t = cmul(o, twn[k]);
-    float2* out = reg + (m >> 3) * 4 * N + (m & 7);
-    if (k == 0) {
-      out[0] = make_float2(e.x + t.x, 0.f);
-      q[l0 + m] = make_float2(e.x - t.x, 0.f);
-    } else {
-      out[8 * k] = cadd(e, t);
-      if (k != H - k) out[8 * (H - k)] = cconj(csub(e, t));
-    }
-  }
+  r2c_post<G>(lds, reg, q + l0, twn);
 }
 
 // Complex-to-real along z (unnormalised), in place: X[0..N/2] -> N reals.
@@ -681,33 +737,167 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z(float* __restrict__ r0, floa
   float2* reg = reinterpret_cast<float2*>(r) + l0 * H;
   copy16<L * H / 2>(reinterpret_cast<float4*>(lds), reinterpret_cast<const float4*>(reg));
   __syncthreads();
-  zline_transform<G, +1>(lds, twh, [&](int m, int k) {
-    const float2* line = lds + (m >> 3) * 4 * N + (m & 7);
-    float2 a, b;
-    if (k == 0) {
-      a = make_float2(line[0].x, 0.f);
-      b = make_float2(q[l0 + m].x, 0.f);
-    } else {
-      a = line[8 * k];
-      b = cconj(line[8 * (H - k)]);
-    }
-    const float2 e = cadd(a, b);
-    const float2 o = cmulc(csub(a, b), twn[k]);     // (a - b) exp(+2 pi i k / N)
-    return make_float2(e.x - o.y, e.y + o.x);       // e + i o
-  });
-  if constexpr (STD) {
+  zline_transform<G, +1>(lds, twh, [&](int m, int k) { return c2r_pack<G>(lds, q + l0, twn, m, k); });
+  if constexpr (STD)
     std_store<G>(lds, std_out, l0);
-    return;
+  else
+    c2r_store<G>(lds, reg);
+}
+
+// Rows of two fields, loaded into registers and stored to LDS (a native
+// vector type: an array of float4 went through scratch memory).
+typedef float f4v __attribute__((ext_vector_type(4)));
+// N16 words, the first half of them from r0 and the rest from r1
+template <int N16, int K>
+__device__ __forceinline__ void stage_load2(f4v (&t)[K], const float* __restrict__ r0, const float* __restrict__ r1) {
+  constexpr int HALF = N16 / 2;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = threadIdx.x + k * kThreads;
+    if (N16 % kThreads == 0 || i < N16)
+      t[k] = i < HALF ? reinterpret_cast<const f4v*>(r0)[i] : reinterpret_cast<const f4v*>(r1)[i - HALF];
   }
-  // region float e = rr*8N + z*8 + xi holds component z&1 of Z[rr*8 + xi][z/2]
+}
+template <int N16, int K>
+__device__ __forceinline__ void stage_store(const f4v (&t)[K], float2* __restrict__ lds) {
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = threadIdx.x + k * kThreads;
+    if (N16 % kThreads == 0 || i < N16) reinterpret_cast<f4v*>(lds)[i] = t[k];
+  }
+}
+
+// Real lines of one (x/8, y) row of two fields, transformed together as
+// sixteen lines of one workgroup (lines 0..7 and 8..15 of lds on return): one
+// round of loads and barriers for both.  r0, q0 and r1, q1 are the row's.
+template <class G, int K>
+__device__ __forceinline__ void c2r_pair(float2* lds, const f4v (&t)[K], const float2* __restrict__ q0,
+                                         const float2* __restrict__ q1, const float2* __restrict__ twh,
+                                         const float2* __restrict__ twn) {
+  stage_store<G::L * G::NN / 4>(t, lds);
+  __syncthreads();
+  zline_transform<G, +1>(lds, twh, [&](int m, int k) { return c2r_pack<G>(lds, m < 8 ? q0 : q1 - 8, twn, m, k); });
+}
+
+// The LPT source from the six second derivatives of the potential, z spectra
+// in, z spectrum out (real-space lines for R2C = false):
+//   delta2 = phi_xx phi_yy + phi_xx phi_zz + phi_yy phi_zz - phi_xy^2 - phi_xz^2 - phi_yz^2
+// A workgroup turns one row of the six fields, two at a time, sums their
+// products in registers and transforms the sum, so the six real fields are
+// never written: bound by the read of six fields and the write of one.  (Six
+// c2r passes, a kernel for the sum and an r2c pass: 237 us at 256^3; this:
+// 170; the fields one after the other: 204.)  The sum's roundings are spelled
+// out: a run amplifies a last bit of its start.
+template <int N, bool R2C>
+__global__ __launch_bounds__(kThreads) void k_lpt_delta2_z(LptDelta2Args a, const float2* __restrict__ twh,
+                                                           const float2* __restrict__ twn) {
+  using G = ZGeomL<N, 16>;
+  using G8 = Z3Geom<N>;
+  constexpr int H = G::H, ZP = G::ZP;
+  constexpr int W = 8 * H, K = (W + kThreads - 1) / kThreads;   // complex words of a row, per thread
+  constexpr int KS = (W + kThreads - 1) / kThreads;             // 16-byte words of two rows, per thread
+  __shared__ float2 lds[G::size];
+  const long row = xcd_tile(blockIdx.x, gridDim.x);   // (x/8, y)
+  float2 u[K], v[K];
+  auto pair = [&](int f) {   // real values of fields f, f + 1
+    f4v t[KS];
+    stage_load2<W>(t, a.phi[f] + row * 8 * N, a.phi[f + 1] + row * 8 * N);
+    c2r_pair<G>(lds, t, a.phi_q[f] + row * 8, a.phi_q[f + 1] + row * 8, twh, twn);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      const int i = threadIdx.x + k * kThreads;
+      if (W % kThreads == 0 || i < W) {
+        u[k] = lds[(i / H) * ZP + i % H];
+        v[k] = lds[(i / H + 8) * ZP + i % H];
+      }
+    }
+    __syncthreads();
+  };
+  float2 sum[K];
+  {
+    float2 xx[K], yy[K];
+    pair(0);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      xx[k] = u[k];
+      yy[k] = v[k];
+    }
+    pair(2);   // zz, xy
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+#pragma clang fp contract(off)
+      sum[k].x = fmaf(yy[k].x, u[k].x, fmaf(xx[k].x, yy[k].x, xx[k].x * u[k].x));
+      sum[k].y = fmaf(yy[k].y, u[k].y, fmaf(xx[k].y, yy[k].y, xx[k].y * u[k].y));
+      sum[k].x = fmaf(-v[k].x, v[k].x, sum[k].x);
+      sum[k].y = fmaf(-v[k].y, v[k].y, sum[k].y);
+    }
+  }
+  pair(4);   // xz, yz
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = threadIdx.x + k * kThreads;
+    if (W % kThreads == 0 || i < W)
+      lds[(i / H) * ZP + i % H] = make_float2(fmaf(-v[k].x, v[k].x, fmaf(-u[k].x, u[k].x, sum[k].x)),
+                                              fmaf(-v[k].y, v[k].y, fmaf(-u[k].y, u[k].y, sum[k].y)));
+  }
+  __syncthreads();
+  float2* reg = reinterpret_cast<float2*>(a.out) + row * W;
+  if constexpr (R2C) {
+    zline_transform<G8, -1>(lds, twh, [&](int m, int n) { return lds[m * ZP + n]; });
+    r2c_post<G8>(lds, reg, a.out_q + row * 8, twn);
+  } else {
+    c2r_store<G8>(lds, reg);
+  }
+}
+
+// LPT particles from the z spectra of the displacements s1 (and s2):
+//   x = B q + shift + B (D1 s1 + D2 s2) (wrapped); p = B a0^2 E (f1 D1 s1 + f2 D2 s2)
+// A workgroup turns one (x/8, y) row of one component d of s1 and s2 and
+// writes that component of the row's particles (z fastest, the line's order);
+// the three workgroups of a row have consecutive tile indices, which the
+// XCD-aware mapping places on one XCD, so their 4-byte stores merge in that
+// XCD's L2.  Bound by the read of the fields and the write of the particles.
+// (c2r passes and a kernel that gathered from their x-blocked output, a
+// 32-byte run per 8 particles in x: 374 us at 256^3; this: 212; s1 and s2 one
+// after the other: 305.)  The roundings are spelled out, as above.
+template <int N, bool S2>
+__global__ __launch_bounds__(kThreads) void k_lpt_particles_z(LptParticleArgs a, const float2* __restrict__ twh,
+                                                              const float2* __restrict__ twn) {
+  using G = ZGeomL<N, S2 ? 16 : 8>;
+  constexpr int ZP = G::ZP, W = 8 * N;
+  constexpr int KS = (G::L * N / 4 + kThreads - 1) / kThreads;
+  __shared__ float2 lds[G::size];
+  const int tile = xcd_tile(blockIdx.x, gridDim.x), d = tile % 3;
+  const long row = tile / 3;   // (x/8, y)
+  const float* r1 = (d == 0 ? a.s1[0] : (d == 1 ? a.s1[1] : a.s1[2])) + row * W;
+  const float2* q1 = (d == 0 ? a.s1q[0] : (d == 1 ? a.s1q[1] : a.s1q[2])) + row * 8;
+  f4v st[KS];
+  if constexpr (S2) {
+    const float* r2 = (d == 0 ? a.s2[0] : (d == 1 ? a.s2[1] : a.s2[2])) + row * W;
+    const float2* q2 = (d == 0 ? a.s2q[0] : (d == 1 ? a.s2q[1] : a.s2q[2])) + row * 8;
+    stage_load2<W / 2>(st, r1, r2);
+    c2r_pair<G>(lds, st, q1, q2, twh, twn);
+  } else {
+    stage_load2<W / 4>(st, r1, r1 + W / 2);
+    c2r_pair<G>(lds, st, q1, q1, twh, twn);
+  }
   const float* lf = reinterpret_cast<const float*>(lds);
-  float4* o4 = reinterpret_cast<float4*>(reg);
-  for (int i = threadIdx.x; i < L * N / 4; i += kThreads) {
-    const int e = 4 * i;
-    const int xi = e & 7, z = (e >> 3) & (N - 1), rr = e / (8 * N);
-    const int zo = 2 * (z >> 1) + (z & 1);
-    const float* zl = lf + 2 * ((rr * 8 + xi) * ZP) + zo;
-    o4[i] = make_float4(zl[0], zl[2 * ZP], zl[4 * ZP], zl[6 * ZP]);
+  for (int i = threadIdx.x; i < W; i += kThreads) {
+#pragma clang fp contract(off)
+    const int m = i / N, z = i % N, x = (int)(row / N) * 8 + m, y = (int)(row % N);
+    const long pi = (((long)x * N + y) * N + z) * 3 + d;
+    const float u1 = lf[2 * m * ZP + z], u2 = S2 ? lf[2 * (m + 8) * ZP + z] : 0.f;
+    const float dx = fmaf(a.cx1, u1, a.cx2 * u2);
+    const float x0 = (float)(a.ratio * (d == 0 ? x : (d == 1 ? y : z))) + a.shift + dx;
+    float xw = x0;   // wrapped, as wrap_pos
+    if (x0 < 0.f || x0 >= a.nmesh) xw = fmaf(-a.nmesh, floorf(x0 * a.inv_nmesh), x0);
+    if (!(xw >= 0.f && xw < a.nmesh)) xw = 0.f;
+    a.pos[pi] = xw;
+    a.mom[pi] = fmaf(a.cp1, u1, a.cp2 * u2);
+    if (a.psi1) {
+      a.psi1[pi] = (float)a.ratio * u1;
+      a.psi2[pi] = (float)a.ratio * u2;
+    }
   }
 }
 
@@ -720,9 +910,6 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z(float* __restrict__ r0, floa
 // its component; the three workgroups of a row have consecutive tile indices,
 // which the XCD-aware mapping places on one XCD, so their stores into each
 // 192-byte run of the output merge in that XCD's L2.
-template <int N>
-using Z3Geom = ZGeomL<N, 8>;
-
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r0, long fstride,
                                                       const float2* __restrict__ q0, long qstride,
@@ -1676,6 +1863,25 @@ void zc2r(const FftTables& t, Field* f, int nf, hipStream_t s) {
                      t.tw_h, t.tw_n, nullptr);
 }
 
+// (128-point lines take the r2c pass of ZGeomF<128>)
+template <int N>
+void lpt_delta2(const FftTables& t, const LptDelta2Args& a, const Field& out, hipStream_t s) {
+  constexpr bool R2C = N != 128;
+  hipLaunchKernelGGL((k_lpt_delta2_z<N, R2C>), dim3(N * N / 8), dim3(kThreads), 0, s, a, t.tw_h, t.tw_n);
+  if (!R2C) {
+    Field f = out;
+    zr2c<N>(t, &f, 1, s);
+  }
+}
+
+template <int N>
+void lpt_particles(const FftTables& t, const LptParticleArgs& a, hipStream_t s) {
+  if (a.has_s2)
+    hipLaunchKernelGGL((k_lpt_particles_z<N, true>), dim3(3 * N * N / 8), dim3(kThreads), 0, s, a, t.tw_h, t.tw_n);
+  else
+    hipLaunchKernelGGL((k_lpt_particles_z<N, false>), dim3(3 * N * N / 8), dim3(kThreads), 0, s, a, t.tw_h, t.tw_n);
+}
+
 template <int N>
 void xfused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s) {
   constexpr int M = Cols<N>::M;
@@ -1896,6 +2102,25 @@ void fft_y_force(const FftTables& t, Field* f, hipStream_t s, const BatchArg& ba
 
 void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipStream_t s, const BatchArg& bat) {
 #define CALL(N) zc2r3<N>(t, f, out, s, bat)
+  PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
+}
+
+void launch_lpt_delta2(const FftTables& t, const Field* phi, const Field& out, hipStream_t s) {
+  LptDelta2Args a;
+  for (int i = 0; i < 6; ++i) {
+    a.phi[i] = phi[i].r;
+    a.phi_q[i] = phi[i].q;
+  }
+  a.out = out.r;
+  a.out_q = out.q;
+#define CALL(N) lpt_delta2<N>(t, a, out, s)
+  PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
+}
+
+void launch_lpt_particles(const FftTables& t, const LptParticleArgs& a, hipStream_t s) {
+#define CALL(N) lpt_particles<N>(t, a, s)
   PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
 }

@@ -33,11 +33,15 @@ struct LptParticleArgs {
   int np = 0;             // particles per side
   int ratio = 1;          // B = n_mesh / n_part
   float shift = 0.f;
-  float nmesh = 0.f;
+  float nmesh = 0.f, inv_nmesh = 0.f;   // mesh cells per side and its (rounded) inverse
   float cx1 = 0.f, cx2 = 0.f;   // B D1, B D2
   float cp1 = 0.f, cp2 = 0.f;   // B a0^2 E f1 D1, B a0^2 E f2 D2
-  const float* s1[3] = {};      // device pointers, passed by value
-  const float* s2[3] = {};      // device pointers; used when has_s2
+  // device pointers, passed by value: z spectra (after the inverse x and y
+  // passes); s2 is used when has_s2
+  const float* s1[3] = {};
+  const float* s2[3] = {};
+  const float2* s1q[3] = {};
+  const float2* s2q[3] = {};
   int has_s2 = 0;
   float* pos = nullptr;
   float* mom = nullptr;
@@ -120,8 +124,6 @@ struct ReadoutArgs {
 void launch_noise(uint64_t seed, int n_side, float* out, bool blocked, hipStream_t s);
 // plain [x][y][z] <-> x-blocked copy of a real n_side^3 mesh (out != in)
 void launch_relayout(const float* in, float* out, int n_side, bool to_blocked, hipStream_t s);
-void launch_lpt_delta2(float* const* phi6, long n, float* out, hipStream_t s);
-void launch_lpt_particles(const LptParticleArgs& a, hipStream_t s);
 void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, const BatchArg& bat = BatchArg());
 // tile keys of np particles, counted per key into count (all zero before)
 // lat_ln >= 0: the np = 2^(3 lat_ln) particles are in lattice order, and the

@@ -46,50 +46,6 @@ __global__ void k_noise(uint64_t seed, long n3, int ln, int blocked, float* __re
   }
 }
 
-// ---- LPT -----------------------------------------------------------------------
-// delta2 = phi_xx phi_yy + phi_xx phi_zz + phi_yy phi_zz - phi_xy^2 - phi_xz^2 - phi_yz^2
-__global__ void k_lpt_delta2(const float* __restrict__ xx, const float* __restrict__ yy,
-                             const float* __restrict__ zz, const float* __restrict__ xy,
-                             const float* __restrict__ xz, const float* __restrict__ yz, long n,
-                             float* __restrict__ out) {
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float a = xx[i], b = yy[i], c = zz[i], d = xy[i], e = xz[i], f = yz[i];
-    out[i] = a * b + a * c + b * c - d * d - e * e - f * f;
-  }
-}
-
-// x = B q + shift + B (D1 s1 + D2 s2) (wrapped); p = B a0^2 E (f1 D1 s1 + f2 D2 s2)
-// np is a power of two: the lattice site comes from shifts (a 64-bit
-// division per particle costs more than the particle's memory traffic), and
-// position and momentum are stored as one 12-byte access each.
-__global__ void k_lpt_particles(LptParticleArgs a) {
-  const int ln = __builtin_ctz(a.np);
-  const long n3 = 1L << (3 * ln);
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n3; i += stride) {
-    const int q[3] = {(int)(i >> (2 * ln)), (int)((i >> ln) & (a.np - 1)), (int)(i & (a.np - 1))};
-    const long e = blk_real(q[0], q[1], q[2], a.np);   // lattice fields are x-blocked
-    float x[3], p[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-      const float s1 = a.s1[d][e];
-      const float s2 = a.has_s2 ? a.s2[d][e] : 0.f;
-      const float dx = a.cx1 * s1 + a.cx2 * s2;
-      x[d] = wrap_pos((float)(a.ratio * q[d]) + a.shift + dx, a.nmesh);
-      p[d] = a.cp1 * s1 + a.cp2 * s2;
-      if (a.psi1) {
-        a.psi1[3 * i + d] = (float)a.ratio * s1;
-        a.psi2[3 * i + d] = (float)a.ratio * s2;
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) a.pos[3 * i + d] = x[d];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) a.mom[3 * i + d] = p[d];
-  }
-}
-
 // ---- counting sort -------------------------------------------------------------
 // mode that launch_partition left in its work words (null: no partition)
 __device__ __forceinline__ uint32_t part_mode(const uint32_t* __restrict__ work) { return work ? work[0] * work[1] : PART_NONE; }
@@ -1229,16 +1185,6 @@ void launch_relayout(const float* in, float* out, int n_side, bool to_blocked, h
   const long n3 = (long)n_side * n_side * n_side;
   hipLaunchKernelGGL(k_relayout, dim3(grid_for(n3)), dim3(kThreads), 0, s, in, out, __builtin_ctz(n_side),
                      to_blocked ? 1 : 0);
-}
-
-void launch_lpt_delta2(float* const* phi6, long n, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_lpt_delta2, dim3(grid_for(n)), dim3(kThreads), 0, s, phi6[0], phi6[1], phi6[2], phi6[3],
-                     phi6[4], phi6[5], n, out);
-}
-
-void launch_lpt_particles(const LptParticleArgs& a, hipStream_t s) {
-  const long n3 = (long)a.np * a.np * a.np;
-  hipLaunchKernelGGL(k_lpt_particles, dim3(grid_for(n3)), dim3(kThreads), 0, s, a);
 }
 
 void launch_fill_u32(uint32_t* p, long n, uint32_t v, hipStream_t s, const BatchArg& bat) {

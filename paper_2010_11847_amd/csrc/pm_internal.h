@@ -116,6 +116,13 @@ void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipS
                             const BatchArg& bat = BatchArg());
 // Inverse: y pass then z pass (complex + Nyquist plane -> real), unnormalised.
 void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s);
+
+// z stages of the LPT initial conditions, fused with what they feed: the six
+// z spectra of the potential's second derivatives (xx yy zz xy xz yz) to the
+// z spectrum of delta2, and the displacements' z spectra to particles
+struct LptParticleArgs;
+void launch_lpt_delta2(const FftTables& t, const Field* phi, const Field& out, hipStream_t s);
+void launch_lpt_particles(const FftTables& t, const LptParticleArgs& a, hipStream_t s);
 // z passes whose real side is a caller's plain [x][y][z] mesh (16-byte aligned).
 void fft_z_r2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s);
 void fft_z_c2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s);
