@@ -910,13 +910,23 @@ __global__ __launch_bounds__(kThreads) void k_lpt_particles_z(LptParticleArgs a,
 // its component; the three workgroups of a row have consecutive tile indices,
 // which the XCD-aware mapping places on one XCD, so their stores into each
 // 192-byte run of the output merge in that XCD's L2.
+//
+// Up to 512^3 one workgroup transforms the row of all three fields as 24 lines
+// (NF = 3) and writes whole 12-byte cells, a wave's 64 next to each other:
+// 16.5 -> 8.0 us for four 64^3 members, 17.1 -> 10.7 at 128^3, 102 -> 76 at
+// 256^3 (85 without the non-temporal loads), 749 -> 670 at 512^3.  The 24
+// lines of 1024 points fill 100 KB, one workgroup per CU: 5.7 -> 7.9 ms.
+template <int N>
+constexpr int z3_fields() { return N <= 512 ? 3 : 1; }
+
 template <int N>
 __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r0, long fstride,
                                                       const float2* __restrict__ q0, long qstride,
                                                       float* __restrict__ out, const float2* __restrict__ twh,
                                                       const float2* __restrict__ twn, BatchArg bat) {
-  using G = Z3Geom<N>;
-  constexpr int H = G::H, L = G::L, ZP = G::ZP;
+  constexpr int NF = z3_fields<N>();
+  using G = ZGeomL<N, 8 * NF>;
+  constexpr int H = G::H, ZP = G::ZP, W = 8 * H;   // W: complex words of a field's row
   __shared__ float2 lds[G::size];
   {
     const long bo = batch_bytes(bat);
@@ -926,22 +936,34 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r
     out = byte_adv(out, bo);
   }
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int row = tile / 3, f = tile - 3 * row;
-  const long l0 = (long)row * L;
+  const int row = NF == 1 ? tile / 3 : tile, f = NF == 1 ? tile - 3 * row : 0;
   // field f by stride arithmetic (a choice among pointer arguments can
   // compile to a lookup table in private memory)
-  const float2* reg = reinterpret_cast<const float2*>(r0 + f * fstride) + l0 * H;
-  const float2* q = q0 + f * qstride;
-  // non-temporal: each 96-byte output run is filled by three workgroups, and
-  // their partial writes merge in L2 only while the output lines stay there
-  copy16<L * H / 2, true>(reinterpret_cast<float4*>(lds), reinterpret_cast<const float4*>(reg));
+  const float2* reg = reinterpret_cast<const float2*>(r0 + f * fstride) + (long)row * W;
+  const float2* q = q0 + f * qstride + (long)row * 8;
+  if constexpr (NF == 1) {
+    // non-temporal: each 96-byte output run is filled by three workgroups, and
+    // their partial writes merge in L2 only while the output lines stay there
+    copy16<W / 2, true>(reinterpret_cast<float4*>(lds), reinterpret_cast<const float4*>(reg));
+  } else {
+    constexpr int KS = (3 * W / 2 + kThreads - 1) / kThreads;
+    f4v t[KS];
+#pragma unroll
+    for (int k = 0; k < KS; ++k) {
+      const int i = threadIdx.x + k * kThreads, fi = i / (W / 2);
+      if ((3 * W / 2) % kThreads == 0 || i < 3 * W / 2)
+        t[k] = __builtin_nontemporal_load(reinterpret_cast<const f4v*>(r0 + fi * fstride) + (long)row * (W / 2) +
+                                          i % (W / 2));
+    }
+    stage_store<3 * W / 2>(t, lds);
+  }
   __syncthreads();
   zline_transform<G, +1>(lds, twh, [&](int m, int k) {
-    const float2* line = lds + m;   // one row: line m is xi = m
+    const float2* line = lds + (NF == 1 ? m : (m >> 3) * 4 * N + (m & 7));
     float2 a, b;
     if (k == 0) {
       a = make_float2(line[0].x, 0.f);
-      b = make_float2(q[l0 + m].x, 0.f);
+      b = make_float2(q[(m >> 3) * qstride + (m & 7)].x, 0.f);
     } else {
       a = line[8 * k];
       b = cconj(line[8 * (H - k)]);
@@ -951,12 +973,24 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r
     return make_float2(e.x - o2.y, e.y + o2.x);     // e + i o
   });
   // Z[m][j] = (x[2j], x[2j+1]) of line m: cells z = 2j, 2j+1 of xi = m
-  float* o = out + (long)row * N * 24 + f;
-  for (int idx = threadIdx.x; idx < L * H; idx += kThreads) {
-    const int m = idx & 7, j = idx >> 3;
-    const float2 v = lds[m * ZP + j];
-    o[((2 * j) * 8 + m) * 3] = v.x;
-    o[((2 * j + 1) * 8 + m) * 3] = v.y;
+  if constexpr (NF == 1) {
+    float* o = out + (long)row * N * 24 + f;
+    for (int idx = threadIdx.x; idx < W; idx += kThreads) {
+      const int m = idx & 7, j = idx >> 3;
+      const float2 v = lds[m * ZP + j];
+      o[((2 * j) * 8 + m) * 3] = v.x;
+      o[((2 * j + 1) * 8 + m) * 3] = v.y;
+    }
+  } else {
+    struct F3 {
+      float x, y, z;
+    };
+    F3* o = reinterpret_cast<F3*>(out) + (long)row * N * 8;
+    const float* lf = reinterpret_cast<const float*>(lds);
+    for (int c = threadIdx.x; c < 8 * N; c += kThreads) {
+      const float* v = lf + 2 * ((c & 7) * ZP) + (c >> 3);
+      o[c] = F3{v[0], v[16 * ZP], v[32 * ZP]};
+    }
   }
 }
 
@@ -1849,7 +1883,7 @@ void zc2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s) {
 
 template <int N>
 void zc2r3(const FftTables& t, const Field* f, float* out, hipStream_t s, const BatchArg& bat = BatchArg()) {
-  dim3 grid(3 * (N * N) / Z3Geom<N>::L, 1, bat.n);
+  dim3 grid(3 * (N * N) / (8 * z3_fields<N>()), 1, bat.n);
   hipLaunchKernelGGL((k_c2r_z3<N>), grid, dim3(kThreads), 0, s, f[0].r, (long)(f[1].r - f[0].r), f[0].q,
                      (long)(f[1].q - f[0].q), out, t.tw_h, t.tw_n, bat);
 }
