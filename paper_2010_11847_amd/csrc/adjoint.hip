@@ -31,7 +31,8 @@ __global__ __launch_bounds__(kThreads) void k_readout_grad(const float* __restri
                                                            const float* __restrict__ mesh,
                                                            const float* __restrict__ pbar, float k,
                                                            float* __restrict__ xbar,
-                                                           const float* __restrict__ m1 = nullptr) {
+                                                           const float* __restrict__ m1, BatchArg bat) {
+  if (batch_bytes(bat) < 0) return;   // (a gate: nothing to add)
   const long j = (long)xcd_tile(blockIdx.x, gridDim.x) * kThreads + threadIdx.x;
   if (j >= np) return;
   int ix, iy, iz;
@@ -83,12 +84,6 @@ __global__ __launch_bounds__(kThreads) void k_readout_grad(const float* __restri
   xbar[3 * p + 0] = xb[0] + gx;
   xbar[3 * p + 1] = xb[1] + gy;
   xbar[3 * p + 2] = xb[2] + gz;
-}
-
-// y += a x  (n floats)
-__global__ void k_axpy(float* __restrict__ y, const float* __restrict__ x, float a, long n) {
-  const long stride = (long)gridDim.x * blockDim.x;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) y[i] += a * x[i];
 }
 
 // LPT: s1_bar_d = cx1 xbar_d + cp1 pbar_d, s2_bar_d = cx2 xbar_d + cp2 pbar_d
@@ -143,14 +138,14 @@ void launch_readout_grad3(const float* pos, const uint32_t* id, long np, int n, 
                           float k, float* xbar, hipStream_t s) {
   const int grid = (int)((np + kThreads - 1) / kThreads);
   hipLaunchKernelGGL((k_readout_grad<3, false>), dim3(grid), dim3(kThreads), 0, s, pos, id, np, n, fi, pbar, k,
-                     xbar);
+                     xbar, (const float*)nullptr, BatchArg());
 }
 
 void launch_readout_grad31(const float* pos, const uint32_t* id, long np, int n, const float* fi, const float* pbar,
-                           float k, const float* m1, float* xbar, hipStream_t s) {
+                           float k, const float* m1, float* xbar, hipStream_t s, const BatchArg& bat) {
   const int grid = (int)((np + kThreads - 1) / kThreads);
   hipLaunchKernelGGL((k_readout_grad<3, false, true>), dim3(grid), dim3(kThreads), 0, s, pos, id, np, n, fi, pbar, k,
-                     xbar, m1);
+                     xbar, m1, bat);
 }
 
 void launch_readout_grad1(const float* pos, const uint32_t* id, long np, int n, const float* m0, float k, float* xbar,
@@ -158,14 +153,10 @@ void launch_readout_grad1(const float* pos, const uint32_t* id, long np, int n, 
   const int grid = (int)((np + kThreads - 1) / kThreads);
   if (std_layout)
     hipLaunchKernelGGL((k_readout_grad<1, true>), dim3(grid), dim3(kThreads), 0, s, pos, id, np, n, m0,
-                       (const float*)nullptr, k, xbar);
+                       (const float*)nullptr, k, xbar, (const float*)nullptr, BatchArg());
   else
     hipLaunchKernelGGL((k_readout_grad<1, false>), dim3(grid), dim3(kThreads), 0, s, pos, id, np, n, m0,
-                       (const float*)nullptr, k, xbar);
-}
-
-void launch_axpy(float* y, const float* x, float a, long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_axpy, dim3(grid_for(n)), dim3(kThreads), 0, s, y, x, a, n);
+                       (const float*)nullptr, k, xbar, (const float*)nullptr, BatchArg());
 }
 
 void launch_lpt_sbar(const float* xbar, const float* pbar, long n3, float cx1, float cp1, float cx2, float cp2,

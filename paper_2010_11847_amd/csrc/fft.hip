@@ -727,7 +727,9 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z(float* __restrict__ r0, floa
                                                      float* __restrict__ r2, const float2* __restrict__ q0,
                                                      const float2* __restrict__ q1, const float2* __restrict__ q2,
                                                      const float2* __restrict__ twh,
-                                                     const float2* __restrict__ twn, float* __restrict__ std_out) {
+                                                     const float2* __restrict__ twn, float* __restrict__ std_out,
+                                                     BatchArg gate) {
+  if (batch_bytes(gate) < 0) return;   // (its input was not written)
   using G = ZGeom<N>;
   constexpr int H = G::H, L = G::L, ZP = G::ZP;
   __shared__ float2 lds[G::size];
@@ -1653,6 +1655,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force_t(FusedArgs a) {
   constexpr int IT = (R1 * R2 + kThreads - 1) / kThreads;
   __shared__ float2 lds[ColLds<N, M>::size];
   __shared__ float2 tws[R1 * R2];   // exp(-2 pi i l j / N), l < R1, j < R2
+  if (batch_bytes(a.bat) < 0) return;   // (a gate: its input was not written)
   int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int mode = tile >= a.nb_main ? 1 : 0;
   if (mode) tile -= a.nb_main;
@@ -1878,7 +1881,7 @@ void zr2c_std(const FftTables& t, const float* in, const Field& f, hipStream_t s
 template <int N>
 void zc2r_std(const FftTables& t, const Field& f, float* out, hipStream_t s) {
   hipLaunchKernelGGL((k_c2r_z<N, true>), dim3((N * N) / ZGeom<N>::L), dim3(kThreads), 0, s, f.r, f.r, f.r, f.q, f.q,
-                     f.q, t.tw_h, t.tw_n, out);
+                     f.q, t.tw_h, t.tw_n, out, BatchArg());
 }
 
 template <int N>
@@ -1889,12 +1892,12 @@ void zc2r3(const FftTables& t, const Field* f, float* out, hipStream_t s, const 
 }
 
 template <int N>
-void zc2r(const FftTables& t, Field* f, int nf, hipStream_t s) {
+void zc2r(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate = BatchArg()) {
   using G = ZGeom<N>;
   dim3 grid((N * N) / G::L, nf);
   hipLaunchKernelGGL((k_c2r_z<N, false>), grid, dim3(kThreads), 0, s, f[0].r, nf > 1 ? f[1].r : f[0].r,
                      nf > 2 ? f[2].r : f[0].r, f[0].q, nf > 1 ? f[1].q : f[0].q, nf > 2 ? f[2].q : f[0].q,
-                     t.tw_h, t.tw_n, nullptr);
+                     t.tw_h, t.tw_n, nullptr, gate);
 }
 
 // (128-point lines take the r2c pass of ZGeomF<128>)
@@ -1980,9 +1983,10 @@ void xforce(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s
 // f[0..2] = the forward-(z, y) spectra of the x, y, z inputs; the result
 // replaces f[0], f[1] and f[2] are left as they were.
 template <int N>
-void xforce_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s) {
+void xforce_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s, const BatchArg& gate) {
   constexpr int M = Cols<N>::M;
   FusedArgs a;
+  a.bat = gate;
   a.op = op;
   a.t = t;
   a.gm = ColGeom{4L * N, 4L * N * N, N / 2, cdiv(N / 2, M)};
@@ -2046,9 +2050,9 @@ void by3(Field* f, int nf, Fn fn) {
     default: break;                                       \
   }
 
-void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s) {
+void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate) {
   by3(f, nf, [&](Field* g, int k) {
-#define CALL(N) zr2c<N>(t, g, k, s); ypass<N, -1>(t, g, k, s)
+#define CALL(N) zr2c<N>(t, g, k, s, gate); ypass<N, -1>(t, g, k, s, gate)
     PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
   });
@@ -2122,8 +2126,8 @@ void fft_x_force(const FftTables& t, const Field& in, const SpecOp& op, hipStrea
 #undef CALL
 }
 
-void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s) {
-#define CALL(N) xforce_t<N>(t, f, op, s)
+void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s, const BatchArg& gate) {
+#define CALL(N) xforce_t<N>(t, f, op, s, gate)
   PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
 }
@@ -2159,9 +2163,9 @@ void launch_lpt_particles(const FftTables& t, const LptParticleArgs& a, hipStrea
 #undef CALL
 }
 
-void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s) {
+void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate) {
   by3(f, nf, [&](Field* g, int k) {
-#define CALL(N) ypass<N, 1>(t, g, k, s); zc2r<N>(t, g, k, s)
+#define CALL(N) ypass<N, 1>(t, g, k, s, gate); zc2r<N>(t, g, k, s, gate)
     PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
   });

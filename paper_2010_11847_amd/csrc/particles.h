@@ -162,14 +162,21 @@ void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& 
                   float offset, uint32_t* clear, bool std_layout, hipStream_t s, const BatchArg& bat = BatchArg());
 void launch_readout(const ReadoutArgs& a, hipStream_t s);
 // *bits = bit pattern of max_i |v_i| over n floats
-void launch_absmax(const float* v, long n, uint32_t* bits, hipStream_t s);
+// With x: v += c x first.  a->gate is a descriptor of member 0 when some value
+// is not zero, else a skipped one: a BatchArg of it makes launches that only
+// carry v's (linear) image return at once when v is all zero.
+struct AbsMax {
+  pm_req_desc gate;
+  uint32_t max_bits;
+};
+void launch_absmax(float* v, const float* x, float c, long n, AbsMax* a, hipStream_t s);
 // x-blocked paint of signed masses wts[3 id + comp] * k (the adjoint's
 // cotangent channels); *maxbits must hold max |wts| (launch_absmax).
 // comp < 0: the three components in one launch, component d into
 // out + d * out_stride.
 void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, const uint32_t* off, const TileGeom& g,
                            const float* wts, int comp, float k, const uint32_t* maxbits, float* out, uint32_t* clear,
-                           hipStream_t s, long out_stride = 0);
+                           hipStream_t s, long out_stride = 0, const BatchArg& bat = BatchArg());
 void launch_kick_drift(float* pos, float* mom, const float* f, long np, float kick, float drift, float nmesh,
                        hipStream_t s);
 // mom[j] += u1 psi1[id[j]] + u2 psi2[id[j]] over np sorted particles (the
@@ -182,11 +189,10 @@ void launch_readout_grad3(const float* pos, const uint32_t* id, long np, int n, 
 // Both readout terms of one force evaluation in one pass: the readout_grad3
 // term plus that of the real x-blocked mesh m1 with weight 1.
 void launch_readout_grad31(const float* pos, const uint32_t* id, long np, int n, const float* fi, const float* pbar,
-                           float k, const float* m1, float* xbar, hipStream_t s);
+                           float k, const float* m1, float* xbar, hipStream_t s, const BatchArg& bat = BatchArg());
 // m0: real mesh, x-blocked (std_layout: plain [x][y][z])
 void launch_readout_grad1(const float* pos, const uint32_t* id, long np, int n, const float* m0, float k, float* xbar,
                           bool std_layout, hipStream_t s);
-void launch_axpy(float* y, const float* x, float a, long n, hipStream_t s);
 void launch_lpt_sbar(const float* xbar, const float* pbar, long n3, float cx1, float cp1, float cx2, float cp2,
                      float* const* s1, float* const* s2, hipStream_t s);
 void launch_lpt_phibar(float* const* phi6, const float* d2b, long n3, hipStream_t s);

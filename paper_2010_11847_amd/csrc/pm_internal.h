@@ -84,7 +84,9 @@ struct SpecOp {
 
 // ---- FFT launchers (fft.hip) ---------------------------------------------
 // Forward r2c: z pass (real -> complex + Nyquist plane), then y pass.
-void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s);
+// (gate: a BatchArg whose one descriptor, of member 0 or skipped, lets the
+// launches run or return at once)
+void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate = BatchArg());
 // Fused x pass: forward x transform of `in`, spectral op, inverse x
 // transforms written to op.out_*.  `in` may alias out[0].
 void fft_x_fused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s);
@@ -103,7 +105,7 @@ void fft_y_force(const FftTables& t, Field* f, hipStream_t s, const BatchArg& ba
 // x pass of the transposed force (OP_FORCE_T: op.scale, deconv, split) over
 // the forward-(z, y) spectra f[0..2] of its x, y, z inputs; the result (the
 // fan-in, inverse-x transformed) replaces f[0].
-void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s);
+void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s, const BatchArg& gate = BatchArg());
 // Single passes (the composites above call these).
 void fft_z_r2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg());
 void fft_y(const FftTables& t, Field* f, int nf, int dir, hipStream_t s, const BatchArg& bat = BatchArg());
@@ -115,7 +117,7 @@ void fft_z_c2r(const FftTables& t, Field* f, int nf, hipStream_t s);
 void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipStream_t s,
                             const BatchArg& bat = BatchArg());
 // Inverse: y pass then z pass (complex + Nyquist plane -> real), unnormalised.
-void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s);
+void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate = BatchArg());
 
 // z stages of the LPT initial conditions, fused with what they feed: the six
 // z spectra of the potential's second derivatives (xx yy zz xy xz yz) to the
