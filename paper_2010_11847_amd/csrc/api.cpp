@@ -516,8 +516,13 @@ struct pm_ctx {
   void force_on(const FftTables& t, Field* f, float* out, long n, double scale, int deconv, int split, int cls,
                 const pmk::BatchArg& bat = pmk::BatchArg()) {
     auto tm_ = [&](int c, auto&& fn) { timed(cls < 0 ? c : cls, fn); };
-    tm_(PC_FFT_R2C_Z, [&] { pmk::fft_z_r2c(t, &f[0], 1, stream, bat); });
-    tm_(PC_FFT_Y_FWD, [&] { pmk::fft_y(t, &f[0], 1, -1, stream, bat); });
+    const bool planes = n <= pmk::kPlaneMax;   // z and y of a plane in one launch, through f[1]
+    if (planes) {
+      tm_(PC_FFT_R2C_Z, [&] { pmk::fft_plane_forward(t, f[0], f[1], stream, bat); });
+    } else {
+      tm_(PC_FFT_R2C_Z, [&] { pmk::fft_z_r2c(t, &f[0], 1, stream, bat); });
+      tm_(PC_FFT_Y_FWD, [&] { pmk::fft_y(t, &f[0], 1, -1, stream, bat); });
+    }
     pmk::SpecOp op;
     op.scale = (float)scale;
     op.deconv = deconv;
@@ -531,7 +536,11 @@ struct pm_ctx {
       op.out_c[i] = f[dst[i]].c();
       op.out_q[i] = f[dst[i]].q;
     }
-    tm_(PC_FFT_X_FORCE, [&] { pmk::fft_x_force(t, f[0], op, stream, bat); });
+    tm_(PC_FFT_X_FORCE, [&] { pmk::fft_x_force(t, planes ? f[1] : f[0], op, stream, bat); });
+    if (planes) {
+      tm_(PC_FFT_C2R_Z, [&] { pmk::fft_plane_force(t, f, out, stream, bat); });
+      return;
+    }
     tm_(PC_FFT_Y_INV, [&] { pmk::fft_y_force(t, f, stream, bat); });
     tm_(PC_FFT_C2R_Z, [&] { pmk::fft_z_c2r_interleaved3(t, f, out, stream, bat); });
   }

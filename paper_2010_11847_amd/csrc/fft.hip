@@ -997,6 +997,115 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r
 }
 
 // ===========================================================================
+// Plane passes of the force on meshes up to 32^3: the z and y transforms of
+// one x plane in one workgroup, whose (N x N) plane fits LDS many times over.
+// A pass of such a mesh takes 3.5-5 us, all of it launch and round trips, so
+// what counts is the number of passes: z and y forward 7.3 -> 5.2 us, y and z
+// inverse of the three components 8.5 -> 6.1 us at 32^3.  The planes of a block
+// interleave by 8-byte words, so both passes write another buffer than they
+// read.  (From 64^3 on, the separate passes keep their products' roundings,
+// which a run would amplify.)
+// ===========================================================================
+template <int LEN, int LINES>
+struct PlaneLines {
+  static constexpr int R1 = LEN == 32 ? 8 : 4, R2 = LEN / R1;
+  static constexpr int L = LINES, LP = L + 1, ZP = LEN + 1;
+  static constexpr int size = LEN * LP > L * ZP ? LEN * LP : L * ZP;
+};
+template <int N, int NF>
+struct PlaneGeom {   // NF fields' planes
+  using Z = PlaneLines<N / 2, NF * N>;         // N lines along z (packed reals)
+  using Y = PlaneLines<N, NF * (N / 2 + 1)>;   // N/2 + 1 columns along y
+  static constexpr int size = Z::size > Y::size ? Z::size : Y::size;
+};
+
+// reals of src to the (z, y) spectrum in dst
+template <int N>
+__global__ __launch_bounds__(kThreads) void k_plane_forward(const float* __restrict__ r, float2* __restrict__ c,
+                                                            float2* __restrict__ q, const float2* __restrict__ twh,
+                                                            const float2* __restrict__ twn, BatchArg bat) {
+  using GZ = typename PlaneGeom<N, 1>::Z;
+  using GY = typename PlaneGeom<N, 1>::Y;
+  constexpr int H = N / 2;
+  __shared__ float2 lds[PlaneGeom<N, 1>::size];
+  const long bo = batch_bytes(bat);
+  if (bo < 0) return;
+  r = byte_adv(r, bo);
+  c = byte_adv(c, bo);
+  q = byte_adv(q, bo);
+  const int x = xcd_tile(blockIdx.x, gridDim.x), xi = x & 7;
+  const long row = (long)(x >> 3) * N;   // (x/8, y = 0)
+  zline_transform<GZ, -1>(lds, twh, [&](int y, int j) {
+    const float* v = r + ((row + y) * N + 2 * j) * 8 + xi;
+    return make_float2(v[0], v[8]);
+  });
+  zline_transform<GY, -1>(lds, twn, [&](int kz, int y) {
+    const float2 zk = lds[y * GZ::ZP + (kz & (H - 1))];
+    const float2 zm = cconj(lds[y * GZ::ZP + ((H - kz) & (H - 1))]);
+    const float2 e = cscale(cadd(zk, zm), 0.5f);
+    const float2 dif = csub(zk, zm);
+    const float2 t = cmul(make_float2(0.5f * dif.y, -0.5f * dif.x), twn[kz & (H - 1)]);
+    if (kz == 0) return make_float2(e.x + t.x, 0.f);
+    if (kz == H) return make_float2(e.x - t.x, 0.f);
+    return cadd(e, t);
+  });
+  for (int i = threadIdx.x; i < (H + 1) * N; i += kThreads) {
+    const int kz = i % (H + 1), ky = i / (H + 1);
+    const float2 v = lds[kz * GY::ZP + ky];
+    if (kz < H)
+      c[((row + ky) * H + kz) * 8 + xi] = v;
+    else
+      q[(row + ky) * 8 + xi] = v;
+  }
+}
+
+// y and z inverse of the force components after an OP_FORCE_XS x pass (F_x,
+// and the shared factor G of F_y = D(w_y) G and F_z = D(w_z) G) into the
+// interleaved mesh of k_c2r_z3
+template <int N>
+__global__ __launch_bounds__(kThreads) void k_plane_force(const float2* __restrict__ cx, const float2* __restrict__ qx,
+                                                          const float2* __restrict__ cg, const float2* __restrict__ qg,
+                                                          float* __restrict__ out, FftTables t, BatchArg bat) {
+  using GZ = typename PlaneGeom<N, 3>::Z;
+  using GY = typename PlaneGeom<N, 3>::Y;
+  constexpr int H = N / 2, HC = H + 1;
+  __shared__ float2 lds[PlaneGeom<N, 3>::size];
+  const long bo = batch_bytes(bat);
+  if (bo < 0) return;
+  cx = byte_adv(cx, bo);
+  qx = byte_adv(qx, bo);
+  cg = byte_adv(cg, bo);
+  qg = byte_adv(qg, bo);
+  out = byte_adv(out, bo);
+  const int x = xcd_tile(blockIdx.x, gridDim.x), xi = x & 7;
+  const long row = (long)(x >> 3) * N;
+  // the three components side by side: one round of loads and barriers each
+  zline_transform<GY, 1>(lds, t.tw_n, [&](int m, int ky) {
+    const int d = m / HC, kz = m - d * HC;
+    const float2* c = d == 0 ? cx : cg;
+    const float2* q = d == 0 ? qx : qg;
+    const float2 v = kz < H ? c[((row + ky) * H + kz) * 8 + xi] : q[(row + ky) * 8 + xi];
+    return cscale(v, d == 0 ? 1.f : (d == 1 ? t.dxy[ky] : t.dz[kz]));
+  });
+  zline_transform<GZ, 1>(lds, t.tw_h, [&](int m, int k) {
+    const float2* l = lds + m / N * HC * GY::ZP + m % N;
+    float2 a = l[k * GY::ZP], b = cconj(l[(H - k) * GY::ZP]);
+    if (k == 0) a.y = b.y = 0.f;
+    const float2 e = cadd(a, b);
+    const float2 o = cmulc(csub(a, b), t.tw_n[k]);   // (a - b) exp(+2 pi i k / N)
+    return make_float2(e.x - o.y, e.y + o.x);        // e + i o
+  });
+  struct F3 {
+    float x, y, z;
+  };
+  const float* lf = reinterpret_cast<const float*>(lds);
+  for (int i = threadIdx.x; i < N * N; i += kThreads) {
+    const float* v = lf + 2 * (i / N) * GZ::ZP + i % N;
+    reinterpret_cast<F3*>(out)[(row * N + i) * 8 + xi] = F3{v[0], v[2 * N * GZ::ZP], v[4 * N * GZ::ZP]};
+  }
+}
+
+// ===========================================================================
 // Fused x pass: forward x transform, spectral op, inverse x transform(s).
 // Geometry as in k_fft_cols with rows n = kx.  mode 0: the main array
 // (b = ky, c = kz < N/2); mode 1: the Nyquist plane (b = 0, c = ky, kz = N/2).
@@ -2050,6 +2159,40 @@ void by3(Field* f, int nf, Fn fn) {
     default: break;                                       \
   }
 
+#define PM_FFT_SWITCH_SMALL(n, CALL) \
+  switch (n) {                       \
+    case 8: CALL(8); break;          \
+    case 16: CALL(16); break;        \
+    case 32: CALL(32); break;        \
+    default: break;                  \
+  }
+
+#define PM_FFT_SWITCH_LARGE(n, CALL) \
+  switch (n) {                       \
+    case 64: CALL(64); break;        \
+    case 128: CALL(128); break;      \
+    case 256: CALL(256); break;      \
+    case 512: CALL(512); break;      \
+    case 1024: CALL(1024); break;    \
+    default: break;                  \
+  }
+
+void fft_plane_forward(const FftTables& t, const Field& in, const Field& out, hipStream_t s, const BatchArg& bat) {
+#define CALL(N)                                                                                                    \
+  hipLaunchKernelGGL((k_plane_forward<N>), dim3(N, 1, bat.n), dim3(kThreads), 0, s, in.r, out.c(), out.q, t.tw_h, \
+                     t.tw_n, bat)
+  PM_FFT_SWITCH_SMALL(t.n, CALL)
+#undef CALL
+}
+
+void fft_plane_force(const FftTables& t, const Field* f, float* out, hipStream_t s, const BatchArg& bat) {
+#define CALL(N)                                                                                                  \
+  hipLaunchKernelGGL((k_plane_force<N>), dim3(N, 1, bat.n), dim3(kThreads), 0, s, f[0].c(), f[0].q, f[2].c(), \
+                     f[2].q, out, t, bat)
+  PM_FFT_SWITCH_SMALL(t.n, CALL)
+#undef CALL
+}
+
 void fft_r2c_zy(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate) {
   by3(f, nf, [&](Field* g, int k) {
 #define CALL(N) zr2c<N>(t, g, k, s, gate); ypass<N, -1>(t, g, k, s, gate)
@@ -2134,13 +2277,13 @@ void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s
 
 void fft_y_force(const FftTables& t, Field* f, hipStream_t s, const BatchArg& bat) {
 #define CALL(N) yforce<N>(t, f, s, bat)
-  PM_FFT_SWITCH(t.n, CALL)
+  PM_FFT_SWITCH_LARGE(t.n, CALL)
 #undef CALL
 }
 
 void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipStream_t s, const BatchArg& bat) {
 #define CALL(N) zc2r3<N>(t, f, out, s, bat)
-  PM_FFT_SWITCH(t.n, CALL)
+  PM_FFT_SWITCH_LARGE(t.n, CALL)
 #undef CALL
 }
 

@@ -101,6 +101,8 @@ void fft_x_force(const FftTables& t, const Field& in, const SpecOp& op, hipStrea
 // f[0] holds F_x, f[2] the shared factor i g X.  f[2] becomes F_z times
 // D(w_z) in place and f[1] receives F_y = transform of D(w_y) i g X; one
 // read of the shared factor feeds both.
+// (64^3 and larger meshes; up to kPlaneMax the plane passes below take its
+// place and that of the z passes)
 void fft_y_force(const FftTables& t, Field* f, hipStream_t s, const BatchArg& bat = BatchArg());
 // x pass of the transposed force (OP_FORCE_T: op.scale, deconv, split) over
 // the forward-(z, y) spectra f[0..2] of its x, y, z inputs; the result (the
@@ -116,6 +118,14 @@ void fft_z_c2r(const FftTables& t, Field* f, int nf, hipStream_t s);
 // for both the arrays and the Nyquist planes), as the workspace meshes are.
 void fft_z_c2r_interleaved3(const FftTables& t, const Field* f, float* out, hipStream_t s,
                             const BatchArg& bat = BatchArg());
+
+// Force passes of meshes up to kPlaneMax cells per side: in.r to the spectrum
+// after z and y in `out` (another field), and F_x in f[0], the shared factor
+// in f[2] (after fft_x_force) to the interleaved mesh.
+constexpr int kPlaneMax = 32;
+void fft_plane_forward(const FftTables& t, const Field& in, const Field& out, hipStream_t s,
+                       const BatchArg& bat = BatchArg());
+void fft_plane_force(const FftTables& t, const Field* f, float* out, hipStream_t s, const BatchArg& bat = BatchArg());
 // Inverse: y pass then z pass (complex + Nyquist plane -> real), unnormalised.
 void fft_c2r_yz(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& gate = BatchArg());
 
