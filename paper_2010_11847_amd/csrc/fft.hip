@@ -1114,7 +1114,8 @@ struct FusedArgs {
   SpecOp op;
   ColGeom gm, gp;          // main array (mode 0) and Nyquist plane (mode 1)
   int nb_main;
-  int pbasis;              // the power of D(w_x) this launch handles
+  int pbasis;              // the (first) power of D(w_x) this launch handles
+  int plast, pmask;        // fan-out: the last one, and the powers of the op
   int first, last;         // fan-in: first / last basis launch of the op
   float2* park_main;       // fan-in: x-spectrum partial sum between launches
   float2* park_nyq;
@@ -1217,6 +1218,9 @@ __device__ __forceinline__ float common_factor(const SpecOp& op, const FftTables
 }
 
 __device__ __forceinline__ float powp(float d, int p) { return p == 0 ? 1.f : (p == 1 ? d : d * d); }
+
+template <int N>
+constexpr bool fan_out_once() { return N <= 256; }   // one launch for all powers of a fan-out op
 
 template <int N, int M, bool FANIN>
 __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
@@ -1388,28 +1392,40 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
     }
     if (a.last) inverse_store(0);
   } else {
-    // fan-out: this launch handles the outputs of one basis power p: the
-    // input tile is transformed, scaled by c(k) D(w_x)^p and inverse
-    // transformed.  The host launches the bases in increasing p (one
-    // launch each, so that the register arrays of one basis are all that
-    // is live); an output that aliases the input has the highest p of its
-    // op, so the input is intact for every earlier basis.
-    const int p = a.pbasis;
+    // fan-out: the input tile is transformed once; for every basis power p
+    // of the launch, in increasing order, its spectrum is scaled by
+    // c(k) D(w_x)^p, inverse transformed and stored to the outputs of that
+    // power.  An output that aliases the input has the highest p of its op,
+    // so nothing is overwritten early.  Up to 256 points one launch takes all
+    // powers of the op (408 -> 360 us for the two ops of the initial
+    // conditions at 256^3, 80 -> 58 at 128^3); from 512 on the kept spectrum
+    // leaves one wave per SIMD (3.9 -> 5.6 ms), and each power is a launch.
+    // (Transforming the tile again for each power fused other products.)
     forward(0);
+    float2 X0[IB][R2];
 #pragma unroll
-    for (int i = 0; i < IB; ++i) {
-      const int it = tid + i * kThreads;
-      const int m = it % M, l1 = it / M;
-      int ky, kz;
-      freq(m, ky, kz);
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
-      for (int l2 = 0; l2 < R2; ++l2) {
-        const int kx = l1 + R1 * l2;
-        Y[i][l2] = it < M * R1 ? cscale(X[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
-                               : make_float2(0.f, 0.f);
+      for (int l2 = 0; l2 < R2; ++l2) X0[i][l2] = X[i][l2];
+    const int plast = fan_out_once<N>() ? a.plast : a.pbasis;
+#pragma unroll 1
+    for (int p = a.pbasis; p <= plast; ++p) {
+      if (fan_out_once<N>() && !(a.pmask >> p & 1)) continue;
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        const int it = tid + i * kThreads;
+        const int m = it % M, l1 = it / M;
+        int ky, kz;
+        freq(m, ky, kz);
+#pragma unroll
+        for (int l2 = 0; l2 < R2; ++l2) {
+          const int kx = l1 + R1 * l2;
+          Y[i][l2] = it < M * R1 ? cscale(X0[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
+                                 : make_float2(0.f, 0.f);
+        }
       }
+      inverse_store(p);
     }
-    inverse_store(p);
   }
 }
 
@@ -2055,15 +2071,19 @@ void xfused(const FftTables& t, const Field& in, const SpecOp& op, hipStream_t s
     a.park_main = op.in_c[first_in];
     a.park_nyq = op.in_q[first_in];
   }
+  a.plast = plast;
+  a.pmask = pmask;
   for (int p = pfirst; p <= plast; ++p) {
     if (!(pmask >> p & 1)) continue;
     a.pbasis = p;
     a.first = p == pfirst;
     a.last = p == plast;
-    if (fan_in)
+    if (fan_in) {
       hipLaunchKernelGGL((k_fft_x_fused<N, M, true>), grid, dim3(kThreads), 0, s, a);
-    else
+    } else {
       hipLaunchKernelGGL((k_fft_x_fused<N, M, false>), grid, dim3(kThreads), 0, s, a);
+      if (fan_out_once<N>()) return;
+    }
   }
 }
 
