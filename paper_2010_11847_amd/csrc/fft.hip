@@ -21,8 +21,9 @@
 //
 // The x pass can be fused with a spectral multiplication and the inverse x
 // transform of each output (the Green's-function/gradient kernel of the
-// force, the LPT kernels), so the spectrum is read once per basis power of
-// the gradient symbol and the product spectra are never written.
+// force, the LPT kernels), so the product spectra are never written.  The z
+// passes are fused with what reads or writes the real fields: a caller's
+// plain meshes, the interleaved force mesh, the LPT source and particles.
 #include "particles.h"
 #include "pm_device.h"
 #include "pm_internal.h"
@@ -1122,7 +1123,8 @@ struct FusedArgs {
   const float2* in_main;   // input spectrum (forward-y transformed)
   const float2* in_nyq;
   FftTables t;
-  BatchArg bat;            // batched launches (k_fft_x_force): blockIdx.z selects the member
+  BatchArg bat;            // batched launches (k_fft_x_force): blockIdx.z selects the member;
+                           // k_fft_x_force_t: a gate
 };
 
 template <int N>
