@@ -20,6 +20,7 @@ namespace {
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kLnAInit = -11.512925464970229;   // ln(1e-5)
 constexpr double kStep = 1.0 / 512.0;              // RK4 step in ln a
+constexpr int kPointEvery = 16;                    // steps between the kept points
 }  // namespace
 
 double Cosmo::E(double a) const { return std::sqrt(om / (a * a * a) + (1.0 - om)); }
@@ -69,14 +70,41 @@ void Cosmo::integrate(double a, double* y) const {
   }
 }
 
-// Fixed steps of kStep in ln a along one trajectory; each target is reached
-// from the last grid point below it by one shorter step taken on a copy.
-void Cosmo::growth_sorted(const double* a, int n, double* out6) const {
+// The trajectory up to a = 1 at every kPointEvery-th step (15 KB).  From its
+// start a factor at a = 0.1 takes 4700 steps, 140 us of host time: of the
+// 340 us that a run with its initial conditions spent on the host, 300.
+const Cosmo::Trajectory& Cosmo::trajectory() const {
+  std::call_once(traj->once, [this] {
+    Point p;
+    growing_mode_start(p.y);
+    p.l = kLnAInit;
+    for (int s = 0;; ++s) {
+      if (s % kPointEvery == 0) traj->points.push_back(p);
+      if (p.l + kStep > 0.0) break;
+      rk4_step(p.l, kStep, p.y, p.y);
+      p.l += kStep;
+    }
+    rk4_step(p.l, -p.l, p.y, p.y);
+    traj->d1_one = p.y[0];
+  });
+  return *traj;
+}
+
+// Fixed steps of kStep in ln a along one trajectory, from the last kept point
+// below the first target; each target is reached from the last step below it
+// by one shorter step taken on a copy.
+void Cosmo::growth_sorted(const double* a, int n, double d1_norm, double* out6) const {
   double y[4], t[4];
   growing_mode_start(y);
   double l = kLnAInit;
+  const std::vector<Point>& pts = trajectory().points;
   for (int j = 0; j < n; ++j) {
     const double lt = std::log(a[j]);
+    auto p = std::upper_bound(pts.begin(), pts.end(), lt, [](double v, const Point& q) { return v < q.l; });
+    if (p != pts.begin() && (--p)->l > l) {
+      l = p->l;
+      std::copy(p->y, p->y + 4, y);
+    }
     while (l + kStep <= lt) {
       rk4_step(l, kStep, y, y);
       l += kStep;
@@ -87,9 +115,9 @@ void Cosmo::growth_sorted(const double* a, int n, double* out6) const {
       for (int i = 0; i < 4; ++i) t[i] = y[i];
     double* o = out6 + 6 * j;
     const double e = E(a[j]);
-    o[0] = t[0] / d1_today;
+    o[0] = t[0] / d1_norm;
     o[1] = t[1] / t[0];
-    o[2] = t[2] / (d1_today * d1_today);
+    o[2] = t[2] / (d1_norm * d1_norm);
     o[3] = t[3] / t[2];
     o[4] = e;
     o[5] = a[j] * a[j] * e * o[1] * o[0];
@@ -103,7 +131,7 @@ void Cosmo::kdk_factors(const double* a, int n_a, double* k1, double* dr, double
   std::vector<double> pts(2 * ns + 1), g(6 * (2 * ns + 1));
   for (int i = 0; i <= ns; ++i) pts[2 * i] = a[i];
   for (int i = 0; i < ns; ++i) pts[2 * i + 1] = std::sqrt(a[i] * a[i + 1]);
-  growth_sorted(pts.data(), 2 * ns + 1, g.data());
+  growth_sorted(pts.data(), 2 * ns + 1, d1_today, g.data());
   auto d1 = [&](int p) { return g[6 * p]; };
   auto gf = [&](int p) { return g[6 * p + 5]; };
   for (int i = 0; i < ns; ++i) {
@@ -155,6 +183,7 @@ void Cosmo::step_factors(int integrator, const double* a, int n_a, double* k1, d
 void Cosmo::init(const pm_cosmo& c) {
   om = c.omega_m;
   par = c;
+  traj = std::make_shared<Trajectory>();
   if (c.pk_kind == PM_PK_TABLE && c.pk_n >= 2 && c.pk_k && c.pk_p) {
     tab_lnk.resize(c.pk_n);
     tab_lnp.resize(c.pk_n);
@@ -181,7 +210,11 @@ void Cosmo::init(const pm_cosmo& c) {
 }
 
 void Cosmo::growth(double a, double* out6) const {
-  double y[4];
+  if (std::log(a) >= kLnAInit) {
+    growth_sorted(&a, 1, trajectory().d1_one, out6);
+    return;
+  }
+  double y[4];   // before the trajectory's start
   integrate(a, y);
   const double d1 = y[0] / d1_today;
   const double f1 = y[1] / y[0];

@@ -1,6 +1,8 @@
 // Host-side cosmology (float64); see cosmo.cpp.
 #pragma once
 
+#include <memory>
+#include <mutex>
 #include <vector>
 
 #include "pm.h"
@@ -40,8 +42,21 @@ struct Cosmo {
   void rhs(double lna, const double* y, double* dy) const;
   void integrate(double a, double* y) const;
   void rk4_step(double l, double h, const double* y, double* out) const;
-  // growth() at n ascending scale factors from a single integration
-  void growth_sorted(const double* a, int n, double* out6) const;
+  // growth() at n ascending scale factors along one trajectory, D1 as a
+  // fraction of d1_norm
+  void growth_sorted(const double* a, int n, double d1_norm, double* out6) const;
+  // Points of that trajectory, kept with the cosmology they belong to: built
+  // by the first call that needs them, read by every later one.
+  struct Point {
+    double l, y[4];   // ln a, (D1, dD1/dlna, D2, dD2/dlna)
+  };
+  struct Trajectory {
+    std::once_flag once;
+    std::vector<Point> points;
+    double d1_one = 1.0;   // D1 along it at a = 1
+  };
+  std::shared_ptr<Trajectory> traj;
+  const Trajectory& trajectory() const;
 };
 
 }  // namespace pmk
