@@ -586,6 +586,13 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
   // particles per thread whose loads are in flight together (the weighted
   // form has a third dependent load, the weight by id)
   constexpr int kBatch = WT ? 4 : 2;
+  // A wave takes four consecutive particles from each of sixteen places of the
+  // round: neighbours in the sort share cells, and their LDS adds queue up
+  // (four 64^3 members 17.1 -> 14.6 us).  The weighted form, whose by-id loads
+  // want consecutive particles, and the 16^3 tiles of k_paint_p, whose blocks
+  // hold eight times the cells, are slower with it (19.3 -> 21.7 us at 128^3,
+  // 313 -> 351 at 512^3).
+  const uint32_t slot = WT ? threadIdx.x : (threadIdx.x & 15) * (kPaintThreads / 16) + (threadIdx.x >> 4);
   for (uint32_t base = 0; base < total; base += kPaintThreads * kBatch) {
     // all range searches (LDS) first, then all loads, so that the kBatch
     // loads of a thread are in flight together; positions past the end are
@@ -593,7 +600,7 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
     uint32_t jj[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-      const uint32_t idx = base + threadIdx.x + u * kPaintThreads;
+      const uint32_t idx = base + slot + u * kPaintThreads;
       jj[u] = range_particle(rt, idx < total ? idx : total - 1);
     }
     float px[kBatch][3];
@@ -619,7 +626,7 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
     }
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
-    if (base + threadIdx.x + u * kPaintThreads >= total) continue;
+    if (base + slot + u * kPaintThreads >= total) continue;
     int ix, iy, iz;
     float fx, fy, fz;
     cic_base(px[u][0], n, ix, fx);
