@@ -24,6 +24,8 @@
 // force, the LPT kernels), so the product spectra are never written.  The z
 // passes are fused with what reads or writes the real fields: a caller's
 // plain meshes, the interleaved force mesh, the LPT source and particles.
+#include <type_traits>
+
 #include "particles.h"
 #include "pm_device.h"
 #include "pm_internal.h"
@@ -136,6 +138,16 @@ template <> struct Split<256> { static constexpr int R1 = 16, R2 = 16; };
 template <> struct Split<512> { static constexpr int R1 = 32, R2 = 16; };
 template <> struct Split<1024> { static constexpr int R1 = 32, R2 = 32; };
 
+// Stages of the passes that make the initial conditions: below 64 points the
+// whole column stays in one thread, for its roundings.  A run on 64^3 from 16^3
+// or 32^3 particles, deconvolved, amplifies the two stages' other last bits to
+// 2.5e-5 (norm) and 1e-3 (largest) of its momenta; they cost it once a run
+// (x 11.8 -> 17.0, y 3.7 -> 5.9 us at 32^3).
+template <int N> struct ExactSplit : Split<N> {};
+template <> struct ExactSplit<8> { static constexpr int R1 = 8, R2 = 1; };
+template <> struct ExactSplit<16> { static constexpr int R1 = 16, R2 = 1; };
+template <> struct ExactSplit<32> { static constexpr int R1 = 32, R2 = 1; };
+
 // Stages of a z line of H complex values: lines are many, so up to 32 points
 // stay in one thread's registers.
 template <int H> struct ZSplit {
@@ -210,9 +222,9 @@ __device__ __forceinline__ long row_off(int n, long sn) {
   return BLK ? (long)(n >> 3) * sn + (n & 7) : (long)n * sn;
 }
 
-template <int N, int M>
+template <int N, int M, class S = Split<N>>
 struct ColLds {
-  static constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
+  static constexpr int R1 = S::R1, R2 = S::R2;
   // forward exchange [l1][j2][m] with a padded l1 stride; the inverse
   // exchange of the fused pass uses [l1'][l1][m] (R2 x R1)
   static constexpr int SA = R2 * M + M;
@@ -240,13 +252,13 @@ struct ColPass {
 // 130 us at 256^3).  Its tiles walk columns fastest: a numpy row's 128-byte
 // pieces are unaligned ((N/2 + 1)-element rows), and the tiles that share
 // their lines then follow each other on one XCD.
-template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false>
+template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false, class S = Split<N>>
 __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __restrict__ tw) {
-  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
+  constexpr int R1 = S::R1, R2 = S::R2;
   constexpr int CS = BLK ? 8 : 1;
   constexpr int IA = (M * R2 + TH - 1) / TH;
   constexpr int IB = (M * R1 + TH - 1) / TH;
-  __shared__ float2 lds[ColLds<N, M>::size];
+  __shared__ float2 lds[ColLds<N, M, S>::size];
   int tile = xcd_tile(blockIdx.x, gridDim.x);
   const bool is_plane = tile >= p.nb_main;
   if (is_plane) tile -= p.nb_main;
@@ -274,7 +286,7 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       base[row_off<BLK>(n, g.sn) + m * CS] = v;
   };
 
-  constexpr int SA = ColLds<N, M>::SA;
+  constexpr int SA = ColLds<N, M, S>::SA;
 #pragma unroll
   for (int i = 0; i < IA; ++i) {
     const int it = tid + i * TH;
@@ -1226,11 +1238,12 @@ constexpr bool fan_out_once() { return N <= 256; }   // one launch for all power
 
 template <int N, int M, bool FANIN>
 __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
-  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
+  using S = std::conditional_t<FANIN, Split<N>, ExactSplit<N>>;
+  constexpr int R1 = S::R1, R2 = S::R2;
   constexpr int IA = (M * R2 + kThreads - 1) / kThreads;   // stage A and inverse stage B'
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;   // stage B and inverse stage A'
-  constexpr int SA = ColLds<N, M>::SA, SB = ColLds<N, M>::SB;
-  __shared__ float2 lds[ColLds<N, M>::size];
+  constexpr int SA = ColLds<N, M, S>::SA, SB = ColLds<N, M, S>::SB;
+  __shared__ float2 lds[ColLds<N, M, S>::size];
   int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int mode = tile >= a.nb_main ? 1 : 0;
   if (mode) tile -= a.nb_main;
@@ -1337,6 +1350,10 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
         float2 v[R1];
 #pragma unroll
         for (int l1 = 0; l1 < R1; ++l1) v[l1] = lds[lp * SB + l1 * M + m];
+        if constexpr (R2 == 1 && !FANIN) {
+#pragma unroll
+          for (int kx = 0; kx < R1; ++kx) v[kx] = cscale(v[kx], powp(t.dxy[kx], p));
+        }
         dft<R1, 1>(v);
         if (c0 + m < g.ncols) {
           if (FANIN) {
@@ -1422,8 +1439,11 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_fused(FusedArgs a) {
 #pragma unroll
         for (int l2 = 0; l2 < R2; ++l2) {
           const int kx = l1 + R1 * l2;
-          Y[i][l2] = it < M * R1 ? cscale(X0[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
-                                 : make_float2(0.f, 0.f);
+          if constexpr (R2 == 1)   // (ExactSplit: D^p is multiplied on where the column is whole)
+            Y[i][l2] = it < M * R1 ? cscale(X0[i][l2], common_factor<N>(op, t, kx, ky, kz)) : make_float2(0.f, 0.f);
+          else
+            Y[i][l2] = it < M * R1 ? cscale(X0[i][l2], common_factor<N>(op, t, kx, ky, kz) * powp(t.dxy[kx], p))
+                                   : make_float2(0.f, 0.f);
         }
       }
       inverse_store(p);
@@ -1932,7 +1952,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force_t(FusedArgs a) {
 // ---------------------------------------------------------------------------
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-template <int N, int DIR, bool BLK, bool NP = false>
+template <int N, int DIR, bool BLK, bool NP = false, bool EXACT = false>
 void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int nbm, ColGeom gp, int nbp,
                  const float2* tw, hipStream_t s, const BatchArg& bat = BatchArg(), float2* np = nullptr,
                  float scale = 1.f) {
@@ -1953,18 +1973,19 @@ void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int n
   p.np = np;
   p.scale = scale;
   dim3 grid(p.ntiles, nf, bat.n);
-  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH, NP>), grid, dim3(TH), 0, s, p, tw);
+  using S = std::conditional_t<(EXACT && N < 64), ExactSplit<N>, Split<N>>;
+  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH, NP, S>), grid, dim3(TH), 0, s, p, tw);
 }
 
 // y pass over the main arrays and the Nyquist planes of nf fields
-template <int N, int DIR>
+template <int N, int DIR, bool EXACT = false>
 void ypass(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg()) {
   float2* dm[3];
   float2* dq[3];
   for (int i = 0; i < nf; ++i) { dm[i] = f[i].c(); dq[i] = f[i].q; }
   // main c[xb][y][kz][xi]: (b = xb, n = y, c = kz*8 + xi): sb = 4N^2, sn = 4N, ncols = 4N
   // Nyquist plane q[xb][y][xi]: (b = xb, n = y, c = xi): sb = 8N, sn = 8, ncols = 8
-  launch_cols<N, DIR, false>(dm, dq, nf, ColGeom{4L * N * N, 4L * N, 4 * N, 0}, N / 8,
+  launch_cols<N, DIR, false, false, EXACT>(dm, dq, nf, ColGeom{4L * N * N, 4L * N, 4 * N, 0}, N / 8,
                              ColGeom{8L * N, 8, 8, 0}, N / 8, t.tw_n, s, bat);
 }
 
@@ -2234,6 +2255,14 @@ void fft_z_r2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchA
 void fft_y(const FftTables& t, Field* f, int nf, int dir, hipStream_t s, const BatchArg& bat) {
   by3(f, nf, [&](Field* g, int k) {
 #define CALL(N) (dir < 0 ? ypass<N, -1>(t, g, k, s, bat) : ypass<N, 1>(t, g, k, s, bat))
+    PM_FFT_SWITCH(t.n, CALL)
+#undef CALL
+  });
+}
+
+void fft_y_exact(const FftTables& t, Field* f, int nf, int dir, hipStream_t s) {
+  by3(f, nf, [&](Field* g, int k) {
+#define CALL(N) (dir < 0 ? ypass<N, -1, true>(t, g, k, s) : ypass<N, 1, true>(t, g, k, s))
     PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
   });
