@@ -1551,7 +1551,7 @@ int pm_power(pm_ctx* ctx, const float* d_delta, int n_bins, int n_max, int decon
   pm_ctx& c = *ctx;
   if (n_bins < 1 || n_bins > c.L.n_bins_max) return c.fail(PM_EINVAL, "n_bins must be in [1, n_mesh/2]");
   c.z_r2c_from(c.tm, d_delta, c.mesh[0]);
-  pmk::fft_y(c.tm, &c.mesh[0], 1, -1, c.stream);
+  pmk::fft_y_exact(c.tm, &c.mesh[0], 1, -1, c.stream);
   pmk::PowerArgs a;
   a.n_bins = n_bins;
   a.n_max = n_max;

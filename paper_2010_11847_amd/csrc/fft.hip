@@ -124,6 +124,65 @@ __device__ __forceinline__ void dft(float2 (&v)[R]) {
   }
 }
 
+// The forward column transform of measured spectra, with the rounding of
+// every product spelled out.  A complex product rounds one real product of
+// each component by itself and fuses the other into the sum; left to the
+// compiler, the choice follows the code around it, and P(k), float64 sums
+// over a float32 spectrum, moved in its ninth digit (1.2e-9 at 256^3, 1.2e-7
+// below) when the transform was moved into another kernel.  With the forms
+// written down the passes below give the same bits wherever they stand.
+
+// a w for a stage's table twiddle w
+__device__ __forceinline__ float2 cmul_fixed(float2 a, float2 w) {
+#pragma clang fp contract(off)
+  return make_float2(fmaf(a.x, w.x, -(a.y * w.y)), fmaf(a.x, w.y, a.y * w.x));
+}
+
+// a exp(-2 pi i idx / 32), idx < 16: the product with the cosine is fused in
+// the imaginary part, and in the real part up to an eighth turn and a half;
+// an eighth turn itself (idx 4) has two forms.
+__device__ __forceinline__ float2 twiddle32_fixed(float2 a, int idx, bool eighth_as_others) {
+#pragma clang fp contract(off)
+  constexpr float c16[16] = {1.000000000e+00f,  9.807852804e-01f,  9.238795325e-01f,  8.314696123e-01f,
+                             7.071067812e-01f,  5.555702330e-01f,  3.826834324e-01f,  1.950903220e-01f,
+                             0.0f,              -1.950903220e-01f, -3.826834324e-01f, -5.555702330e-01f,
+                             -7.071067812e-01f, -8.314696123e-01f, -9.238795325e-01f, -9.807852804e-01f};
+  if (idx == 0) return a;
+  if (idx == 8) return make_float2(a.y, -a.x);
+  const float c = c16[idx], s = -c16[idx < 8 ? 8 - idx : idx - 8];   // cos, -sin
+  const bool eighth = idx == 4 && !eighth_as_others;
+  const float re = idx > 8 || (idx == 4 && eighth_as_others) ? fmaf(-a.y, s, a.x * c) : fmaf(a.x, c, -(a.y * s));
+  const float im = eighth ? fmaf(a.x, s, a.y * c) : fmaf(a.y, c, a.x * s);
+  return make_float2(re, im);
+}
+
+// dft<R, -1> as the first or the second stage of a column.  In the second
+// stage the eighth turn takes the form of the other angles, except in the
+// last group of each level of 16 and 32 points.
+template <int R, bool SECOND>
+__device__ __forceinline__ void dft_fixed(float2 (&v)[R]) {
+  if constexpr (R > 1) {
+#pragma unroll
+    for (int len = R; len >= 2; len >>= 1) {
+      const int half = len >> 1;
+#pragma unroll
+      for (int s = 0; s < R; s += len) {
+#pragma unroll
+        for (int k = 0; k < half; ++k) {
+          const float2 a = v[s + k], b = v[s + k + half];
+          v[s + k] = cadd(a, b);
+          v[s + k + half] = twiddle32_fixed(csub(a, b), k * (32 / len), SECOND && (R == 8 || s + len < R));
+        }
+      }
+    }
+    float2 t[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) t[i] = v[bitrev<R>(i)];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = t[i];
+  }
+}
+
 // Stages of the column passes.  Every size takes two: with a whole column of
 // N <= 32 in one thread, 16 lanes of a workgroup's 256 worked on a chain of
 // 32-point transforms (two 12.5 us x passes at 32^3, whose data is 0.1 us of
@@ -138,8 +197,8 @@ template <> struct Split<256> { static constexpr int R1 = 16, R2 = 16; };
 template <> struct Split<512> { static constexpr int R1 = 32, R2 = 16; };
 template <> struct Split<1024> { static constexpr int R1 = 32, R2 = 32; };
 
-// Stages of the passes that make the initial conditions: below 64 points the
-// whole column stays in one thread, for its roundings.  A run on 64^3 from 16^3
+// Stages of the passes that make the initial conditions and of P(k): below 64
+// points the whole column stays in one thread, for its roundings.  A run on 64^3 from 16^3
 // or 32^3 particles, deconvolved, amplifies the two stages' other last bits to
 // 2.5e-5 (norm) and 1e-3 (largest) of its momenta; they cost it once a run
 // (x 11.8 -> 17.0, y 3.7 -> 5.9 us at 32^3).
@@ -255,6 +314,7 @@ struct ColPass {
 template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false, class S = Split<N>>
 __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __restrict__ tw) {
   constexpr int R1 = S::R1, R2 = S::R2;
+  constexpr bool FIXED = NP && DIR < 0;   // the bits of the spectrum that k_power_x bins
   constexpr int CS = BLK ? 8 : 1;
   constexpr int IA = (M * R2 + TH - 1) / TH;
   constexpr int IB = (M * R1 + TH - 1) / TH;
@@ -297,9 +357,15 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1)
         v[j1] = ok ? load(R2 * j1 + j2, m) : make_float2(0.f, 0.f);
-      dft<R1, DIR>(v);
+      if constexpr (FIXED) {
+        dft_fixed<R1, false>(v);
 #pragma unroll
-      for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<DIR>(tw, j2 * l1));
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul_fixed(v[l1], tw[j2 * l1]);
+      } else {
+        dft<R1, DIR>(v);
+#pragma unroll
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<DIR>(tw, j2 * l1));
+      }
     }
   }
   __syncthreads();
@@ -311,7 +377,10 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       float2 v[R2];
 #pragma unroll
       for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
-      dft<R2, DIR>(v);
+      if constexpr (FIXED)
+        dft_fixed<R2, true>(v);
+      else
+        dft<R2, DIR>(v);
       if (c0 + m < g.ncols) {
 #pragma unroll
         for (int l2 = 0; l2 < R2; ++l2) store(l1 + R1 * l2, m, v[l2]);
@@ -1469,7 +1538,8 @@ constexpr int kPowerBlocks = 512;
 template <int N, int M>
 __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, int nb_main, int ntiles,
                                                       const float2* __restrict__ tw, PowerArgs a) {
-  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2, H = N / 2;
+  using S = ExactSplit<N>;   // two stages from 64 points up
+  constexpr int R1 = S::R1, R2 = S::R2, H = N / 2;
   constexpr int IA = (M * R2 + kThreads - 1) / kThreads;
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;
   constexpr int SA = R2 * M + M;
@@ -1502,9 +1572,10 @@ __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, in
 #pragma unroll
         for (int j1 = 0; j1 < R1; ++j1)
           v[j1] = ok ? base[row_off<true>(R2 * j1 + j2, g.sn) + m * 8] : make_float2(0.f, 0.f);
-        dft<R1, -1>(v);
+        dft_fixed<R1, false>(v);
 #pragma unroll
-        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul(v[l1], tw_get<-1>(tw, j2 * l1));
+        for (int l1 = 0; l1 < R1; ++l1)
+          lds[l1 * SA + j2 * M + m] = l1 == 0 || R2 == 1 ? v[l1] : cmul_fixed(v[l1], tw[j2 * l1]);
       }
     }
     __syncthreads();
@@ -1516,7 +1587,7 @@ __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, in
         float2 v[R2];
 #pragma unroll
         for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
-        dft<R2, -1>(v);
+        dft_fixed<R2, true>(v);
         // back into the slots this item read (no other thread's), so that the
         // binning below is a loop: unrolled over registers it needed more
         // than 256 of them and left one wave per SIMD
