@@ -146,6 +146,21 @@ enum PartMode : uint32_t { PART_NONE = 0, PART_SORTED = 1, PART_MOVED = 2 };
 constexpr long kPartitionMin = 1L << 17;
 constexpr int kPartitionBuckets = 1024;   // at most
 constexpr int kPartitionWords = 64 + 2 * kPartitionBuckets;
+// Its buckets, runs of 2^kbits keys (64 a tile).  1024 of them keep the windows
+// of the sorting pass smaller (30 million particles on 512^3: 536 -> 424 us of
+// it), 512 and half the chunk fill the chip with fewer particles (the three
+// passes at 0.2 million: 24.3 us against 32.3).  A 1024^3 mesh takes 1024 at any
+// count: with 512 a bucket's keys fill 128 KB of LDS, and its workgroup has a
+// CU to itself (paint of 0.5 to 8 million 2043 to 2359 us, 2006 to 2256 so).
+struct PartitionGeom {
+  int threads;   // of a workgroup of the first passes, the most buckets there may be
+  int buckets, kbits;
+};
+static inline PartitionGeom partition_geom(long np, int ntiles) {
+  PartitionGeom p{np >= (1L << 23) || ntiles > (1 << 17) ? kPartitionBuckets : kPartitionBuckets / 2, ntiles, 6};
+  for (; p.buckets > p.threads; p.buckets >>= 1) ++p.kbits;
+  return p;
+}
 void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos,
                       uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s);
 long scan_scratch_words(long n);

@@ -235,11 +235,6 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(uint32_t* __restric
 // exceed its L2).  Whether the order is scattered is decided on the device
 // from a sample, since an ordered catalogue is sorted faster by the passes
 // below.
-//
-// B buckets, and as many threads per workgroup in the first passes: 1024 keep
-// the windows of the last pass smaller (30 million particles: 536 -> 424 us
-// of it), 512 and half the chunk fill the chip with fewer particles (the
-// three passes at 0.2 million: 24.3 us against 32.3).
 constexpr int kPartItems = 8;                               // particles per thread of a chunk
 constexpr int kPartHist = 64, kPartFill = kPartHist + kPartitionBuckets;   // word offsets in `work`
 constexpr int kPartSortThreads = 1024;
@@ -343,8 +338,8 @@ __global__ __launch_bounds__(B) void k_part_move(const float* __restrict__ pos, 
   }
   const uint32_t total = work[kPartHist + tid];
   if (blockIdx.x == 0) {
-    const bool large = __syncthreads_or(total > (uint32_t)(np / (B / 4) + 32768));
-    if (tid == 0) work[1] = large ? PART_MOVED : PART_SORTED;
+    const bool moved = __syncthreads_or(total > (uint32_t)(np / (B / 4) + 32768));
+    if (tid == 0) work[1] = moved ? PART_MOVED : PART_SORTED;
   }
   const uint32_t gstart = part_scan(total, wsum);   // first slot of bucket tid (its barriers also order h)
   uint32_t rank[kPartItems], b[kPartItems];
@@ -1244,29 +1239,29 @@ void launch_keys(const float* pos, long np, const TileGeom& g, uint32_t* key, ui
 
 namespace {
 template <int B, bool ID>
-void partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos, uint32_t* part_id,
-               uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s) {
-  int kbits = 6, nb = g.ntiles;   // at most B buckets of 2^kbits keys (64 per tile)
-  for (; nb > B; nb >>= 1) ++kbits;
-  hipLaunchKernelGGL(k_part_sample, dim3(1), dim3(1024), 0, s, pos, np, g, kbits, work);
-  hipLaunchKernelGGL(k_part_hist<B>, dim3(grid_for(np, B * 16, 512 * 1024 / B)), dim3(B), 0, s, pos, np, g, kbits, work);
+void partition(const float* pos, long np, const TileGeom& g, const PartitionGeom& p, uint32_t* work, float* part_pos,
+               uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s) {
+  hipLaunchKernelGGL(k_part_sample, dim3(1), dim3(1024), 0, s, pos, np, g, p.kbits, work);
+  hipLaunchKernelGGL(k_part_hist<B>, dim3(grid_for(np, B * 16, 512 * 1024 / B)), dim3(B), 0, s, pos, np, g, p.kbits,
+                     work);
   hipLaunchKernelGGL((k_part_move<B, ID>), dim3(grid_for(np, B * kPartItems, 1 << 30)), dim3(B), 0, s, pos, np, g,
-                     kbits, work, part_pos, part_id);
-  // LDS: the bucket's keys, at most 64 KB (kbits = 14 at 1024^3 and B = 512)
-  hipLaunchKernelGGL(k_part_sort<ID>, dim3(nb), dim3(kPartSortThreads), (size_t)4 << kbits, s, part_pos, part_id, np,
-                     g, kbits, work, off, pos_out, id_out);
+                     p.kbits, work, part_pos, part_id);
+  // LDS: the bucket's keys, at most 64 KB
+  hipLaunchKernelGGL(k_part_sort<ID>, dim3(p.buckets), dim3(kPartSortThreads), (size_t)4 << p.kbits, s, part_pos,
+                     part_id, np, g, p.kbits, work, off, pos_out, id_out);
 }
 }  // namespace
 
 void launch_partition(const float* pos, long np, const TileGeom& g, uint32_t* work, float* part_pos,
                       uint32_t* part_id, uint32_t* off, float* pos_out, uint32_t* id_out, hipStream_t s) {
-  const bool large = np >= (1L << 23);
+  const PartitionGeom p = partition_geom(np, g.ntiles);
+  constexpr int B = kPartitionBuckets;
   if (part_id)
-    large ? partition<1024, true>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s)
-          : partition<512, true>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s);
+    p.threads == B ? partition<B, true>(pos, np, g, p, work, part_pos, part_id, off, pos_out, id_out, s)
+                   : partition<B / 2, true>(pos, np, g, p, work, part_pos, part_id, off, pos_out, id_out, s);
   else
-    large ? partition<1024, false>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s)
-          : partition<512, false>(pos, np, g, work, part_pos, part_id, off, pos_out, id_out, s);
+    p.threads == B ? partition<B, false>(pos, np, g, p, work, part_pos, part_id, off, pos_out, id_out, s)
+                   : partition<B / 2, false>(pos, np, g, p, work, part_pos, part_id, off, pos_out, id_out, s);
 }
 
 long scan_scratch_words(long n) { return (n + kScanBlock - 1) / kScanBlock; }
