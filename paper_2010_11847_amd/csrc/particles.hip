@@ -311,11 +311,10 @@ __global__ __launch_bounds__(B) void k_part_hist(const float* __restrict__ pos, 
 // A chunk of B * kPartItems particles per workgroup: ranked by bucket in LDS,
 // room reserved with one global atomic per bucket and chunk, and written out
 // in runs of the chunk's particles of one bucket.  Workgroup 0 also settles
-// the mode: a bucket of more than four times the mean would keep one
-// workgroup of the next pass busy longer than the rest together.
+// the mode: moved only, when a bucket holds more than `large`.
 template <int B, bool ID>
 __global__ __launch_bounds__(B) void k_part_move(const float* __restrict__ pos, long np, TileGeom g,
-                                                            int kbits, uint32_t* __restrict__ work,
+                                                            int kbits, uint32_t large, uint32_t* __restrict__ work,
                                                             float* __restrict__ part_pos,
                                                             uint32_t* __restrict__ part_id) {
   if (!work[0]) return;   // uniform
@@ -338,7 +337,7 @@ __global__ __launch_bounds__(B) void k_part_move(const float* __restrict__ pos, 
   }
   const uint32_t total = work[kPartHist + tid];
   if (blockIdx.x == 0) {
-    const bool moved = __syncthreads_or(total > (uint32_t)(np / (B / 4) + 32768));
+    const bool moved = __syncthreads_or(total > large);
     if (tid == 0) work[1] = moved ? PART_MOVED : PART_SORTED;
   }
   const uint32_t gstart = part_scan(total, wsum);   // first slot of bucket tid (its barriers also order h)
@@ -1245,7 +1244,7 @@ void partition(const float* pos, long np, const TileGeom& g, const PartitionGeom
   hipLaunchKernelGGL(k_part_hist<B>, dim3(grid_for(np, B * 16, 512 * 1024 / B)), dim3(B), 0, s, pos, np, g, p.kbits,
                      work);
   hipLaunchKernelGGL((k_part_move<B, ID>), dim3(grid_for(np, B * kPartItems, 1 << 30)), dim3(B), 0, s, pos, np, g,
-                     p.kbits, work, part_pos, part_id);
+                     p.kbits, partition_large(np, p.buckets), work, part_pos, part_id);
   // LDS: the bucket's keys, at most 64 KB
   hipLaunchKernelGGL(k_part_sort<ID>, dim3(p.buckets), dim3(kPartSortThreads), (size_t)4 << p.kbits, s, part_pos,
                      part_id, np, g, p.kbits, work, off, pos_out, id_out);
