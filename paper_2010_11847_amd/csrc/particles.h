@@ -166,7 +166,7 @@ static inline PartitionGeom partition_geom(long np, int ntiles) {
 // moved only.  (Of uniform sets, 16 million on 32^3 in 64 buckets: paint
 // 1198 us sorted in the buckets, 2379 moved only.)  The 8 buckets of 8^3 and
 // 16^3 meshes count as 64: 8 workgroups sort 4 million on 16^3 in 1825 us,
-// against 1693 moved only; at 0.2 million either takes the same.
+// against 1666 moved only; at 0.2 million either takes the same.
 static inline uint32_t partition_large(long np, int buckets) {
   return (uint32_t)(4 * np / (buckets < 64 ? 64 : buckets) + 32768);
 }

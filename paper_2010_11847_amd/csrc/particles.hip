@@ -74,8 +74,10 @@ __global__ __launch_bounds__(kThreads) void k_keys(const float* __restrict__ pos
   // not where a tile holds many: the counts of the few tiles that an XCD then
   // works on lie on a few of its L2 channels (16 million particles in tile
   // order on 128^3, 31000 a tile: this pass 116 us in plain order, 319 so; at
-  // 7800 a tile paint 153 against 177 us, at 4000 and less the same).
-  const bool dense = np > 4096L * g.ntiles;
+  // 7800 a tile paint 153 against 177 us, at 4000 and less the same).  The 8
+  // tiles of an 8^3 or 16^3 mesh go one to an XCD at any density (4 million in
+  // cell order on 16^3: 1650 us so, 1768 in plain order).
+  const bool dense = np > 4096L * g.ntiles && g.ntiles > 8;
   for (long b0 = (long)(dense ? (int)blockIdx.x : xcd_tile(blockIdx.x, gridDim.x)) * blockDim.x; b0 < np; b0 += stride) {
     const long t = b0 + threadIdx.x;
     const bool valid = t < np;
