@@ -1313,8 +1313,8 @@ int pm_run_adjoint(pm_ctx* ctx, const double* h_a, int n_a, const float* d_ckpt,
         pmk::launch_readout_grad3(c.pos_s[0], c.id_s[0], np, c.ng, fmesh, pbar, (float)kj, xbar, c.stream);
       // term B: positions that paint the density, through G^T
       // the three channels in one launch (the meshes are equally spaced)
-      pmk::launch_paint_weighted(c.pos_s[0], c.id_s[0], c.off, c.tg, pbar, -1, (float)kj, &c.absmax->max_bits,
-                                 c.mesh[0].r, c.count, c.stream, (long)(c.mesh[1].r - c.mesh[0].r), gate);
+      pmk::launch_paint_weighted(c.pos_s[0], c.id_s[0], c.off, c.tg, pbar, (float)kj, &c.absmax->max_bits,
+                                 c.mesh[0].r, (long)(c.mesh[1].r - c.mesh[0].r), c.count, c.stream, gate);
       if (gate.d) c.clear_counts();   // (the paints may have returned at once)
       // pyramid force: F_d^T m = G_d^T (m - E R m) + 2^f E G_c,d^T R m
       // (R = REDUCE, E = EXPAND); the interleaved force mesh, read by term A

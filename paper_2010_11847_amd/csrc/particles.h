@@ -185,8 +185,8 @@ void launch_scatter(const ScatterArgs& a, hipStream_t s);
 void launch_paint(const float* pos_sorted, const uint32_t* off, const TileGeom& g, float* out, float scale,
                   float offset, uint32_t* clear, bool std_layout, hipStream_t s, const BatchArg& bat = BatchArg());
 void launch_readout(const ReadoutArgs& a, hipStream_t s);
-// *bits = bit pattern of max_i |v_i| over n floats
-// With x: v += c x first.  a->gate is a descriptor of member 0 when some value
+// a->max_bits = bit pattern of max_i |v_i| over n floats (a NaN is passed over);
+// with x: v += c x first.  a->gate is a descriptor of member 0 when some value
 // is not zero, else a skipped one: a BatchArg of it makes launches that only
 // carry v's (linear) image return at once when v is all zero.
 struct AbsMax {
@@ -195,12 +195,11 @@ struct AbsMax {
 };
 void launch_absmax(float* v, const float* x, float c, long n, AbsMax* a, hipStream_t s);
 // x-blocked paint of signed masses wts[3 id + comp] * k (the adjoint's
-// cotangent channels); *maxbits must hold max |wts| (launch_absmax).
-// comp < 0: the three components in one launch, component d into
-// out + d * out_stride.
+// cotangent channels), the three components in one launch, component comp
+// into out + comp * out_stride; *maxbits must hold max |wts| (launch_absmax).
 void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, const uint32_t* off, const TileGeom& g,
-                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, uint32_t* clear,
-                           hipStream_t s, long out_stride = 0, const BatchArg& bat = BatchArg());
+                           const float* wts, float k, const uint32_t* maxbits, float* out, long out_stride, uint32_t* clear,
+                           hipStream_t s, const BatchArg& bat = BatchArg());
 void launch_kick_drift(float* pos, float* mom, const float* f, long np, float kick, float drift, float nmesh,
                        hipStream_t s);
 // mom[j] += u1 psi1[id[j]] + u2 psi2[id[j]] over np sorted particles (the

@@ -532,8 +532,7 @@ __global__ void k_scatter(ScatterArgs a) {
 //    |deposit| < 2^40 is an integer held exactly and 2^23 of them fit.
 struct PaintWeights {
   const uint32_t* id = nullptr;     // sorted particle ids
-  const float* wts = nullptr;       // [np][3] in particle-id order
-  int comp = 0;                     // < 0: component blockIdx.y, into out + blockIdx.y * out_stride
+  const float* wts = nullptr;       // [np][3] in particle-id order: component blockIdx.y into out + blockIdx.y * out_stride
   long out_stride = 0;
   float k = 1.f;
   const uint32_t* maxbits = nullptr;   // bits of max |wts| (non-negative float)
@@ -562,10 +561,8 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
   }
   // the sort's spent cursors, the counts of the next sort
   if (blockIdx.y == 0 && threadIdx.x < 64) clear[(long)blockIdx.x * 64 + threadIdx.x] = 0u;
-  if (WT && pw.comp < 0) {   // uniform: one component per blockIdx.y
-    pw.comp = (int)blockIdx.y;
-    out += blockIdx.y * pw.out_stride;
-  }
+  const int comp = (int)blockIdx.y;
+  if (WT) out += comp * pw.out_stride;
   const int TX = g.tx, TY = g.ty, TZ = g.tz, n = g.n;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   int tx, ty, tz;
@@ -617,7 +614,7 @@ __global__ __launch_bounds__(kPaintThreads) void k_paint(const float* __restrict
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) pid[u] = pw.id[jj[u]];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) mp[u] = pw.wts[3 * (long)pid[u] + pw.comp] * pw.k;
+      for (int u = 0; u < kBatch; ++u) mp[u] = pw.wts[3 * (long)pid[u] + comp] * pw.k;
     }
     // pin the loads here: each particle's use sits in its own branch, and
     // sunk into those branches the loads would run one round trip at a time
@@ -1110,16 +1107,13 @@ __global__ void k_kick_drift(float* __restrict__ pos, float* __restrict__ mom, c
   }
 }
 
-// bits of max_i |v_i| (non-negative floats order like their bit patterns);
-// NaNs are ignored by fmaxf
-// (16-byte loads; one atomic per workgroup: the atomics on the one word
-// are serialized, so their number, not the loads, set the time of a small
-// launch)
-// max |v| as float bits into a->max_bits; a->gate.member becomes 0 when any
-// value is not zero (NaN, which the maximum passes over, included).  AXPY:
-// v += c x first, so that the sweep's update of the momentum cotangent and
-// the next step's maximum share one pass (15.8 + 12.9 -> 20.3 us for 128^3
-// particles).
+// max |v| as float bits into a->max_bits (non-negative floats order like their
+// bit patterns; fmaxf passes over NaN); a->gate.member becomes 0 when any value
+// is not zero, NaN included.  16-byte loads; one atomic per workgroup: the
+// atomics on the one word are serialized, so their number, not the loads, set
+// the time of a small launch.  AXPY: v += c x first, so that the sweep's update
+// of the momentum cotangent and the next step's maximum share one pass
+// (15.8 + 12.9 -> 20.3 us for 128^3 particles).
 __global__ void k_absmax_init(AbsMax* __restrict__ a) {
   a->max_bits = 0u;
   a->gate.member = -1;
@@ -1318,16 +1312,15 @@ void launch_absmax(float* v, const float* x, float c, long n, AbsMax* a, hipStre
 }
 
 void launch_paint_weighted(const float* pos_sorted, const uint32_t* id_sorted, const uint32_t* off, const TileGeom& g,
-                           const float* wts, int comp, float k, const uint32_t* maxbits, float* out, uint32_t* clear,
-                           hipStream_t s, long out_stride, const BatchArg& bat) {
+                           const float* wts, float k, const uint32_t* maxbits, float* out, long out_stride, uint32_t* clear,
+                           hipStream_t s, const BatchArg& bat) {
   PaintWeights pw;
   pw.id = id_sorted;
   pw.wts = wts;
-  pw.comp = comp;
   pw.out_stride = out_stride;
   pw.k = k;
   pw.maxbits = maxbits;
-  hipLaunchKernelGGL((k_paint<false, true>), dim3(g.ntiles, comp < 0 ? 3 : 1), dim3(kPaintThreads), 0, s, pos_sorted,
+  hipLaunchKernelGGL((k_paint<false, true>), dim3(g.ntiles, 3), dim3(kPaintThreads), 0, s, pos_sorted,
                      off, g, out, 1.f, 0.f, pw, bat, clear);
 }
 

@@ -122,13 +122,6 @@ static __device__ __forceinline__ void store_walk(int c, const TileGeom& g, int&
   cx = ((r >> (g.lz + g.ly)) << 3) | (c & 7);
 }
 
-// (x, y, z) cell offsets inside a tile of flattened cell index c (z fastest)
-static __device__ __forceinline__ void cell_coords(int c, const TileGeom& g, int& cx, int& cy, int& cz) {
-  cz = c & (g.tz - 1);
-  cy = (c >> g.lz) & (g.ty - 1);
-  cx = c >> (g.lz + g.ly);
-}
-
 // Rank of this lane's key among all keys counted so far (count[key] is
 // advanced by the group and its old value returned).  Lanes of a wave with
 // equal keys share one atomic: the groups are found with ballots
