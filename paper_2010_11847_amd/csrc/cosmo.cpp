@@ -105,7 +105,7 @@ void Cosmo::growth_sorted(const double* a, int n, double d1_norm, double* out6) 
       l = p->l;
       std::copy(p->y, p->y + 4, y);
     }
-    while (l + kStep <= lt) {
+    while (l + kStep <= lt && std::isfinite(lt)) {   // (infinity: one step, NaN)
       rk4_step(l, kStep, y, y);
       l += kStep;
     }
