@@ -890,7 +890,7 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
     if (d_noise_out) pmk::launch_relayout(f[0].r, d_noise_out, c.npart, false, c.stream);
     pmk::fft_z_r2c(c.tl, &f[0], 1, c.stream);
   }
-  pmk::fft_y_exact(c.tl, &f[0], 1, -1, c.stream);
+  pmk::fft_y(c.tl, &f[0], 1, -1, c.stream);
   const int order = c.cfg.lpt_order;
   pmk::SpecOp op;
   op.kind = pmk::OP_LPT1;
@@ -901,10 +901,10 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
     op.out_q[i] = f[1 + i].q;
   }
   pmk::fft_x_fused(c.tl, f[0], op, c.stream);
-  pmk::fft_y_exact(c.tl, &f[1], op.n_out, 1, c.stream);
+  pmk::fft_y(c.tl, &f[1], op.n_out, 1, c.stream);
   if (order >= 2) {
     pmk::launch_lpt_delta2(c.tl, &f[4], f[0], c.stream);
-    pmk::fft_y_exact(c.tl, &f[0], 1, -1, c.stream);
+    pmk::fft_y(c.tl, &f[0], 1, -1, c.stream);
     pmk::SpecOp op2;
     op2.kind = pmk::OP_LPT2;
     op2.n_out = 3;
@@ -914,7 +914,7 @@ int pm_init_lpt(pm_ctx* ctx, uint64_t seed, double a0, const float* d_noise_in, 
       op2.out_q[i] = f[4 + i].q;
     }
     pmk::fft_x_fused(c.tl, f[0], op2, c.stream);
-    pmk::fft_y_exact(c.tl, &f[4], 3, 1, c.stream);
+    pmk::fft_y(c.tl, &f[4], 3, 1, c.stream);
   }
   double g[6];
   c.cosmo.growth(a0, g);
@@ -1551,7 +1551,7 @@ int pm_power(pm_ctx* ctx, const float* d_delta, int n_bins, int n_max, int decon
   pm_ctx& c = *ctx;
   if (n_bins < 1 || n_bins > c.L.n_bins_max) return c.fail(PM_EINVAL, "n_bins must be in [1, n_mesh/2]");
   c.z_r2c_from(c.tm, d_delta, c.mesh[0]);
-  pmk::fft_y_exact(c.tm, &c.mesh[0], 1, -1, c.stream);
+  pmk::fft_y(c.tm, &c.mesh[0], 1, -1, c.stream);
   pmk::PowerArgs a;
   a.n_bins = n_bins;
   a.n_max = n_max;

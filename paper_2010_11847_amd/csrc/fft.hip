@@ -183,6 +183,92 @@ __device__ __forceinline__ void dft_fixed(float2 (&v)[R]) {
   }
 }
 
+// Meshes below 64^3 keep the roundings of whole columns: a radix-2 transform of
+// N points in one thread, as the passes once had, whose bits a run amplifies
+// (a deconvolved run of 8^3 particles on 32^3 moved by 3e-5 of its momenta with
+// other ones, against bounds of 2e-5).  The levels are shared by the N / R
+// threads of a column: dft_head takes the first log2 R levels on the elements
+// j + (N / R) e of thread j, and the last N / R points are a small transform
+// without products.  An N-point twiddle of a thread depends on j, so it comes
+// from a table, and which of its products is fused (SmallForm) is data too.
+enum SmallForm { SMALL_FWD, SMALL_INV, SMALL_Z_FWD, SMALL_Z_INV };   // columns forward, inverse; z lines
+
+__constant__ const float2 kTurn32[16] = {   // exp(2 pi i idx / 32)
+    {1.000000000e+00f, 0.0f},             {9.807852804e-01f, 1.950903220e-01f},  {9.238795325e-01f, 3.826834324e-01f},
+    {8.314696123e-01f, 5.555702330e-01f}, {7.071067812e-01f, 7.071067812e-01f},  {5.555702330e-01f, 8.314696123e-01f},
+    {3.826834324e-01f, 9.238795325e-01f}, {1.950903220e-01f, 9.807852804e-01f},  {0.0f, 1.000000000e+00f},
+    {-1.950903220e-01f, 9.807852804e-01f}, {-3.826834324e-01f, 9.238795325e-01f}, {-5.555702330e-01f, 8.314696123e-01f},
+    {-7.071067812e-01f, 7.071067812e-01f}, {-8.314696123e-01f, 5.555702330e-01f}, {-9.238795325e-01f, 3.826834324e-01f},
+    {-9.807852804e-01f, 1.950903220e-01f}};
+
+// a times the twiddle k of the level of `len` points, in its group that starts
+// at s, of an N-point transform.  The real part fuses the product with the
+// sine where re_sine, the imaginary part the one with the cosine where im_cos.
+template <int N, int DIR, SmallForm F>
+__device__ __forceinline__ float2 twiddle_small(float2 a, int len, int s, int k) {
+#pragma clang fp contract(off)
+  const int idx = k * (32 / len);
+  bool re_sine, im_cos;
+  if (F == SMALL_FWD) {
+    re_sine = idx > 8;
+    im_cos = idx != 4;
+  } else if (F == SMALL_Z_FWD) {
+    re_sine = im_cos = !(N == 16 && len == 8 && s == 8 && k == 1);
+  } else {
+    re_sine = false;
+    im_cos = len == 16 && s == (F == SMALL_INV ? 16 : 0) && (k == 1 || k == 3) && N == (F == SMALL_INV ? 32 : 16);
+  }
+  const float2 w = kTurn32[idx];
+  const float c = w.x, t = DIR < 0 ? -w.y : w.y;
+  const float re = re_sine ? fmaf(-a.y, t, a.x * c) : fmaf(a.x, c, -(a.y * t));
+  const float im = im_cos ? fmaf(a.y, c, a.x * t) : fmaf(a.x, t, a.y * c);
+  const float2 q = cmul_i<DIR>(a);   // no products in the turns by 0 and by a quarter (0 times infinity)
+  return make_float2(idx == 0 ? a.x : (idx == 8 ? q.x : re), idx == 0 ? a.y : (idx == 8 ? q.y : im));
+}
+
+// SCALED: the elements are v[e] d[e] with real d, whose products the first
+// level fuses: v0 d0 +- (v1 d1, rounded)
+template <int N, int R, int DIR, SmallForm F, bool SCALED = false>
+__device__ __forceinline__ void dft_head(float2 (&v)[R], int j, const float* d = nullptr) {
+#pragma clang fp contract(off)
+  constexpr int T = N / R;
+#pragma unroll
+  for (int h = R / 2; h >= 1; h >>= 1) {
+    const int len = 2 * h * T;
+#pragma unroll
+    for (int s = 0; s < R; s += 2 * h) {
+#pragma unroll
+      for (int k = 0; k < h; ++k) {
+        const float2 a = v[s + k];
+        float2 b = v[s + k + h], diff;
+        if (SCALED && h == R / 2) {
+          b = make_float2(b.x * d[s + k + h], b.y * d[s + k + h]);
+          v[s + k] = make_float2(fmaf(a.x, d[s + k], b.x), fmaf(a.y, d[s + k], b.y));
+          diff = make_float2(fmaf(a.x, d[s + k], -b.x), fmaf(a.y, d[s + k], -b.y));
+        } else {
+          v[s + k] = make_float2(a.x + b.x, a.y + b.y);   // (a and b may be products: not fused)
+          diff = make_float2(a.x - b.x, a.y - b.y);
+        }
+        v[s + k + h] = twiddle_small<N, DIR, F>(diff, len, s * T, j + T * k);
+      }
+    }
+  }
+  float2 t[R];
+#pragma unroll
+  for (int i = 0; i < R; ++i) t[i] = v[bitrev<R>(i)];
+#pragma unroll
+  for (int i = 0; i < R; ++i) v[i] = t[i];
+}
+
+// The last log2 R levels of an inverse, on R consecutive elements.
+template <int R>
+__device__ __forceinline__ void dft_tail_inv(float2 (&v)[R]) {
+  if constexpr (R <= 4)
+    dft<R, 1>(v);   // no products
+  else
+    dft_head<R, R, 1, SMALL_INV>(v, 0);
+}
+
 // Stages of the column passes.  Every size takes two: with a whole column of
 // N <= 32 in one thread, 16 lanes of a workgroup's 256 worked on a chain of
 // 32-point transforms (two 12.5 us x passes at 32^3, whose data is 0.1 us of
@@ -197,11 +283,11 @@ template <> struct Split<256> { static constexpr int R1 = 16, R2 = 16; };
 template <> struct Split<512> { static constexpr int R1 = 32, R2 = 16; };
 template <> struct Split<1024> { static constexpr int R1 = 32, R2 = 32; };
 
-// Stages of the passes that make the initial conditions and of P(k): below 64
-// points the whole column stays in one thread, for its roundings.  A run on 64^3 from 16^3
-// or 32^3 particles, deconvolved, amplifies the two stages' other last bits to
-// 2.5e-5 (norm) and 1e-3 (largest) of its momenta; they cost it once a run
-// (x 11.8 -> 17.0, y 3.7 -> 5.9 us at 32^3).
+// Stages of the x pass that makes the initial conditions: below 64 points the
+// whole column stays in one thread, for its roundings.  A run on 64^3 from 16^3
+// or 32^3 particles, deconvolved, amplifies other last bits to 2.5e-5 (norm) and
+// 1e-3 (largest) of its momenta; they cost it once a run (11.8 -> 17.0 us at
+// 32^3).
 template <int N> struct ExactSplit : Split<N> {};
 template <> struct ExactSplit<8> { static constexpr int R1 = 8, R2 = 1; };
 template <> struct ExactSplit<16> { static constexpr int R1 = 16, R2 = 1; };
@@ -311,14 +397,14 @@ struct ColPass {
 // 130 us at 256^3).  Its tiles walk columns fastest: a numpy row's 128-byte
 // pieces are unaligned ((N/2 + 1)-element rows), and the tiles that share
 // their lines then follow each other on one XCD.
-template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false, class S = Split<N>>
+template <int N, int M, int DIR, bool BLK, int TH = kThreads, bool NP = false>
 __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __restrict__ tw) {
-  constexpr int R1 = S::R1, R2 = S::R2;
+  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2;
   constexpr bool FIXED = NP && DIR < 0;   // the bits of the spectrum that k_power_x bins
   constexpr int CS = BLK ? 8 : 1;
   constexpr int IA = (M * R2 + TH - 1) / TH;
   constexpr int IB = (M * R1 + TH - 1) / TH;
-  __shared__ float2 lds[ColLds<N, M, S>::size];
+  __shared__ float2 lds[ColLds<N, M>::size];
   int tile = xcd_tile(blockIdx.x, gridDim.x);
   const bool is_plane = tile >= p.nb_main;
   if (is_plane) tile -= p.nb_main;
@@ -346,7 +432,7 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       base[row_off<BLK>(n, g.sn) + m * CS] = v;
   };
 
-  constexpr int SA = ColLds<N, M, S>::SA;
+  constexpr int SA = ColLds<N, M>::SA;
 #pragma unroll
   for (int i = 0; i < IA; ++i) {
     const int it = tid + i * TH;
@@ -357,7 +443,11 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
 #pragma unroll
       for (int j1 = 0; j1 < R1; ++j1)
         v[j1] = ok ? load(R2 * j1 + j2, m) : make_float2(0.f, 0.f);
-      if constexpr (FIXED) {
+      if constexpr (N < 64) {
+        dft_head<N, R1, DIR, DIR < 0 ? SMALL_FWD : SMALL_INV>(v, j2);
+#pragma unroll
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = v[l1];
+      } else if constexpr (FIXED) {
         dft_fixed<R1, false>(v);
 #pragma unroll
         for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[l1] : cmul_fixed(v[l1], tw[j2 * l1]);
@@ -377,10 +467,10 @@ __global__ __launch_bounds__(TH) void k_fft_cols(ColPass p, const float2* __rest
       float2 v[R2];
 #pragma unroll
       for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
-      if constexpr (FIXED)
+      if constexpr (FIXED && N >= 64)
         dft_fixed<R2, true>(v);
       else
-        dft<R2, DIR>(v);
+        dft<R2, DIR>(v);   // below 64 points: at most 4, no products
       if (c0 + m < g.ncols) {
 #pragma unroll
         for (int l2 = 0; l2 < R2; ++l2) store(l1 + R1 * l2, m, v[l2]);
@@ -627,7 +717,9 @@ __device__ __forceinline__ void std_store(const float2* __restrict__ lds, float*
 // load happens before the first write to lds).  On return Z[m][k] is in lds
 // at m*ZP + k (natural order).  Items map with the line m fastest so that
 // LDS accesses of a wave spread over the banks.
-template <class G, int DIR, class Load>
+// FORM >= 0: the roundings of one of the forms of SmallForm, on lines of R1 R2
+// points.
+template <class G, int DIR, int FORM = -1, class Load>
 __device__ __forceinline__ void zline_transform(float2* lds, const float2* __restrict__ twh, Load load) {
   constexpr int R1 = G::R1, R2 = G::R2, L = G::L, LP = G::LP, ZP = G::ZP;
   const int tid = threadIdx.x;
@@ -671,10 +763,16 @@ __device__ __forceinline__ void zline_transform(float2* lds, const float2* __res
       const int it = tid + i * kThreads;
       if (it < L * R2) {
         const int m = it % L, j2 = it / L;
-        dft<R1, DIR>(v[i]);
+        if constexpr (FORM >= 0) {
+          dft_head<R1 * R2, R1, DIR, (SmallForm)FORM>(v[i], j2);
 #pragma unroll
-        for (int l1 = 0; l1 < R1; ++l1)
-          lds[(l1 * R2 + j2) * LP + m] = l1 == 0 ? v[i][l1] : cmul(v[i][l1], tw_get<DIR>(twh, j2 * l1));
+          for (int l1 = 0; l1 < R1; ++l1) lds[(l1 * R2 + j2) * LP + m] = v[i][l1];
+        } else {
+          dft<R1, DIR>(v[i]);
+#pragma unroll
+          for (int l1 = 0; l1 < R1; ++l1)
+            lds[(l1 * R2 + j2) * LP + m] = l1 == 0 ? v[i][l1] : cmul(v[i][l1], tw_get<DIR>(twh, j2 * l1));
+        }
       }
     }
     __syncthreads();
@@ -1085,8 +1183,7 @@ __global__ __launch_bounds__(kThreads) void k_c2r_z3(const float* __restrict__ r
 // what counts is the number of passes: z and y forward 7.3 -> 5.2 us, y and z
 // inverse of the three components 8.5 -> 6.1 us at 32^3.  The planes of a block
 // interleave by 8-byte words, so both passes write another buffer than they
-// read.  (From 64^3 on, the separate passes keep their products' roundings,
-// which a run would amplify.)
+// read.  Their roundings are those of the separate passes, spelled out.
 // ===========================================================================
 template <int LEN, int LINES>
 struct PlaneLines {
@@ -1117,16 +1214,18 @@ __global__ __launch_bounds__(kThreads) void k_plane_forward(const float* __restr
   q = byte_adv(q, bo);
   const int x = xcd_tile(blockIdx.x, gridDim.x), xi = x & 7;
   const long row = (long)(x >> 3) * N;   // (x/8, y = 0)
-  zline_transform<GZ, -1>(lds, twh, [&](int y, int j) {
+  zline_transform<GZ, -1, SMALL_Z_FWD>(lds, twh, [&](int y, int j) {
     const float* v = r + ((row + y) * N + 2 * j) * 8 + xi;
     return make_float2(v[0], v[8]);
   });
-  zline_transform<GY, -1>(lds, twn, [&](int kz, int y) {
+  zline_transform<GY, -1, SMALL_FWD>(lds, twn, [&](int kz, int y) {
+#pragma clang fp contract(off)
     const float2 zk = lds[y * GZ::ZP + (kz & (H - 1))];
     const float2 zm = cconj(lds[y * GZ::ZP + ((H - kz) & (H - 1))]);
     const float2 e = cscale(cadd(zk, zm), 0.5f);
     const float2 dif = csub(zk, zm);
-    const float2 t = cmul(make_float2(0.5f * dif.y, -0.5f * dif.x), twn[kz & (H - 1)]);
+    const float2 o = make_float2(0.5f * dif.y, -0.5f * dif.x), w = twn[kz & (H - 1)];
+    const float2 t = make_float2(fmaf(o.x, w.x, -(o.y * w.y)), fmaf(o.y, w.x, o.x * w.y));
     if (kz == 0) return make_float2(e.x + t.x, 0.f);
     if (kz == H) return make_float2(e.x - t.x, 0.f);
     return cadd(e, t);
@@ -1162,19 +1261,22 @@ __global__ __launch_bounds__(kThreads) void k_plane_force(const float2* __restri
   const int x = xcd_tile(blockIdx.x, gridDim.x), xi = x & 7;
   const long row = (long)(x >> 3) * N;
   // the three components side by side: one round of loads and barriers each
-  zline_transform<GY, 1>(lds, t.tw_n, [&](int m, int ky) {
+  zline_transform<GY, 1, SMALL_INV>(lds, t.tw_n, [&](int m, int ky) {
+#pragma clang fp contract(off)
     const int d = m / HC, kz = m - d * HC;
     const float2* c = d == 0 ? cx : cg;
     const float2* q = d == 0 ? qx : qg;
     const float2 v = kz < H ? c[((row + ky) * H + kz) * 8 + xi] : q[(row + ky) * 8 + xi];
-    return cscale(v, d == 0 ? 1.f : (d == 1 ? t.dxy[ky] : t.dz[kz]));
+    const float f = d == 0 ? 1.f : (d == 1 ? t.dxy[ky] : t.dz[kz]);
+    return make_float2(v.x * f, v.y * f);
   });
-  zline_transform<GZ, 1>(lds, t.tw_h, [&](int m, int k) {
+  zline_transform<GZ, 1, SMALL_Z_INV>(lds, t.tw_h, [&](int m, int k) {
+#pragma clang fp contract(off)
     const float2* l = lds + m / N * HC * GY::ZP + m % N;
     float2 a = l[k * GY::ZP], b = cconj(l[(H - k) * GY::ZP]);
     if (k == 0) a.y = b.y = 0.f;
-    const float2 e = cadd(a, b);
-    const float2 o = cmulc(csub(a, b), t.tw_n[k]);   // (a - b) exp(+2 pi i k / N)
+    const float2 e = cadd(a, b), f = csub(a, b), w = t.tw_n[k];
+    const float2 o = make_float2(fmaf(f.x, w.x, f.y * w.y), fmaf(f.y, w.x, -(f.x * w.y)));   // f exp(+2 pi i k / N)
     return make_float2(e.x - o.y, e.y + o.x);        // e + i o
   });
   struct F3 {
@@ -1538,8 +1640,7 @@ constexpr int kPowerBlocks = 512;
 template <int N, int M>
 __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, int nb_main, int ntiles,
                                                       const float2* __restrict__ tw, PowerArgs a) {
-  using S = ExactSplit<N>;   // two stages from 64 points up
-  constexpr int R1 = S::R1, R2 = S::R2, H = N / 2;
+  constexpr int R1 = Split<N>::R1, R2 = Split<N>::R2, H = N / 2;
   constexpr int IA = (M * R2 + kThreads - 1) / kThreads;
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;
   constexpr int SA = R2 * M + M;
@@ -1572,10 +1673,13 @@ __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, in
 #pragma unroll
         for (int j1 = 0; j1 < R1; ++j1)
           v[j1] = ok ? base[row_off<true>(R2 * j1 + j2, g.sn) + m * 8] : make_float2(0.f, 0.f);
-        dft_fixed<R1, false>(v);
+        if constexpr (N < 64)
+          dft_head<N, R1, -1, SMALL_FWD>(v, j2);
+        else
+          dft_fixed<R1, false>(v);
 #pragma unroll
         for (int l1 = 0; l1 < R1; ++l1)
-          lds[l1 * SA + j2 * M + m] = l1 == 0 || R2 == 1 ? v[l1] : cmul_fixed(v[l1], tw[j2 * l1]);
+          lds[l1 * SA + j2 * M + m] = l1 == 0 || N < 64 ? v[l1] : cmul_fixed(v[l1], tw[j2 * l1]);
       }
     }
     __syncthreads();
@@ -1587,7 +1691,10 @@ __global__ __launch_bounds__(kThreads) void k_power_x(ColGeom gm, ColGeom gp, in
         float2 v[R2];
 #pragma unroll
         for (int j2 = 0; j2 < R2; ++j2) v[j2] = lds[l1 * SA + j2 * M + m];
-        dft_fixed<R2, true>(v);
+        if constexpr (N < 64)
+          dft<R2, -1>(v);
+        else
+          dft_fixed<R2, true>(v);
         // back into the slots this item read (no other thread's), so that the
         // binning below is a loop: unrolled over registers it needed more
         // than 256 of them and left one wave per SIMD
@@ -1662,7 +1769,9 @@ __global__ __launch_bounds__(kThreads) void k_power_reduce(const double* __restr
 // element costs about ten instructions.  FILT = false leaves out the
 // deconvolution and split branches (their registers included): callers
 // that take it are launched only for ops with neither.
-template <int R1, int R2, bool FILT = true>
+// SMALL (meshes below 64^3): sums and products along x, y, z in that order,
+// their roundings spelled out.
+template <int R1, int R2, bool FILT = true, bool SMALL = false>
 __device__ __forceinline__ void force_factors(const FftTables& t, const SpecOp& op, int l1, int ky, int kz,
                                               float (&fac)[R2]) {
   float aux[R2];
@@ -1670,6 +1779,24 @@ __device__ __forceinline__ void force_factors(const FftTables& t, const SpecOp& 
   for (int l2 = 0; l2 < R2; ++l2) fac[l2] = t.kxy[l1 + R1 * l2];
 #pragma unroll
   for (int l2 = 0; l2 < R2; ++l2) asm volatile("" : "+v"(fac[l2]));
+  if constexpr (SMALL) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int l2 = 0; l2 < R2; ++l2) {
+      const int kx = l1 + R1 * l2;
+      const float kk = fac[l2] + t.kxy[ky] + t.kz[kz];
+      fac[l2] = kk > 0.f ? op.scale * __builtin_amdgcn_rcpf(kk) : 0.f;
+      if (op.deconv) {
+        const float wv = t.wxy[kx] * t.wxy[ky] * t.wz[kz];
+        fac[l2] *= __builtin_amdgcn_rcpf(op.deconv == 1 ? wv : wv * wv);
+      }
+      if (op.split) {
+        const float sxy = t.sxy[kx] * t.sxy[ky], sz = t.sz[kz];
+        fac[l2] *= op.split == 1 ? sxy * sz : fmaf(-sxy, sz, 1.f);
+      }
+    }
+    return;
+  }
   const float kyz = t.kxy[ky] + t.kz[kz];
 #pragma unroll
   for (int l2 = 0; l2 < R2; ++l2) {
@@ -1716,7 +1843,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
   constexpr int IB = (M * R1 + kThreads - 1) / kThreads;   // forward stage B, inverse stage A
   constexpr int SA = ColLds<N, M>::SA, SB = ColLds<N, M>::SB;
   __shared__ float2 lds[ColLds<N, M>::size];
-  __shared__ float2 tws[R1 * R2];   // exp(-2 pi i l j / N), l < R1, j < R2
+  __shared__ float2 tws[N >= 64 ? R1 * R2 : 1];   // exp(-2 pi i l j / N), l < R1, j < R2
   int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int mode = tile >= a.nb_main ? 1 : 0;
   if (mode) tile -= a.nb_main;
@@ -1747,7 +1874,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
 #pragma unroll
   for (int k = 0; k < IT; ++k) {
     const int e = tid + k * kThreads;
-    if (e < R1 * R2) twv[k] = t.tw_n[(e / R2) * (e % R2)];
+    if (N >= 64 && e < R1 * R2) twv[k] = t.tw_n[(e / R2) * (e % R2)];
   }
   // forward stage A: rows x = R2 j1 + j2, all loads first (non-temporal:
   // the two outputs, not the input, gain from staying in L2, measured 3.61
@@ -1772,7 +1899,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
       const int m = it % M, l1 = it / M;
       int ky, kz;
       freq(m, ky, kz);
-      force_factors<R1, R2>(t, op, l1, ky, kz, fac[i]);
+      force_factors<R1, R2, true, (N < 64)>(t, op, l1, ky, kz, fac[i]);
 #pragma unroll
       for (int l2 = 0; l2 < R2; ++l2) dxv[i][l2] = t.dxy[l1 + R1 * l2];
     }
@@ -1780,7 +1907,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
 #pragma unroll
   for (int k = 0; k < IT; ++k) {
     const int e = tid + k * kThreads;
-    if (e < R1 * R2) tws[e] = twv[k];
+    if (N >= 64 && e < R1 * R2) tws[e] = twv[k];
   }
   __syncthreads();
 #pragma unroll
@@ -1788,9 +1915,15 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
     const int it = tid + i * kThreads;
     if (it < M * R2) {
       const int m = it % M, j2 = it / M;
-      dft<R1, -1>(v[i]);
+      if constexpr (N < 64) {
+        dft_head<N, R1, -1, SMALL_FWD>(v[i], j2);
 #pragma unroll
-      for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[i][l1] : cmul(v[i][l1], tws[l1 * R2 + j2]);
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = v[i][l1];
+      } else {
+        dft<R1, -1>(v[i]);
+#pragma unroll
+        for (int l1 = 0; l1 < R1; ++l1) lds[l1 * SA + j2 * M + m] = l1 == 0 ? v[i][l1] : cmul(v[i][l1], tws[l1 * R2 + j2]);
+      }
     }
   }
   __syncthreads();
@@ -1817,12 +1950,23 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
       if (it < M * R1) {
         const int m = it % M, l1 = it / M;
         float2 y[R2];
+        if constexpr (N < 64) {
 #pragma unroll
-        for (int l2 = 0; l2 < R2; ++l2) y[l2] = p ? cscale(X[i][l2], dxv[i][l2]) : X[i][l2];
-        dft<R2, 1>(y);
+          for (int l2 = 0; l2 < R2; ++l2) y[l2] = X[i][l2];
+          if (p)
+            dft_head<N, R2, 1, SMALL_INV, true>(y, l1, dxv[i]);
+          else
+            dft_head<N, R2, 1, SMALL_INV>(y, l1);
 #pragma unroll
-        for (int lp = 0; lp < R2; ++lp)
-          lds[lp * SB + l1 * M + m] = lp == 0 ? y[0] : cmulc(y[lp], tws[l1 * R2 + lp]);
+          for (int lp = 0; lp < R2; ++lp) lds[lp * SB + l1 * M + m] = y[lp];
+        } else {
+#pragma unroll
+          for (int l2 = 0; l2 < R2; ++l2) y[l2] = p ? cscale(X[i][l2], dxv[i][l2]) : X[i][l2];
+          dft<R2, 1>(y);
+#pragma unroll
+          for (int lp = 0; lp < R2; ++lp)
+            lds[lp * SB + l1 * M + m] = lp == 0 ? y[0] : cmulc(y[lp], tws[l1 * R2 + lp]);
+        }
       }
     }
     __syncthreads();
@@ -1834,7 +1978,10 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force(FusedArgs a) {
         float2 v[R1];
 #pragma unroll
         for (int l1 = 0; l1 < R1; ++l1) v[l1] = lds[lp * SB + l1 * M + m];
-        dft<R1, 1>(v);
+        if constexpr (N < 64)
+          dft_tail_inv<R1>(v);
+        else
+          dft<R1, 1>(v);
         if (c0 + m < g.ncols) {
 #pragma unroll
           for (int l2p = 0; l2p < R1; ++l2p) dst[row_off<true>(lp + R2 * l2p, g.sn) + m * 8] = cmul_i<1>(v[l2p]);
@@ -2023,7 +2170,7 @@ __global__ __launch_bounds__(kThreads) void k_fft_x_force_t(FusedArgs a) {
 // ---------------------------------------------------------------------------
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
-template <int N, int DIR, bool BLK, bool NP = false, bool EXACT = false>
+template <int N, int DIR, bool BLK, bool NP = false>
 void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int nbm, ColGeom gp, int nbp,
                  const float2* tw, hipStream_t s, const BatchArg& bat = BatchArg(), float2* np = nullptr,
                  float scale = 1.f) {
@@ -2044,19 +2191,18 @@ void launch_cols(float2* const* dm, float2* const* dq, int nf, ColGeom gm, int n
   p.np = np;
   p.scale = scale;
   dim3 grid(p.ntiles, nf, bat.n);
-  using S = std::conditional_t<(EXACT && N < 64), ExactSplit<N>, Split<N>>;
-  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH, NP, S>), grid, dim3(TH), 0, s, p, tw);
+  hipLaunchKernelGGL((k_fft_cols<N, M, DIR, BLK, TH, NP>), grid, dim3(TH), 0, s, p, tw);
 }
 
 // y pass over the main arrays and the Nyquist planes of nf fields
-template <int N, int DIR, bool EXACT = false>
+template <int N, int DIR>
 void ypass(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg()) {
   float2* dm[3];
   float2* dq[3];
   for (int i = 0; i < nf; ++i) { dm[i] = f[i].c(); dq[i] = f[i].q; }
   // main c[xb][y][kz][xi]: (b = xb, n = y, c = kz*8 + xi): sb = 4N^2, sn = 4N, ncols = 4N
   // Nyquist plane q[xb][y][xi]: (b = xb, n = y, c = xi): sb = 8N, sn = 8, ncols = 8
-  launch_cols<N, DIR, false, false, EXACT>(dm, dq, nf, ColGeom{4L * N * N, 4L * N, 4 * N, 0}, N / 8,
+  launch_cols<N, DIR, false>(dm, dq, nf, ColGeom{4L * N * N, 4L * N, 4 * N, 0}, N / 8,
                              ColGeom{8L * N, 8, 8, 0}, N / 8, t.tw_n, s, bat);
 }
 
@@ -2326,14 +2472,6 @@ void fft_z_r2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchA
 void fft_y(const FftTables& t, Field* f, int nf, int dir, hipStream_t s, const BatchArg& bat) {
   by3(f, nf, [&](Field* g, int k) {
 #define CALL(N) (dir < 0 ? ypass<N, -1>(t, g, k, s, bat) : ypass<N, 1>(t, g, k, s, bat))
-    PM_FFT_SWITCH(t.n, CALL)
-#undef CALL
-  });
-}
-
-void fft_y_exact(const FftTables& t, Field* f, int nf, int dir, hipStream_t s) {
-  by3(f, nf, [&](Field* g, int k) {
-#define CALL(N) (dir < 0 ? ypass<N, -1, true>(t, g, k, s) : ypass<N, 1, true>(t, g, k, s))
     PM_FFT_SWITCH(t.n, CALL)
 #undef CALL
   });

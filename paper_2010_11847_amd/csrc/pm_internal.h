@@ -111,9 +111,6 @@ void fft_x_force_t(const FftTables& t, Field* f, const SpecOp& op, hipStream_t s
 // Single passes (the composites above call these).
 void fft_z_r2c(const FftTables& t, Field* f, int nf, hipStream_t s, const BatchArg& bat = BatchArg());
 void fft_y(const FftTables& t, Field* f, int nf, int dir, hipStream_t s, const BatchArg& bat = BatchArg());
-// fft_y for the fields of the initial conditions and of measured spectra
-// (roundings kept below 64 points, where fft_y's other stages would be faster)
-void fft_y_exact(const FftTables& t, Field* f, int nf, int dir, hipStream_t s);
 void fft_z_c2r(const FftTables& t, Field* f, int nf, hipStream_t s);
 // z pass of three fields written as one interleaved real mesh
 // out[x/8][y][z][x%8][3] (the force meshes the particle readout gathers from).

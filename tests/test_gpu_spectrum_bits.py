@@ -20,7 +20,8 @@ F = np.float32
 fmaf = ctypes.CDLL(ctypes.util.find_library("m")).fmaf
 fmaf.restype = ctypes.c_float
 fmaf.argtypes = [ctypes.c_float] * 3
-STAGES = {8: (4, 2), 16: (4, 4), 32: (8, 4), 64: (8, 8), 128: (16, 8), 256: (16, 16), 512: (32, 16), 1024: (32, 32)}
+# below 64 points the levels are those of a whole column, whichever threads share them
+STAGES = {8: (8, 1), 16: (16, 1), 32: (32, 1), 64: (8, 8), 128: (16, 8), 256: (16, 16), 512: (32, 16), 1024: (32, 32)}
 
 
 def twiddle(x, y, idx, eighth_as_others):
@@ -91,12 +92,11 @@ def test_rfft_bits(gpu, n):
 @pytest.mark.parametrize("n,deconv", [(8, False), (16, True), (32, False), (64, True), (128, False), (256, False),
                                       (512, True)])
 def test_power_digits(gpu, n, deconv):
-    """Below 64 points the whole column is one stage.  The float64 sums of at
-    most 2e6 positive terms, in any order, agree to 1e-12."""
+    """Float64 sums of at most 2e6 positive terms, in any order, agree to 1e-12."""
     banner(f"power digits n={n} deconv={deconv}")
     w = inputs.scaled(inputs.MEDIUM, n, 8)
     line, d = line_mesh(n)
-    x = column(line, STAGES[n] if n >= 64 else (n, 1)).astype(np.complex128)
+    x = column(line, STAGES[n]).astype(np.complex128)
     f = np.fft.fftfreq(n, 1 / n)
     fy, fz = f[:, None], np.arange(n // 2 + 1)[None, :]
     win = np.sinc(f / n) ** 2
